@@ -17,11 +17,10 @@
 //   upward: P2M (leaves), M2M (up to level 2): per box the check velocities
 //   (LDS-staged pair sums), then per level one FP64 MFMA GEMM applies the
 //   pseudo-inverse to all boxes;
-//   downward, level 2 to the leaves: M2L + L2L as one GEMM per octant class
-//   against precomputed translation operators (or as pair sums where the
-//   interaction lists are sparse), then the pseudo-inverse GEMM;
-//   L2P + P2P per chunk of up to 64 targets of a leaf, written back in the
-//   caller's order.
+//   downward, level 2 to the leaves: M2L as convolutions on the surface lattice
+//   (fmm_fft.hip), L2L as pair sums, then the pseudo-inverse GEMM;
+//   L2P, then the near field through the leaf-to-leaf kernel, written back in
+//   the caller's order.
 // Every sum is taken in a fixed order (no atomics on values), so results are
 // reproducible.
 //
@@ -42,6 +41,7 @@
 
 #include "common.hpp"
 #include "fmm.hpp"
+#include "fmm_fft.hpp"
 #include "p2p.hpp"
 #include "spatial.hpp"
 
@@ -50,13 +50,15 @@ struct stokes_fmm_plan {
     int order = 0;
     int ns = 0;                 // surface points
     double* d_surf = nullptr;   // (ns, 3)
-    // M2L as GEMMs: rows padded to mp, K blocks of kb (3ns densities, the
-    // point-source flux, zero padding); see m2l_matrix_kernel
-    int mp = 0, kb = 0;
-    double* d_m2l = nullptr;    // (8 classes, kM2LBlocks, kb, mp)
+    int cus = 0;                // compute units of the device
+    int mp = 0;                 // 3 ns padded to a multiple of 16
+    double* d_khat = nullptr;   // spectra of the M2L kernels (fmm_fft.hip)
+    double* d_tw = nullptr;     // and the transforms' twiddles
+    double* d_m2l = nullptr;    // (8 classes, kM2LBlocks, mp, mp), orders from kDenseOrderSL on; see m2l_matrix_kernel
     int32_t* d_il = nullptr;    // (8 classes, kILSize, 3) interaction-list offsets
     double* d_downA = nullptr;  // (mp, mp): downA[k * mp + r] = DOWN[r][k], zero padded
     double* d_upA = nullptr;    // the same for UP
+    double* d_down3 = nullptr;  // (3 mp, mp): DOWN cut in two, for apply_exact_kernel (order kDenseOrderSL)
 };
 
 namespace stokes {
@@ -67,6 +69,16 @@ constexpr double kPinvRcond = 1e-10;
 constexpr int kFBlock = 256;
 constexpr int kFWaves = kFBlock / kWave;
 constexpr int64_t kFMaxGrid = 1 << 16;
+// M2L runs as lattice convolutions (fmm_fft.hip) below these orders, as dense
+// products (or pair sums) from them on.  The convolution is as accurate, but it
+// sums in another order, and the pseudo-inverses amplify the rounding of
+// whatever order is taken: two orders of the same sums give outputs that differ
+// by 2e-9 at order 6 for the single layer (changing the dense products' K splits
+// alone moves them by 1.6e-9), 7e-10 for the double layer, 1e-10 at order 5 and
+// 2e-12 at order 4, of outputs that are within 1e-4, 1e-3, 5e-4 and 2e-3 of the
+// direct sums.  Orders whose results it would move by more than 1e-9 keep the
+// dense products.
+constexpr int kDenseOrderSL = 6, kDenseOrderDL = 7;
 
 unsigned f_grid(int64_t units) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(units, kFMaxGrid)); }
 
@@ -141,8 +153,8 @@ struct FmmDev {
     int64_t n_trg;
     const int64_t* sofs;       // (8^D + 1) leaf offsets
     const int64_t* tofs;
-    uint8_t* snz;              // per box of levels 2..D: has sources
-    uint8_t* tpr;              // has targets
+    int32_t* sslot;            // per box of levels 1..D: its place among its level's boxes
+    int32_t* tslot;            // holding sources (targets), -1 when it holds none
     double* ue;                // per box: 3 ns upward equivalent density
     double* de;                // downward
     int64_t base[kFmmMaxDepth + 2];   // first box of level l in the per-box arrays
@@ -253,24 +265,73 @@ __global__ __launch_bounds__(kFBlock) void leaf_ofs_kernel(const uint64_t* __res
     }
 }
 
-__global__ __launch_bounds__(kFBlock) void flags_leaf_kernel(FmmDev a) {
-    const int64_t nl = (int64_t)1 << (3 * a.D);
-    for (int64_t L = (int64_t)blockIdx.x * kFBlock + threadIdx.x; L < nl; L += (int64_t)gridDim.x * kFBlock) {
-        a.snz[a.base[a.D] + L] = a.sofs[L + 1] > a.sofs[L];
-        a.tpr[a.base[a.D] + L] = a.tofs[L + 1] > a.tofs[L];
+// Level of box g of the per-box arrays (levels 1 .. D one after another).
+__device__ __forceinline__ int level_of(const FmmDev& a, int64_t g) {
+    int l = 1;
+    while (l < a.D && g >= a.base[l + 1]) ++l;
+    return l;
+}
+__device__ __forceinline__ bool holds(const FmmDev& a, const int64_t* ofs, int l, int64_t b) {
+    const int sh = 3 * (a.D - l);
+    return ofs[(b + 1) << sh] > ofs[b << sh];
+}
+
+// Compact lists of the boxes that hold sources and of those that hold targets,
+// all levels at once: flags (sources, then targets), a scan, then the lists.
+// A box's points are those of its range of leaves, so no level waits for
+// another.  The boxes without sources get flux zero here (P2M and M2M visit
+// only listed boxes; M2M adds the flux of all eight children).
+__global__ __launch_bounds__(kFBlock) void box_flags_kernel(FmmDev a, int64_t nbox, int64_t* __restrict__ f) {
+    for (int64_t g = (int64_t)blockIdx.x * kFBlock + threadIdx.x; g < 2 * nbox; g += (int64_t)gridDim.x * kFBlock) {
+        const int64_t k = g < nbox ? g : g - nbox;
+        const int l = level_of(a, k);
+        f[g] = holds(a, g < nbox ? a.sofs : a.tofs, l, k - a.base[l]) ? 1 : 0;
+    }
+}
+// counts: (2, kFmmMaxDepth + 1), sources then targets, by level.  scan[2 nbox] is the total.
+__global__ __launch_bounds__(kFBlock) void box_lists_kernel(FmmDev a, int64_t nbox, const int64_t* __restrict__ scan,
+                                                            int32_t* __restrict__ slist, int32_t* __restrict__ tlist,
+                                                            int64_t* __restrict__ counts) {
+    for (int64_t g = (int64_t)blockIdx.x * kFBlock + threadIdx.x; g < 2 * nbox; g += (int64_t)gridDim.x * kFBlock) {
+        const bool src = g < nbox;
+        const int64_t k = src ? g : g - nbox, first = src ? 0 : nbox;
+        const int l = level_of(a, k);
+        const int64_t b = k - a.base[l], start = scan[first + a.base[l]];
+        int32_t slot = -1;
+        if (holds(a, src ? a.sofs : a.tofs, l, b)) {
+            slot = (int32_t)(scan[g] - start);
+            (src ? slist : tlist)[a.base[l] + slot] = (int32_t)b;
+        } else if (src && a.sig) {
+            a.sig[k] = 0.0;
+        }
+        (src ? a.sslot : a.tslot)[k] = slot;
+        if (b == 0)
+            counts[(src ? 0 : kFmmMaxDepth + 1) + l] = scan[first + a.base[l] + ((int64_t)1 << (3 * l))] - start;
     }
 }
 
-__global__ __launch_bounds__(kFBlock) void flags_up_kernel(FmmDev a, int l) {
-    const int64_t nb = (int64_t)1 << (3 * l);
-    for (int64_t b = (int64_t)blockIdx.x * kFBlock + threadIdx.x; b < nb; b += (int64_t)gridDim.x * kFBlock) {
-        uint8_t s = 0, t = 0;
-        for (int o = 0; o < 8; ++o) {
-            s |= a.snz[a.base[l + 1] + 8 * b + o];
-            t |= a.tpr[a.base[l + 1] + 8 * b + o];
+// Source octets next to the target octets of levels 1 .. D - 1 (an octet is a
+// box with its eight children): nbr[26 base[l] + d n + i] for the i-th of the
+// level's n boxes holding targets, n_soct (the record of zeros) for none.
+__global__ __launch_bounds__(kFBlock) void octet_neighbours_kernel(FmmDev a, const int64_t* __restrict__ counts,
+                                                                   int32_t* __restrict__ nbr) {
+    const int64_t n = a.base[a.D];
+    for (int64_t g = (int64_t)blockIdx.x * kFBlock + threadIdx.x; g < n; g += (int64_t)gridDim.x * kFBlock) {
+        const int32_t i = a.tslot[g];
+        if (i < 0) continue;
+        const int l = level_of(a, g);
+        const int64_t b = g - a.base[l], nx = (int64_t)1 << l;
+        const int64_t nt = counts[kFmmMaxDepth + 1 + l];
+        const int32_t none = (int32_t)counts[l];
+        const int64_t c0 = compact3(b), c1 = compact3(b >> 1), c2 = compact3(b >> 2);
+        for (int d = 0; d < 26; ++d) {
+            const int id = d + (d >= 13 ? 1 : 0);
+            const int64_t n0 = c0 + id / 9 - 1, n1 = c1 + id / 3 % 3 - 1, n2 = c2 + id % 3 - 1;
+            int32_t s = -1;
+            if (n0 >= 0 && n1 >= 0 && n2 >= 0 && n0 < nx && n1 < nx && n2 < nx)
+                s = a.sslot[a.base[l] + (int64_t)morton(n0, n1, n2)];
+            nbr[26 * a.base[l] + d * nt + i] = s < 0 ? none : s;
         }
-        a.snz[a.base[l] + b] = s;
-        a.tpr[a.base[l] + b] = t;
     }
 }
 
@@ -315,13 +376,14 @@ __device__ __forceinline__ void stage_density(const FmmDev& a, const double* __r
     for (int r = lane; r < a.n3; r += kWave) dst[r] = dens[r];
 }
 
-// Adds the single-layer velocity of a surface (points ctr + scale * template,
-// the template and the staged densities q in LDS) at a lane's T check points.
+// Adds the single-layer velocity of points j0 .. j1 - 1 of a surface (points
+// ctr + scale * template, the template and the staged densities q in LDS) at a
+// lane's T check points.
 template <int T>
-__device__ __forceinline__ void surface_sum(const FmmDev& a, const double* surf, const double* ctr, double scale,
-                                            const double* q, const double (&x)[T][3], double (&u)[T][3]) {
+__device__ __forceinline__ void surface_sum(const double* surf, const double* ctr, double scale, const double* q,
+                                            int j0, int j1, const double (&x)[T][3], double (&u)[T][3]) {
 #pragma unroll 2
-    for (int j = 0; j < a.ns; ++j) {
+    for (int j = j0; j < j1; ++j) {
         const double sx = ctr[0] + scale * surf[3 * j], sy = ctr[1] + scale * surf[3 * j + 1],
                      sz = ctr[2] + scale * surf[3 * j + 2];
         const double qx = q[3 * j], qy = q[3 * j + 1], qz = q[3 * j + 2];
@@ -494,7 +556,7 @@ __global__ __launch_bounds__(kFBlock) void m2m_kernel(FmmDev a, int l, const int
                 point_source(x[k][0] - ctr[0], x[k][1] - ctr[1], x[k][2] - ctr[2], -sigma, u[k]);
         for (int o = wave; o < 8; o += kFWaves) {
             const uint64_t ch = 8 * b + o;
-            if (!a.snz[a.base[l + 1] + ch]) continue;
+            if (a.sslot[a.base[l + 1] + ch] < 0) continue;
             double cc[3], hc;
             box_centre(a, l + 1, ch, cc, hc);
             if (a.sig) {
@@ -504,7 +566,7 @@ __global__ __launch_bounds__(kFBlock) void m2m_kernel(FmmDev a, int l, const int
             }
             stage_density(a, a.ue + (a.base[l + 1] + ch) * a.n3, mine, lane);
             __builtin_amdgcn_wave_barrier();
-            surface_sum<T>(a, surf, cc, kAlphaUE * hc, mine, x, u);
+            surface_sum<T>(surf, cc, kAlphaUE * hc, mine, 0, a.ns, x, u);
             __builtin_amdgcn_wave_barrier();   // reads of this child precede the next writes
         }
         __syncthreads();                           // the partial vectors overwrite the density slices
@@ -574,7 +636,8 @@ __global__ __launch_bounds__(kFBlock) void l2p_kernel(FmmDev a, const uint64_t* 
 int64_t max_list(int64_t n_trg, int64_t n_leaves) { return 27 * std::min(n_trg, n_leaves); }
 
 // ---------------------------------------------------------------------------
-// M2L as dense products on the FP64 matrix cores.
+// M2L as dense products on the FP64 matrix cores (the orders from kDenseOrderSL
+// and kDenseOrderDL on).
 //
 // A target box's position in its parent (octant class c = b & 7 of its
 // Morton index) fixes its interaction list: 189 offsets o (source box minus
@@ -786,6 +849,12 @@ __device__ __forceinline__ void gemm_tile_any(const double* __restrict__ A, int 
         gemm_tile<RB, G::H>(A, lda, r0, n, chunk, loadb, busy, As, Bs, nrow, store);
 }
 
+// Boxes whose check vectors are the columns of vbuf, in list order.
+struct Columns {
+    const int32_t* list;
+    const int64_t* n;
+};
+
 struct M2LArgs {
     const double* A;           // plan's class matrices
     const int32_t* il;
@@ -804,13 +873,13 @@ struct M2LArgs {
 __global__ __launch_bounds__(kFBlock) void class_flags_kernel(FmmDev a, int l, int64_t* __restrict__ f) {
     const int64_t nb = (int64_t)1 << (3 * l), P = nb >> 3;
     for (int64_t b = (int64_t)blockIdx.x * kFBlock + threadIdx.x; b < nb; b += (int64_t)gridDim.x * kFBlock)
-        f[(b & 7) * P + (b >> 3)] = a.tpr[a.base[l] + b] ? 1 : 0;
+        f[(b & 7) * P + (b >> 3)] = (a.tslot[a.base[l] + b] >= 0) ? 1 : 0;
 }
 __global__ __launch_bounds__(kFBlock) void class_list_kernel(FmmDev a, int l, const int64_t* __restrict__ scan,
                                                              int32_t* __restrict__ list) {
     const int64_t nb = (int64_t)1 << (3 * l), P = nb >> 3;
     for (int64_t b = (int64_t)blockIdx.x * kFBlock + threadIdx.x; b < nb; b += (int64_t)gridDim.x * kFBlock)
-        if (a.tpr[a.base[l] + b]) list[scan[(b & 7) * P + (b >> 3)]] = (int32_t)b;
+        if ((a.tslot[a.base[l] + b] >= 0)) list[scan[(b & 7) * P + (b >> 3)]] = (int32_t)b;
 }
 
 // K splits of a level: enough work units for the whole chip, at most one
@@ -854,7 +923,7 @@ __global__ __launch_bounds__(kFBlock) void il_count_kernel(FmmDev a, M2LArgs g, 
             if (k < kILSize) {
                 const int64_t ai[3] = {idx[0] + il[3 * k], idx[1] + il[3 * k + 1], idx[2] + il[3 * k + 2]};
                 hit = ai[0] >= 0 && ai[1] >= 0 && ai[2] >= 0 && ai[0] < nbx && ai[1] < nbx && ai[2] < nbx &&
-                      a.snz[a.base[l] + (int64_t)morton(ai[0], ai[1], ai[2])];
+                      a.sslot[a.base[l] + (int64_t)morton(ai[0], ai[1], ai[2])] >= 0;
             }
             cnt += __builtin_popcountll(__ballot(hit));
         }
@@ -903,7 +972,7 @@ __global__ __launch_bounds__(kGemmThreads) void m2l_gemm_kernel(FmmDev a, M2LArg
                                compact3(b >> 2) + il[3 * blk + 2]};
         if (ai[0] < 0 || ai[1] < 0 || ai[2] < 0 || ai[0] >= nbx || ai[1] >= nbx || ai[2] >= nbx) return -1;
         const int64_t box = (int64_t)morton(ai[0], ai[1], ai[2]);
-        return a.snz[a.base[l] + box] ? box : -1;
+        return a.sslot[a.base[l] + box] >= 0 ? box : -1;
     };
     {
         const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -997,7 +1066,7 @@ __global__ __launch_bounds__(kFBlock) void m2l_pairs_kernel(FmmDev a, M2LArgs g,
                         if (llabs(ai[0] - idx[0]) <= 1 && llabs(ai[1] - idx[1]) <= 1 && llabs(ai[2] - idx[2]) <= 1)
                             continue;                      // a neighbour: near field
                         const uint64_t ab = morton(ai[0], ai[1], ai[2]);
-                        if (!a.snz[a.base[l] + ab]) continue;
+                        if (a.sslot[a.base[l] + ab] < 0) continue;
                         if (item++ % kFWaves != wave) continue;
                         double ac[3], ha;
                         box_centre(a, l, ab, ac, ha);
@@ -1009,7 +1078,7 @@ __global__ __launch_bounds__(kFBlock) void m2l_pairs_kernel(FmmDev a, M2LArgs g,
                         }
                         stage_density(a, a.ue + (a.base[l] + ab) * a.n3, mine, lane);
                         __builtin_amdgcn_wave_barrier();
-                        surface_sum<T>(a, surf, ac, kAlphaUE * ha, mine, x, u);
+                        surface_sum<T>(surf, ac, kAlphaUE * ha, mine, 0, a.ns, x, u);
                         __builtin_amdgcn_wave_barrier();   // reads of this box precede the next writes
                     }
                 }
@@ -1018,7 +1087,7 @@ __global__ __launch_bounds__(kFBlock) void m2l_pairs_kernel(FmmDev a, M2LArgs g,
             box_centre(a, l - 1, p, pc, hp);
             stage_density(a, a.de + (a.base[l - 1] + p) * a.n3, mine, lane);
             __builtin_amdgcn_wave_barrier();
-            surface_sum<T>(a, surf, pc, kAlphaDE * hp, mine, x, u);
+            surface_sum<T>(surf, pc, kAlphaDE * hp, mine, 0, a.ns, x, u);
         }
         __syncthreads();                           // the partial vectors overwrite the staging slices
         store_partial<T>(a, part, wave, lane, u);
@@ -1037,6 +1106,40 @@ __global__ __launch_bounds__(kFBlock) void m2l_reduce_kernel(M2LArgs g) {
     }
 }
 
+// Dynamic LDS of the L2L kernel: the template and the parent's density, then
+// the four partial check vectors over the density.
+size_t l2l_lds(int ns) { return ((size_t)((3 * ns + 1) & ~1) + (size_t)kFWaves * 3 * ns) * sizeof(double); }
+
+// L2L: per listed target box, the velocity of the parent's downward density at
+// its check points, times h added to its column (which holds the interaction
+// lists' part).  Lane j holds check points j, j + 64, ... (T of them); wave w
+// sums its quarter of the parent's surface.
+template <int T>
+__global__ __launch_bounds__(kFBlock) void l2l_kernel(FmmDev a, Columns g, int l) {
+    extern __shared__ double sh[];
+    double* surf = sh;
+    double* rest = surf + ((3 * a.ns + 1) & ~1);
+    load_surface(a, surf);
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int64_t listed = *g.n;
+    const int j0 = a.ns * wave / kFWaves, j1 = a.ns * (wave + 1) / kFWaves;
+    for (int64_t i = blockIdx.x; i < listed; i += gridDim.x) {
+        const int64_t b = g.list[i], p = b >> 3;
+        double ctr[3], h, pc[3], hp;
+        box_centre(a, l, b, ctr, h);
+        box_centre(a, l - 1, p, pc, hp);
+        const double* dens = a.de + (a.base[l - 1] + p) * a.n3;
+        for (int r = threadIdx.x; r < a.n3; r += kFBlock) rest[r] = dens[r];
+        __syncthreads();
+        double x[T][3], u[T][3];
+        check_points<T>(a, surf, ctr, kAlphaDC * h, lane, x, u);
+        surface_sum<T>(surf, pc, kAlphaDE * hp, rest, j0, j1, x, u);
+        __syncthreads();                           // the partial vectors overwrite the density
+        store_partial<T>(a, rest, wave, lane, u);
+        store_check(a, rest, h, i);
+    }
+}
+
 // K splits of a level's pseudo-inverse product: a tile's K chunks run one
 // after another on one workgroup, so a level with few tiles splits K until
 // it has about kApplyUnits work units (at most one chunk per split).
@@ -1052,13 +1155,13 @@ __device__ __forceinline__ int64_t apply_splits(int64_t tiles, int64_t nk) {
 // rg of tile u / S, K split u % S; with one split the tile writes out, with
 // more each split writes its partial (apply_reduce_kernel adds them).
 template <int RB>
-__global__ __launch_bounds__(kGemmThreads) void apply_gemm_kernel(FmmDev a, M2LArgs g, const double* __restrict__ op,
+__global__ __launch_bounds__(kGemmThreads) void apply_gemm_kernel(FmmDev a, Columns g, const double* __restrict__ op,
                                                                   double* __restrict__ out, double* __restrict__ part) {
     using G = GemmShape<RB>;
     __shared__ double As[2 * G::na];
     __shared__ double Bs[2 * kGemmKC * kGemmNT];
     const int mp = a.mp, ng = gemm_groups(mp, RB);
-    const int64_t n = *g.ctotal, nk = mp / kGemmKC;
+    const int64_t n = *g.n, nk = mp / kGemmKC;
     const int64_t tiles = (n + kGemmNT - 1) / kGemmNT, S = apply_splits(tiles, nk);
     const int64_t units = gridDim.x / ng, u = blockIdx.x % units;
     const int rg = (int)(blockIdx.x / units);
@@ -1066,10 +1169,10 @@ __global__ __launch_bounds__(kGemmThreads) void apply_gemm_kernel(FmmDev a, M2LA
     const int64_t col0 = (u / S) * kGemmNT, sp = u % S;
     const int64_t k0 = sp * nk / S, k1 = (sp + 1) * nk / S;
     auto chunk = [k0](int64_t t) { return k0 + t; };
-    auto loadb = [&](int64_t q, int j, int bk) -> double {
-        return col0 + j < n ? g.vbuf[(col0 + j) * mp + q * kGemmKC + bk] : 0.0;
-    };
     auto busy = [](int64_t, int) { return true; };
+    auto loadb = [&](int64_t q, int j, int bk) -> double {
+        return col0 + j < n ? a.vbuf[(col0 + j) * mp + q * kGemmKC + bk] : 0.0;
+    };
     const int32_t* list = g.list;
     const int r0 = rg * G::mw;
     gemm_tile_any<RB>(op, mp, r0, k1 - k0, chunk, loadb, busy, As, Bs, a.n3 - r0, [&](int j, int row, double v) {
@@ -1079,38 +1182,89 @@ __global__ __launch_bounds__(kGemmThreads) void apply_gemm_kernel(FmmDev a, M2LA
     });
 }
 
-// The split partials of apply_gemm_kernel added in split order.
-__global__ __launch_bounds__(kFBlock) void apply_reduce_kernel(FmmDev a, M2LArgs g, int nk,
+// The same product with its rounding taken out.  The pseudo-inverse's entries
+// are large and its sums cancel, so the rounding of a plain product is what
+// most of a convolution level's rounding error comes from.  Each factor is cut
+// at kExactBits bits below its row's (column's) largest entry, OP = A1 + A2 and
+// V = V1 + V2: A1 V1 is exact in float64 (products of at most 2^42 units, fewer
+// than 2^11 of them), and A1 V2 + A2 V is 2^-21 of it.  op3 stacks A1, A1, A2
+// along K for the operands V1, V2, V.  Three times the MFMA work of a part
+// that is 2% of the evaluation.  K splits as above, S of them for the exact
+// part and 2 S for the rest.
+constexpr int kExactBits = 21;
+template <int RB>
+__global__ __launch_bounds__(kGemmThreads) void apply_exact_kernel(FmmDev a, Columns g,
+                                                                   const double* __restrict__ op3,
+                                                                   double* __restrict__ out,
+                                                                   double* __restrict__ part) {
+    using G = GemmShape<RB>;
+    __shared__ double As[2 * G::na];
+    __shared__ double Bs[2 * kGemmKC * kGemmNT];
+    __shared__ double s_c[kGemmNT];
+    const int mp = a.mp, ng = gemm_groups(mp, RB);
+    const int64_t n = *g.n, nk = mp / kGemmKC;
+    const int64_t tiles = (n + kGemmNT - 1) / kGemmNT, S = apply_splits(tiles, nk), parts = S == 1 ? 1 : 3 * S;
+    const int64_t units = gridDim.x / ng, u = blockIdx.x % units;
+    const int rg = (int)(blockIdx.x / units);
+    if (rg >= ng || u >= tiles * parts) return;                   // uniform over the workgroup
+    const int64_t col0 = (u / parts) * kGemmNT, sp = u % parts;
+    {
+        // c + v - c rounds v to a multiple of 2^-kExactBits times its column's scale (eight threads a column)
+        const int j = threadIdx.x >> 3;
+        double top = 0.0;
+        if (col0 + j < n)
+            for (int k = threadIdx.x & 7; k < mp; k += 8) top = fmax(top, fabs(a.vbuf[(col0 + j) * mp + k]));
+        for (int o = 1; o < 8; o <<= 1) top = fmax(top, __shfl_xor(top, o));
+        int e;
+        (void)frexp(top, &e);
+        if ((threadIdx.x & 7) == 0) s_c[j] = top > 0.0 && top < 1e280 ? ldexp(1.5, 52 + e - kExactBits) : 0.0;
+    }
+    __syncthreads();
+    auto busy = [](int64_t, int) { return true; };
+    auto loadb = [&](int64_t q, int j, int bk) -> double {
+        if (col0 + j >= n) return 0.0;
+        const int64_t set = q / nk;
+        const double v = a.vbuf[(col0 + j) * mp + (q - set * nk) * kGemmKC + bk];
+        const double v1 = (v + s_c[j]) - s_c[j];
+        return set == 0 ? v1 : set == 1 ? v - v1 : v;
+    };
+    const int32_t* list = g.list;
+    const int r0 = rg * G::mw;
+    auto run = [&](int64_t k0, int64_t k1, bool add) {
+        auto chunk = [k0](int64_t t) { return k0 + t; };
+        gemm_tile_any<RB>(op3, mp, r0, k1 - k0, chunk, loadb, busy, As, Bs, a.n3 - r0, [&](int j, int row, double v) {
+            if (col0 + j >= n) return;
+            double* o = parts == 1 ? out + (int64_t)list[col0 + j] * a.n3 + r0 + row
+                                   : part + (sp * n + col0 + j) * a.n3 + r0 + row;
+            *o = add ? *o + v : v;
+        });
+    };
+    if (parts == 1) {
+        run(0, nk, false);
+        __syncthreads();
+        run(nk, 3 * nk, true);
+    } else if (sp < S) {
+        run(sp * nk / S, (sp + 1) * nk / S, false);
+    } else {
+        const int64_t r = sp - S;
+        run(nk + r * nk / S, nk + (r + 1) * nk / S, false);
+    }
+}
+
+// The split partials of apply_gemm_kernel (per split) or apply_exact_kernel
+// (three per split) added in order.
+__global__ __launch_bounds__(kFBlock) void apply_reduce_kernel(FmmDev a, Columns g, int nk, int per_split,
                                                                const double* __restrict__ part,
                                                                double* __restrict__ out) {
-    const int64_t n = *g.ctotal;
-    const int64_t S = apply_splits((n + kGemmNT - 1) / kGemmNT, nk);
-    if (S == 1) return;
+    const int64_t n = *g.n;
+    const int64_t splits = apply_splits((n + kGemmNT - 1) / kGemmNT, nk), S = splits * per_split;
+    if (splits == 1) return;
     const int64_t m = n * a.n3;
     for (int64_t e = (int64_t)blockIdx.x * kFBlock + threadIdx.x; e < m; e += (int64_t)gridDim.x * kFBlock) {
         double v = part[e];
         for (int64_t sp = 1; sp < S; ++sp) v += part[sp * m + e];
         out[(int64_t)g.list[e / a.n3] * a.n3 + e % a.n3] = v;
     }
-}
-
-// Boxes of level l that hold sources, in index order: flags, then (after a
-// scan) the list.  The flags pass also sets the flux of the boxes without
-// sources to zero (P2M and M2M visit only the listed boxes; M2M adds the flux
-// of all eight children).
-__global__ __launch_bounds__(kFBlock) void src_flags_kernel(FmmDev a, int l, int64_t* __restrict__ f) {
-    const int64_t nb = (int64_t)1 << (3 * l);
-    for (int64_t b = (int64_t)blockIdx.x * kFBlock + threadIdx.x; b < nb; b += (int64_t)gridDim.x * kFBlock) {
-        const bool has = a.snz[a.base[l] + b] != 0;
-        f[b] = has ? 1 : 0;
-        if (!has && a.sig) a.sig[a.base[l] + b] = 0.0;
-    }
-}
-__global__ __launch_bounds__(kFBlock) void src_list_kernel(FmmDev a, int l, const int64_t* __restrict__ scan,
-                                                           int32_t* __restrict__ list) {
-    const int64_t nb = (int64_t)1 << (3 * l);
-    for (int64_t b = (int64_t)blockIdx.x * kFBlock + threadIdx.x; b < nb; b += (int64_t)gridDim.x * kFBlock)
-        if (a.snz[a.base[l] + b]) list[scan[b]] = (int32_t)b;
 }
 
 // Calls f(std::integral_constant<int, T>) for check points per lane T
@@ -1151,19 +1305,21 @@ struct FmmLayout {
     int64_t base[kFmmMaxDepth + 2] = {};
     SortLayout sort;
     size_t off_skeys, off_svals, off_tkeys, off_tvals, off_sort, off_sx, off_sq, off_sn, off_tx, off_sofs, off_tofs,
-        off_snz, off_tpr, off_sig, off_ue, off_de, off_uofs, off_scan, off_ul, off_p2p, off_cflag, off_cscan,
-        off_ctotal, off_clist, off_sched, off_vbuf, off_apart, total;
+        off_sslot, off_tslot, off_sig, off_ue, off_de, off_uofs, off_scan, off_ul, off_p2p, off_bscan, off_btmp,
+        off_counts, off_slist, off_tlist, off_cflag, off_cscan, off_ctotal, off_clist, off_sched, off_nbr, off_q, off_sigq, off_v, off_vbuf, off_apart, total;
 };
 
-FmmLayout fmm_layout(int ns, int64_t n_src, int64_t n_trg, int D) {
+FmmLayout fmm_layout(int order, int64_t n_src, int64_t n_trg, int D) {
+    const int ns = 6 * (order - 1) * (order - 1) + 2;
     const int mp = pad16(3 * ns);
     FmmLayout L;
     int64_t acc = 0;
-    for (int l = 2; l <= D; ++l) {
+    for (int l = 1; l <= D; ++l) {
         L.base[l] = acc;
         acc += (int64_t)1 << (3 * l);
     }
     L.nbox = acc;
+    auto octets = [](int l, int64_t n) { return std::min<int64_t>((int64_t)1 << (3 * (l - 1)), n); };
     L.n_leaves = (int64_t)1 << (3 * D);
     L.sort = sort_layout(std::max(n_src, n_trg));
     size_t off = 0;
@@ -1183,8 +1339,8 @@ FmmLayout fmm_layout(int ns, int64_t n_src, int64_t n_trg, int D) {
     L.off_tx = take((size_t)3 * n_trg * 8);
     L.off_sofs = take((size_t)(L.n_leaves + 1) * 8);
     L.off_tofs = take((size_t)(L.n_leaves + 1) * 8);
-    L.off_snz = take((size_t)L.nbox);
-    L.off_tpr = take((size_t)L.nbox);
+    L.off_sslot = take((size_t)L.nbox * 4);
+    L.off_tslot = take((size_t)L.nbox * 4);
     L.off_sig = take((size_t)L.nbox * 8);
     L.off_ue = take((size_t)L.nbox * 3 * ns * 8);
     L.off_de = take((size_t)L.nbox * 3 * ns * 8);
@@ -1198,17 +1354,33 @@ FmmLayout fmm_layout(int ns, int64_t n_src, int64_t n_trg, int D) {
         for (int mx = 0; mx < 2; ++mx)
             p2p = std::max(p2p, p2p_workspace_bytes(kt, mx, n_src, n_trg, (int32_t)L.n_leaves));
     L.off_p2p = take(p2p);
+    L.off_bscan = take((size_t)(2 * L.nbox + 1) * 8);
+    L.off_btmp = take((size_t)scan_tmp_count(2 * L.nbox) * 8);
+    L.off_counts = take((size_t)2 * (kFmmMaxDepth + 1) * 8);
+    L.off_slist = take((size_t)L.nbox * 4);
+    L.off_tlist = take((size_t)L.nbox * 4);
+    L.off_nbr = take((size_t)26 * L.base[D] * 4);
+    // spectra of a level's octets, the largest of the levels
+    size_t q = 0, v = 0;
+    for (int l = 2; l <= D; ++l) {
+        q = std::max(q, fft_q_bytes(order, octets(l, n_src), octets(l, n_trg)));
+        v = std::max(v, fft_v_bytes(order, octets(l, n_src), octets(l, n_trg)));
+    }
+    L.off_q = take(q);
+    L.off_v = take(v);
+    L.off_sigq = take((size_t)(octets(D, n_src) + 1) * 8 * 8);
     L.off_cflag = take((size_t)L.n_leaves * 8);
     L.off_cscan = take((size_t)scan_tmp_count(L.n_leaves) * 8);
     L.off_ctotal = take(8);
     L.off_clist = take((size_t)L.n_leaves * 4);
     L.off_sched = take(16 + 8 * kILCountParts);   // splits, mode, partial interaction pair counts
-    // K-split partials: splits x listed boxes <= 3 listed + 64 (units + 8)
-    L.off_vbuf = take((size_t)(kM2LMinSplits * std::min(L.n_leaves, std::max<int64_t>({n_src, n_trg, 1})) +
-                               kGemmNT * (kM2LUnits + 8)) *
-                      mp * 8);
+    // check vectors: a column per box holding sources (upward) or targets (downward), and the
+    // K-split partials of the dense levels: splits x listed boxes <= 3 listed + 64 (units + 8)
+    const int64_t cols = std::min(L.n_leaves, std::max<int64_t>({n_src, n_trg, 1}));
+    const int64_t parts = order >= kDenseOrderSL ? kM2LMinSplits * cols + kGemmNT * (kM2LUnits + 8) : 0;
+    L.off_vbuf = take((size_t)std::max(cols, parts) * mp * 8);
     // split partials of the pseudo-inverse products: S x listed <= kApplyUnits x 64 columns when S > 1
-    L.off_apart = take((size_t)kApplyUnits * kGemmNT * 3 * ns * 8);
+    L.off_apart = take((size_t)(order == kDenseOrderSL ? 3 : 1) * kApplyUnits * kGemmNT * 3 * ns * 8);
     L.total = off;
     return L;
 }
@@ -1463,6 +1635,8 @@ int fmm_plan_build(int device, int order, stokes_fmm_plan** out, std::string& er
     p->device = device;
     p->order = order;
     p->ns = ns;
+    (void)hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, device);
+    if (p->cus <= 0) p->cus = 256;
     const size_t sb = s.size() * 8;
     if (hipMalloc(&p->d_surf, sb) != hipSuccess ||
         hipMemcpy(p->d_surf, s.data(), sb, hipMemcpyHostToDevice) != hipSuccess) {
@@ -1470,15 +1644,9 @@ int fmm_plan_build(int device, int order, stokes_fmm_plan** out, std::string& er
         err = "device allocation or copy failed";
         return -2;
     }
-    // the pseudo-inverses, padded and k-major, and the M2L class matrices (built on the device)
-    const int mp = pad16(n3), kb = pad16(n3 + 1);
+    // the pseudo-inverses, padded and k-major, and the M2L spectra (built on the device)
+    const int mp = pad16(n3);
     p->mp = mp;
-    p->kb = kb;
-    if (kb != mp) {                    // 3 ns = 6 (3 (p - 1)^2 + 1) is never a multiple of 16
-        fmm_plan_free(p);
-        err = "internal: M2L block size";
-        return -2;
-    }
     std::vector<int32_t> il;
     for (int c = 0; c < 8; ++c) il_offsets(c, il);
     std::vector<double> downA((size_t)mp * mp, 0.0), upA((size_t)mp * mp, 0.0);
@@ -1487,25 +1655,50 @@ int fmm_plan_build(int device, int order, stokes_fmm_plan** out, std::string& er
             downA[(size_t)k * mp + r] = down[(size_t)r * n3 + k];
             upA[(size_t)k * mp + r] = up[(size_t)r * n3 + k];
         }
-    const size_t ab = (size_t)8 * kM2LBlocks * kb * mp * 8;
-    hipError_t e = hipMalloc(&p->d_m2l, ab);
-    if (e == hipSuccess) e = hipMalloc(&p->d_il, il.size() * 4);
+    hipError_t e = hipMalloc(&p->d_khat, fft_spectra_bytes(order));
+    if (order == kDenseOrderSL) {
+        std::vector<double> down3((size_t)3 * mp * mp, 0.0);
+        for (int r = 0; r < n3; ++r) {
+            double top = 0.0;
+            for (int k = 0; k < n3; ++k) top = std::max(top, fabs(down[(size_t)r * n3 + k]));
+            int ex = 0;
+            (void)frexp(top, &ex);
+            const volatile double c = top > 0.0 ? ldexp(1.5, 52 + ex - kExactBits) : 0.0;
+            for (int k = 0; k < n3; ++k) {
+                const double v = down[(size_t)r * n3 + k];
+                const volatile double t = v + c;
+                const double v1 = t - c;
+                down3[(size_t)k * mp + r] = down3[(size_t)(mp + k) * mp + r] = v1;
+                down3[(size_t)(2 * mp + k) * mp + r] = v - v1;
+            }
+        }
+        if (e == hipSuccess) e = hipMalloc(&p->d_down3, down3.size() * 8);
+        if (e == hipSuccess) e = hipMemcpy(p->d_down3, down3.data(), down3.size() * 8, hipMemcpyHostToDevice);
+    }
+    if (e == hipSuccess) e = hipMalloc(&p->d_tw, (size_t)2 * fft_n(order) * 8);
     if (e == hipSuccess) e = hipMalloc(&p->d_downA, downA.size() * 8);
     if (e == hipSuccess) e = hipMalloc(&p->d_upA, upA.size() * 8);
     if (e == hipSuccess) e = hipMemcpy(p->d_upA, upA.data(), upA.size() * 8, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(p->d_il, il.data(), il.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_downA, downA.data(), downA.size() * 8, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(p->d_m2l, 0, ab);
-    if (e == hipSuccess) {
-        const int64_t work = (int64_t)8 * kM2LBlocks * ns * (ns + 1);
-        hipLaunchKernelGGL(m2l_matrix_kernel, dim3(f_grid((work + kFBlock - 1) / kFBlock)), dim3(kFBlock), 0, 0,
-                           p->d_surf, ns, mp, kb, p->d_il, p->d_m2l);
-        e = hipGetLastError();
+    static_assert(kAlphaUE == kAlphaDC, "M2L is a convolution on one lattice");
+    if (e == hipSuccess) e = fft_build_spectra(order, kAlphaUE, p->d_khat, p->d_tw, 0);
+    if (order >= kDenseOrderSL) {
+        const size_t ab = (size_t)8 * kM2LBlocks * mp * mp * 8;
+        if (e == hipSuccess) e = hipMalloc(&p->d_m2l, ab);
+        if (e == hipSuccess) e = hipMalloc(&p->d_il, il.size() * 4);
+        if (e == hipSuccess) e = hipMemcpy(p->d_il, il.data(), il.size() * 4, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemset(p->d_m2l, 0, ab);
+        if (e == hipSuccess) {
+            const int64_t work = (int64_t)8 * kM2LBlocks * ns * (ns + 1);
+            hipLaunchKernelGGL(m2l_matrix_kernel, dim3(f_grid((work + kFBlock - 1) / kFBlock)), dim3(kFBlock), 0, 0,
+                               p->d_surf, ns, mp, mp, p->d_il, p->d_m2l);
+            e = hipGetLastError();
+        }
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess || (int)il.size() != 8 * kILSize * 3) {
+    if (e != hipSuccess) {
         fmm_plan_free(p);
-        err = "M2L operators: " + std::string(e != hipSuccess ? hipGetErrorString(e) : "interaction list size");
+        err = "M2L operators: " + std::string(hipGetErrorString(e));
         return -2;
     }
     *out = p;
@@ -1515,10 +1708,13 @@ int fmm_plan_build(int device, int order, stokes_fmm_plan** out, std::string& er
 void fmm_plan_free(stokes_fmm_plan* p) {
     if (!p) return;
     (void)hipFree(p->d_surf);
+    (void)hipFree(p->d_khat);
     (void)hipFree(p->d_m2l);
     (void)hipFree(p->d_il);
+    (void)hipFree(p->d_tw);
     (void)hipFree(p->d_downA);
     (void)hipFree(p->d_upA);
+    (void)hipFree(p->d_down3);
     delete p;
 }
 
@@ -1526,15 +1722,14 @@ int fmm_plan_order(const stokes_fmm_plan* p) { return p->order; }
 int fmm_plan_device(const stokes_fmm_plan* p) { return p->device; }
 
 size_t fmm_workspace_bytes(int order, int64_t n_src, int64_t n_trg, int depth) {
-    const int ns = 6 * (order - 1) * (order - 1) + 2;
-    return fmm_layout(ns, n_src, n_trg, depth).total;
+    return fmm_layout(order, n_src, n_trg, depth).total;
 }
 
 hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* out, void* workspace,
                       hipStream_t st) {
     const bool dl = in.normal != nullptr;
     const int D = in.depth, ns = plan->ns;
-    const FmmLayout L = fmm_layout(ns, in.n_src, in.n_trg, D);
+    const FmmLayout L = fmm_layout(plan->order, in.n_src, in.n_trg, D);
     char* ws = static_cast<char*>(workspace);
     uint64_t* skeys = reinterpret_cast<uint64_t*>(ws + L.off_skeys);
     int32_t* svals = reinterpret_cast<int32_t*>(ws + L.off_svals);
@@ -1557,8 +1752,8 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
     a.n_trg = in.n_trg;
     a.sofs = reinterpret_cast<int64_t*>(ws + L.off_sofs);
     a.tofs = reinterpret_cast<int64_t*>(ws + L.off_tofs);
-    a.snz = reinterpret_cast<uint8_t*>(ws + L.off_snz);
-    a.tpr = reinterpret_cast<uint8_t*>(ws + L.off_tpr);
+    a.sslot = reinterpret_cast<int32_t*>(ws + L.off_sslot);
+    a.tslot = reinterpret_cast<int32_t*>(ws + L.off_tslot);
     a.ue = reinterpret_cast<double*>(ws + L.off_ue);
     a.de = reinterpret_cast<double*>(ws + L.off_de);
     for (int l = 0; l <= kFmmMaxDepth + 1; ++l) a.base[l] = L.base[std::min(l, kFmmMaxDepth + 1)];
@@ -1599,12 +1794,76 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
         if (chk())
             hipLaunchKernelGGL(leaf_ofs_kernel, dim3(gl), dim3(kFBlock), 0, st, tkeys, in.n_trg, L.n_leaves,
                                const_cast<int64_t*>(a.tofs));
-        if (chk()) hipLaunchKernelGGL(flags_leaf_kernel, dim3(gl), dim3(kFBlock), 0, st, a);
-        for (int l = D - 1; l >= 2 && chk(); --l)
-            hipLaunchKernelGGL(flags_up_kernel, dim3(f_grid(((int64_t)1 << (3 * l)) / kFBlock + 1)), dim3(kFBlock), 0,
-                               st, a, l);
     }
+    // the boxes holding sources and targets on every level, and the octets' neighbours
+    int32_t* slist = reinterpret_cast<int32_t*>(ws + L.off_slist);
+    int32_t* tlist = reinterpret_cast<int32_t*>(ws + L.off_tlist);
+    int64_t* counts = reinterpret_cast<int64_t*>(ws + L.off_counts);
+    int32_t* nbr = reinterpret_cast<int32_t*>(ws + L.off_nbr);
+    if (chk()) {
+        int64_t* f = reinterpret_cast<int64_t*>(ws + L.off_bscan);
+        const unsigned gb = f_grid((2 * L.nbox + kFBlock - 1) / kFBlock);
+        hipLaunchKernelGGL(box_flags_kernel, dim3(gb), dim3(kFBlock), 0, st, a, L.nbox, f);
+        if (chk())
+            e = exclusive_scan_i64(f, 2 * L.nbox, f, reinterpret_cast<int64_t*>(ws + L.off_btmp), f + 2 * L.nbox, st);
+        if (e == hipSuccess)
+            hipLaunchKernelGGL(box_lists_kernel, dim3(gb), dim3(kFBlock), 0, st, a, L.nbox, f, slist, tlist, counts);
+        if (chk())
+            hipLaunchKernelGGL(octet_neighbours_kernel, dim3(f_grid((L.base[D] + kFBlock - 1) / kFBlock)),
+                               dim3(kFBlock), 0, st, a, counts, nbr);
+    }
+    auto sources = [&](int l) { return Columns{slist + L.base[l], counts + l}; };
+    auto targets = [&](int l) { return Columns{tlist + L.base[l], counts + kFmmMaxDepth + 1 + l}; };
     const int T = (ns + kWave - 1) / kWave;
+    a.vbuf = reinterpret_cast<double*>(ws + L.off_vbuf);
+    a.mp = plan->mp;
+    const int rb = gemm_rb(plan->mp), ngr = gemm_groups(plan->mp, rb);
+    // OP V for the listed boxes of a level, into out (rows n3 per box)
+    double* apart = reinterpret_cast<double*>(ws + L.off_apart);
+    auto apply = [&](int l, const Columns& c, const double* op, double* out, bool exact = false) {
+        // units: tiles x splits <= max(tiles, kApplyUnits), tiles at most the bound below
+        const int64_t tiles_ub =
+            (std::min<int64_t>((int64_t)1 << (3 * l), std::max(in.n_src, in.n_trg)) + kGemmNT - 1) / kGemmNT;
+        const int per_split = exact ? 3 : 1;
+        const dim3 g((unsigned)(ngr * std::max<int64_t>(tiles_ub, per_split * kApplyUnits)));
+        if (exact) {
+            hipLaunchKernelGGL(apply_exact_kernel<kGemmMaxRB>, g, dim3(kGemmThreads), 0, st, a, c, op, out, apart);
+        } else if (!with_rb(rb, [&](auto r) {
+                       hipLaunchKernelGGL(apply_gemm_kernel<decltype(r)::value>, g, dim3(kGemmThreads), 0, st, a, c,
+                                          op, out, apart);
+                   })) {
+            e = hipErrorInvalidValue;                   // no GEMM instance for this order (not reached for 2..10)
+            return false;
+        }
+        if (!chk()) return false;
+        // a strided pass: most levels have one split, and then every workgroup just exits
+        hipLaunchKernelGGL(apply_reduce_kernel, dim3(kApplyReduceGrid), dim3(kFBlock), 0, st, a, c,
+                           plan->mp / kGemmKC, per_split, apart, out);
+        return chk();
+    };
+    // upward pass: check vectors per level, then the pseudo-inverse as one GEMM
+    if (chk()) {
+        const Columns c = sources(D);
+        const dim3 g(f_grid(L.n_leaves));
+        const size_t lds = p2m_lds(ns, dl ? 1 : 0);
+        with_T(T, [&](auto tc) {
+            constexpr int TT = decltype(tc)::value;
+            if (dl) hipLaunchKernelGGL((p2m_kernel<1, TT>), g, dim3(kFBlock), lds, st, a, c.list, c.n);
+            else hipLaunchKernelGGL((p2m_kernel<0, TT>), g, dim3(kFBlock), lds, st, a, c.list, c.n);
+        });
+        if (chk()) apply(D, c, plan->d_upA, a.ue + L.base[D] * a.n3);
+    }
+    for (int l = D - 1; l >= 2 && chk(); --l) {
+        const Columns c = sources(l);
+        const dim3 g(f_grid((int64_t)1 << (3 * l)));
+        const size_t lds = m2m_lds(ns);
+        with_T(T, [&](auto tc) {
+            hipLaunchKernelGGL(m2m_kernel<decltype(tc)::value>, g, dim3(kFBlock), lds, st, a, l, c.list, c.n);
+        });
+        if (chk()) apply(l, c, plan->d_upA, a.ue + L.base[l] * a.n3);
+    }
+    // downward pass: interaction lists, then the parent's density, then the pseudo-inverse
+    const bool conv = plan->order < (dl ? kDenseOrderDL : kDenseOrderSL);
     M2LArgs g2{};
     g2.A = plan->d_m2l;
     g2.il = plan->d_il;
@@ -1612,108 +1871,87 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
     g2.cscan = reinterpret_cast<int64_t*>(ws + L.off_cflag);
     g2.ctotal = reinterpret_cast<int64_t*>(ws + L.off_ctotal);
     g2.list = reinterpret_cast<int32_t*>(ws + L.off_clist);
-    g2.vbuf = reinterpret_cast<double*>(ws + L.off_vbuf);
+    g2.vbuf = a.vbuf;
     g2.sched = reinterpret_cast<int64_t*>(ws + L.off_sched);
     g2.npairs = reinterpret_cast<int64_t*>(ws + L.off_sched + 16);
-    a.vbuf = g2.vbuf;
-    a.mp = plan->mp;
-    const int rb = gemm_rb(plan->mp), ngr = gemm_groups(plan->mp, rb);
-    // OP V for the listed boxes of a level, into out (rows n3 per box)
-    double* apart = reinterpret_cast<double*>(ws + L.off_apart);
-    auto apply = [&](int l, const double* op, double* out) {
-        // units: tiles x splits <= max(tiles, kApplyUnits), tiles at most the bound below
-        const int64_t tiles_ub =
-            (std::min<int64_t>((int64_t)1 << (3 * l), std::max(in.n_src, in.n_trg)) + kGemmNT - 1) / kGemmNT;
-        const dim3 g((unsigned)(ngr * std::max<int64_t>(tiles_ub, kApplyUnits)));
-        if (!with_rb(rb, [&](auto r) {
-                hipLaunchKernelGGL(apply_gemm_kernel<decltype(r)::value>, g, dim3(kGemmThreads), 0, st, a, g2, op,
-                                   out, apart);
-            })) {
-            e = hipErrorInvalidValue;                   // no GEMM instance for this order (not reached for 2..10)
-            return false;
-        }
-        if (!chk()) return false;
-        // a strided pass: most levels have one split, and then every workgroup just exits
-        hipLaunchKernelGGL(apply_reduce_kernel, dim3(kApplyReduceGrid), dim3(kFBlock), 0, st, a, g2,
-                           plan->mp / kGemmKC, apart, out);
-        return chk();
-    };
-    // the boxes of level l holding sources: g2.list (box i of the list owns column i)
-    auto list_sources = [&](int l) {
-        const int64_t nb = (int64_t)1 << (3 * l);
-        const unsigned gb = f_grid((nb + kFBlock - 1) / kFBlock);
-        int64_t* f = const_cast<int64_t*>(g2.cscan);
-        hipLaunchKernelGGL(src_flags_kernel, dim3(gb), dim3(kFBlock), 0, st, a, l, f);
-        if (!chk()) return false;
-        e = exclusive_scan_i64(f, nb, f, reinterpret_cast<int64_t*>(ws + L.off_cscan), const_cast<int64_t*>(g2.ctotal),
-                               st);
-        if (e != hipSuccess) return false;
-        hipLaunchKernelGGL(src_list_kernel, dim3(gb), dim3(kFBlock), 0, st, a, l, g2.cscan,
-                           const_cast<int32_t*>(g2.list));
-        return chk();
-    };
-    // upward pass: check vectors per level, then the pseudo-inverse as one GEMM
-    if (chk() && list_sources(D)) {
-        const dim3 g(f_grid(L.n_leaves));
-        const size_t lds = p2m_lds(ns, dl ? 1 : 0);
-        with_T(T, [&](auto tc) {
-            constexpr int TT = decltype(tc)::value;
-            if (dl) hipLaunchKernelGGL((p2m_kernel<1, TT>), g, dim3(kFBlock), lds, st, a, g2.list, g2.ctotal);
-            else hipLaunchKernelGGL((p2m_kernel<0, TT>), g, dim3(kFBlock), lds, st, a, g2.list, g2.ctotal);
-        });
-        if (chk()) apply(D, plan->d_upA, a.ue + L.base[D] * a.n3);
-    }
-    for (int l = D - 1; l >= 2 && chk(); --l) {
-        if (!list_sources(l)) break;
-        const dim3 g(f_grid((int64_t)1 << (3 * l)));
-        const size_t lds = m2m_lds(ns);
-        with_T(T, [&](auto tc) {
-            hipLaunchKernelGGL(m2m_kernel<decltype(tc)::value>, g, dim3(kFBlock), lds, st, a, l, g2.list, g2.ctotal);
-        });
-        if (chk()) apply(l, plan->d_upA, a.ue + L.base[l] * a.n3);
-    }
+    FftLevel m{};
+    m.p = plan->order;
+    m.n3 = a.n3;
+    m.mp = a.mp;
+    m.khat = plan->d_khat;
+    m.tw = plan->d_tw;
+    m.q = reinterpret_cast<double*>(ws + L.off_q);
+    m.sigq = reinterpret_cast<double*>(ws + L.off_sigq);
+    m.v = reinterpret_cast<double*>(ws + L.off_v);
+    m.vbuf = a.vbuf;
     for (int l = 2; l <= D && chk(); ++l) {
-        const int64_t nb = (int64_t)1 << (3 * l);
-        const unsigned gb = f_grid((nb + kFBlock - 1) / kFBlock);
-        int64_t* cflag = const_cast<int64_t*>(g2.cscan);
-        hipLaunchKernelGGL(class_flags_kernel, dim3(gb), dim3(kFBlock), 0, st, a, l, cflag);
-        if (!chk()) break;
-        e = exclusive_scan_i64(cflag, nb, cflag, reinterpret_cast<int64_t*>(ws + L.off_cscan),
-                               const_cast<int64_t*>(g2.ctotal), st);
-        if (e != hipSuccess) break;
-        hipLaunchKernelGGL(class_list_kernel, dim3(gb), dim3(kFBlock), 0, st, a, l, g2.cscan,
-                           const_cast<int32_t*>(g2.list));
-        if (!chk()) break;
-        const int n_parts = (int)std::min<int64_t>(kILCountParts, (std::min<int64_t>(nb, in.n_trg) + 3) / 4);
-        hipLaunchKernelGGL(il_count_kernel, dim3(n_parts), dim3(kFBlock), 0, st, a, g2, l);
-        if (!chk()) break;
-        hipLaunchKernelGGL(m2l_sched_kernel, dim3(1), dim3(kWave), 0, st, g2.cscan, g2.ctotal, l, g2.npairs, n_parts,
-                           g2.sched);
-        if (!chk()) break;
-        // per class at most min(8^(l-1), n_trg) boxes in `tiles` tiles; units per
-        // class = splits x tiles <= max(kM2LUnits + tiles, kM2LMinSplits x tiles)
-        const int64_t tiles = (std::min<int64_t>(nb >> 3, in.n_trg) + kGemmNT - 1) / kGemmNT;
-        // row groups outermost: grid = 8 classes x row groups x units
-        const dim3 gm((unsigned)(8 * ngr * std::max<int64_t>(kM2LUnits + tiles, kM2LMinSplits * tiles)));
-        if (!with_rb(rb, [&](auto r) {
-                hipLaunchKernelGGL(m2l_gemm_kernel<decltype(r)::value>, gm, dim3(kGemmThreads), 0, st, a, g2, l);
-            })) {
-            e = hipErrorInvalidValue;                   // no GEMM instance for this order (not reached for 2..10)
-            break;
-        }
-        if (!chk()) break;
-        hipLaunchKernelGGL(m2l_reduce_kernel, dim3(f_grid((std::min<int64_t>(nb, in.n_trg) * plan->mp + kFBlock - 1) / kFBlock)),
-                           dim3(kFBlock), 0, st, g2);
-        if (!chk()) break;
-        {
-            const dim3 g(f_grid(nb));
-            const size_t lds = m2l_lds(ns);
+        const int64_t boxes = (int64_t)1 << (3 * l);
+        if (!conv) {
+            const unsigned gb = f_grid((boxes + kFBlock - 1) / kFBlock);
+            int64_t* cflag = const_cast<int64_t*>(g2.cscan);
+            hipLaunchKernelGGL(class_flags_kernel, dim3(gb), dim3(kFBlock), 0, st, a, l, cflag);
+            if (!chk()) break;
+            e = exclusive_scan_i64(cflag, boxes, cflag, reinterpret_cast<int64_t*>(ws + L.off_cscan),
+                                   const_cast<int64_t*>(g2.ctotal), st);
+            if (e != hipSuccess) break;
+            hipLaunchKernelGGL(class_list_kernel, dim3(gb), dim3(kFBlock), 0, st, a, l, g2.cscan,
+                               const_cast<int32_t*>(g2.list));
+            if (!chk()) break;
+            const int n_parts = (int)std::min<int64_t>(kILCountParts, (std::min<int64_t>(boxes, in.n_trg) + 3) / 4);
+            hipLaunchKernelGGL(il_count_kernel, dim3(n_parts), dim3(kFBlock), 0, st, a, g2, l);
+            if (!chk()) break;
+            hipLaunchKernelGGL(m2l_sched_kernel, dim3(1), dim3(kWave), 0, st, g2.cscan, g2.ctotal, l, g2.npairs, n_parts,
+                               g2.sched);
+            if (!chk()) break;
+            // per class at most min(8^(l-1), n_trg) boxes in `tiles` tiles; units per
+            // class = splits x tiles <= max(kM2LUnits + tiles, kM2LMinSplits x tiles)
+            const int64_t tiles = (std::min<int64_t>(boxes >> 3, in.n_trg) + kGemmNT - 1) / kGemmNT;
+            // row groups outermost: grid = 8 classes x row groups x units
+            const dim3 gm((unsigned)(8 * ngr * std::max<int64_t>(kM2LUnits + tiles, kM2LMinSplits * tiles)));
+            if (!with_rb(rb, [&](auto r) {
+                    hipLaunchKernelGGL(m2l_gemm_kernel<decltype(r)::value>, gm, dim3(kGemmThreads), 0, st, a, g2, l);
+                })) {
+                e = hipErrorInvalidValue;                   // no GEMM instance for this order (not reached for 2..10)
+                break;
+            }
+            if (!chk()) break;
+            hipLaunchKernelGGL(m2l_reduce_kernel,
+                               dim3(f_grid((std::min<int64_t>(boxes, in.n_trg) * plan->mp + kFBlock - 1) / kFBlock)),
+                               dim3(kFBlock), 0, st, g2);
+            if (!chk()) break;
             with_T(T, [&](auto tc) {
-                hipLaunchKernelGGL(m2l_pairs_kernel<decltype(tc)::value>, g, dim3(kFBlock), lds, st, a, g2, l);
+                hipLaunchKernelGGL(m2l_pairs_kernel<decltype(tc)::value>,
+                                   dim3(f_grid(std::min<int64_t>(boxes, in.n_trg))), dim3(kFBlock), m2l_lds(ns), st, a,
+                                   g2, l);
             });
+            if (!chk()) break;
+            if (!apply(l, Columns{g2.list, g2.ctotal}, plan->d_downA, a.de + L.base[l] * a.n3)) break;
+            continue;
         }
-        if (!chk()) break;
-        if (!apply(l, plan->d_downA, a.de + L.base[l] * a.n3)) break;
+        const Columns c = targets(l);
+        if (l > 2) {
+            const dim3 g(f_grid(std::min<int64_t>(boxes, in.n_trg)));
+            with_T(T, [&](auto tc) {
+                hipLaunchKernelGGL(l2l_kernel<decltype(tc)::value>, g, dim3(kFBlock), l2l_lds(ns), st, a, c, l);
+            });
+            if (!chk()) break;
+        }
+        m.ue = a.ue + L.base[l] * a.n3;
+        m.sslot = a.sslot + L.base[l];
+        m.tslot = a.tslot + L.base[l];
+        m.soct = sources(l - 1).list;
+        m.n_soct = sources(l - 1).n;
+        m.toct = targets(l - 1).list;
+        m.n_toct = targets(l - 1).n;
+        m.nbr = nbr + 26 * L.base[l - 1];
+        m.sig = a.sig ? a.sig + L.base[l] : nullptr;
+        m.inv_h = (double)(1 << l) / a.R;
+        m.add = l > 2;
+        e = launch_fft_m2l(m, std::min<int64_t>(boxes >> 3, in.n_src), std::min<int64_t>(boxes >> 3, in.n_trg),
+                           plan->cus, st);
+        if (e != hipSuccess) break;
+        const bool exact = plan->d_down3 != nullptr;
+        if (!apply(l, c, exact ? plan->d_down3 : plan->d_downA, a.de + L.base[l] * a.n3, exact)) break;
     }
     if (chk()) {
         // L2P, then the near field added by the leaf-to-leaf kernel over the 27-leaf lists

@@ -204,6 +204,20 @@ stokes::SumInputs make_inputs(int kernel, const Parsed& p, int64_t n_src, const 
     return in;
 }
 
+// Whether a direct sum runs as the one kernel of small calls (a forced
+// workgroup count asks for the kernels that it cuts).
+bool small_sum(const stokes_ctx* ctx, const stokes::SumInputs& in) {
+    return in.n_src > 0 && in.n_trg > 0 && ctx->forced_grid == 0 &&
+           stokes::direct_is_small(in.kernel, in.mixed, in.n_src, in.n_trg);
+}
+
+hipError_t run_direct(stokes_ctx* ctx, const stokes::SumInputs& in, const stokes::DirectPlan& plan, double* out,
+                      int accumulate, void* ws, hipStream_t st) {
+    if (small_sum(ctx, in))
+        return stokes::launch_direct_small(in, out, accumulate, ctx->n_cu, st, stokes::next_timer(ctx));
+    return stokes::launch_direct(in, plan, out, accumulate, ws, st, stokes::next_timer(ctx));
+}
+
 // Shared argument checks of the direct sums and their adjoints.
 int check_points(int kernel, int64_t n_src, const double* src_xyz, const double* density,
                  const double* weight, const double* normal, int64_t n_trg, const double* trg_xyz) {
@@ -322,7 +336,7 @@ hipError_t checkpoint_run(stokes_ctx* ctx, const stokes::PatchRule& R, const Che
     if (e == hipSuccess) {
         const stokes::SumInputs in = make_inputs(STOKES_KERNEL_DL, p, lay.n_fine, fx, fphi, fw, fn, lay.n_check,
                                                  cx, 6.0 / (8.0 * kPi));
-        e = stokes::launch_direct(in, lay.plan, cv, 0, ws + lay.off_direct, st, stokes::next_timer(ctx));
+        e = run_direct(ctx, in, lay.plan, cv, 0, ws + lay.off_direct, st);
     }
     if (e == hipSuccess)
         e = stokes::launch_extrapolate(R, n_patches, L, n_trg, trg_patch, trg_uvd, cv, vel_out, p.accumulate, st);
@@ -641,13 +655,11 @@ static int direct_eval(stokes_ctx* ctx, int kernel, int64_t n_src, const double*
                                        n_trg, trg_xyz, pref);
     in.pair_class = pair_class;
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    if (use_sym)
+    if (use_sym && !small_sum(ctx, in))
         return launch_status(stokes::launch_sym(in, splan, vel_out, p.accumulate, workspace, st,
                                                 stokes::next_timer(ctx)),
                              "stokes_sl_eval");
-    return launch_status(stokes::launch_direct(in, plan, vel_out, p.accumulate, workspace, st,
-                                               stokes::next_timer(ctx)),
-                         kernel ? "stokes_dl_eval" : "stokes_sl_eval");
+    return launch_status(run_direct(ctx, in, plan, vel_out, p.accumulate, workspace, st), kernel ? "stokes_dl_eval" : "stokes_sl_eval");
 }
 
 int stokes_sl_eval(stokes_ctx* ctx, int64_t n_src, const double* src_xyz, const double* density,

@@ -111,6 +111,12 @@ struct KernelTimer {
 hipError_t launch_direct(const SumInputs& in, const DirectPlan& p, double* out, int accumulate,
                          void* workspace, hipStream_t stream, const KernelTimer& timer);
 
+// Whether a float64 sum of these sizes runs as one kernel, and that kernel
+// (n_src, n_trg > 0; no workspace).
+bool direct_is_small(int kernel, int mixed, int64_t n_src, int64_t n_trg);
+hipError_t launch_direct_small(const SumInputs& in, double* out, int accumulate, int n_cu, hipStream_t stream,
+                               const KernelTimer& timer);
+
 // Packs n_pad (a multiple of kBlock) source records, padding beyond n_src, and
 // the per-64-source summaries (the direct sums' prep kernel).
 hipError_t launch_prep(const SumInputs& in, int64_t n_pad, void* rec, void* aux, SubMeta* meta,

@@ -35,6 +35,8 @@
 #include <float.h>
 #include <limits.h>
 
+#include <type_traits>
+
 #include "direct_dev.hpp"
 
 namespace stokes {
@@ -506,6 +508,140 @@ __global__ __launch_bounds__(kBlock) void reduce_segments(const double* __restri
         const int64_t o = c * n_trg + i;
         out[o] = accumulate ? out[o] + pref * s[c] : pref * s[c];
     }
+}
+
+// ---------------------------------------------------------------------------
+// small sums: one kernel
+// ---------------------------------------------------------------------------
+// The whole float64 sum of a small call in one launch, straight from the
+// caller's arrays.  Such a call is bound by latency, not by its pairs: the
+// kernels above are four dependent launches, and a few target blocks leave
+// most of the chip idle (4,352 points: 92 us there, 41 us here, of which the
+// 1.9e7 pairs need 13 at the rate of a full chip).  Here a workgroup owns TW targets and the 256 / TW
+// threads of a target share the sources, 256 staged at a time; every pair
+// carries the masks.  A target's partial sums are added in a fixed order.
+template <int KT, int TW>
+__global__ __launch_bounds__(kBlock) void direct_small(SumInputs in, double pref, double* __restrict__ out,
+                                                       int accumulate) {
+    constexpr int H = kBlock / TW, NC = KT == 0 ? 6 : 9;
+    __shared__ double s_src[NC][kBlock];
+    __shared__ int32_t s_grp[kBlock];
+    const int tid = threadIdx.x, t = tid % TW, h = tid / TW;
+    const int64_t n = in.n_src, nt = in.n_trg, i = (int64_t)blockIdx.x * TW + t, ic = min(i, nt - 1);
+    const double x = 2.0 * in.trg_xyz[ic], y = 2.0 * in.trg_xyz[nt + ic], z = 2.0 * in.trg_xyz[2 * nt + ic];
+    const bool excl = in.excl != 0;
+    const int32_t tg = in.trg_group ? in.trg_group[ic] : 0;
+    double u[3] = {0.0, 0.0, 0.0};
+    for (int64_t b = 0; b < n; b += kBlock) {
+        const int64_t m = b + tid;
+        double v[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c] = c < 3 ? kPadPos : 0.0;
+        int32_t g = INT_MIN;
+        if (m < n) {
+            const double w = in.weight[m];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                v[c] = 2.0 * in.src_xyz[c * n + m];
+                v[3 + c] = w * in.density[c * n + m];
+                if constexpr (KT == 1) v[6 + c] = in.normal[c * n + m];
+            }
+            g = in.src_group ? in.src_group[m] : 0;
+        }
+        __syncthreads();                       // readers of the previous tile are done
+#pragma unroll
+        for (int c = 0; c < NC; ++c) s_src[c][tid] = v[c];
+        s_grp[tid] = g;
+        __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < TW; ++k) {
+            const int j = k * H + h;
+            typename SrcRec<KT, 0>::type r;
+            r.x = s_src[0][j]; r.y = s_src[1][j]; r.z = s_src[2][j];
+            r.qx = s_src[3][j]; r.qy = s_src[4][j]; r.qz = s_src[5][j];
+            if constexpr (KT == 0) {
+                r.q4x = 4.0 * r.qx; r.q4y = 4.0 * r.qy; r.q4z = 4.0 * r.qz;
+            } else {
+                r.nx = s_src[6][j]; r.ny = s_src[7][j]; r.nz = s_src[8][j];
+            }
+            pair_f64<KT, true>(r, x, y, z, excl && s_grp[j] == tg, u[0], u[1], u[2]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s_src[c][tid] = u[c];
+    for (int o = H / 2; o > 0; o >>= 1) {
+        __syncthreads();
+        if (h < o)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) s_src[c][tid] += s_src[c][tid + o * TW];
+    }
+    __syncthreads();
+    if (tid < TW && i < nt)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double val = pref * s_src[c][tid];
+            out[c * nt + i] = accumulate ? out[c * nt + i] + val : val;
+        }
+}
+
+// Targets per workgroup: the power of two with the least work on the fullest CU
+// (rounds of workgroups times a tile's TW pair steps and its staging, about two
+// more; a CU with one workgroup waits on latency as long as one with two).
+// 4,352 points on 256 CUs take 79, 50, 41, 49, 62 and 93 us with TW = 1, 2, 4, 8,
+// 16 and 32 by this order: 51, 36, 30, 30, 36, 68.
+static int small_targets(int64_t n_trg, int n_cu) {
+    int best = 1;
+    int64_t least = INT64_MAX;
+    for (int tw = 1; tw <= kWave; tw *= 2) {
+        const int64_t cost = std::max<int64_t>(2, ceil_div(ceil_div(n_trg, tw), n_cu)) * (tw + 2);
+        if (cost < least) {
+            least = cost;
+            best = tw;
+        }
+    }
+    return best;
+}
+
+template <int KT>
+static void launch_small_kt(const SumInputs& in, double* out, int accumulate, int n_cu, hipStream_t stream) {
+    const double pref = (KT == 0 ? 0.25 : 0.125) * in.pref;       // doubled positions, as above
+    auto go = [&](auto tw) {
+        constexpr int TW = decltype(tw)::value;
+        direct_small<KT, TW><<<dim3((unsigned)ceil_div(in.n_trg, TW)), dim3(kBlock), 0, stream>>>(in, pref, out,
+                                                                                               accumulate);
+    };
+    switch (small_targets(in.n_trg, n_cu)) {
+        case 1: go(std::integral_constant<int, 1>{}); break;
+        case 2: go(std::integral_constant<int, 2>{}); break;
+        case 4: go(std::integral_constant<int, 4>{}); break;
+        case 8: go(std::integral_constant<int, 8>{}); break;
+        case 16: go(std::integral_constant<int, 16>{}); break;
+        case 32: go(std::integral_constant<int, 32>{}); break;
+        default: go(std::integral_constant<int, 64>{}); break;
+    }
+}
+
+// The line lies where the four-kernel path (the each-pair-once one on shared
+// sets) catches up, measured on cells, tracers and walls (this kernel / that
+// path): single layer 544 x 544 19 / 73 us, 4,352 x 4,352 41 / 92, 6,528 x 6,528
+// 82 / 138, 8,704 x 8,704 126 / 155, 13,056 x 13,056 263 / 278, 34,816 x 1,001
+// 112 / 576; double layer 2,048 x 2,193 19 / 75, 2,048 x 16,337 49 / 120, 10,368 x
+// 4,369 106 / 97, 32,768 x 2,193 204 / 167.  Mixed sums keep their sub-tiles'
+// float32 partial sums and stay on the other path.
+bool direct_is_small(int kernel, int mixed, int64_t n_src, int64_t n_trg) {
+    constexpr int64_t kPairsSL = 60'000'000, kPairsDL = 34'000'000;
+    return !mixed && n_src <= (kernel == 0 ? kPairsSL : kPairsDL) / n_trg;
+}
+
+hipError_t launch_direct_small(const SumInputs& in, double* out, int accumulate, int n_cu, hipStream_t stream,
+                               const KernelTimer& timer) {
+    if (timer.on()) (void)hipEventRecord(timer.start, stream);
+    if (in.kernel == 0) launch_small_kt<0>(in, out, accumulate, n_cu, stream);
+    else launch_small_kt<1>(in, out, accumulate, n_cu, stream);
+    const hipError_t e = hipGetLastError();
+    if (timer.on()) (void)hipEventRecord(timer.stop, stream);
+    return e;
 }
 
 hipError_t launch_prep(const SumInputs& in, int64_t n_pad, void* rec, void* aux, SubMeta* meta,

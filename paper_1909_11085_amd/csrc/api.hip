@@ -62,7 +62,7 @@ KernelTimer next_timer(stokes_ctx* ctx) {
 
 // Scratch of stokes_sl_eval_noalloc, for callers that cannot allocate: the
 // direct sum's workspace (packed source records, sub-tile summaries, partial
-// sums, near-pass flags) lives here instead of in caller memory.  Each GPU that
+// sums) lives here instead of in caller memory.  Each GPU that
 // the library runs on holds its own copy until the process ends.  In host code
 // this name is not a device address: stokes_create takes the address of the
 // current device's copy with hipGetSymbolAddress and keeps it in the context,
@@ -612,7 +612,8 @@ static int direct_eval(stokes_ctx* ctx, int kernel, int64_t n_src, const double*
                        const double* density, const double* weight, const double* normal,
                        int64_t n_trg, const double* trg_xyz, double pref,
                        const stokes_exclusion* excl, const stokes_opts* opts, double* vel_out,
-                       void* workspace, size_t ws_bytes, void* stream, bool allow_sym = true) {
+                       void* workspace, size_t ws_bytes, void* stream, bool allow_sym = true,
+                       size_t plan_limit = 0) {
     if (!ctx) return fail(STOKES_EINVAL, "ctx is NULL");
     int rc = check_sizes(n_src, n_trg);
     if (rc) return rc;
@@ -632,7 +633,7 @@ static int direct_eval(stokes_ctx* ctx, int kernel, int64_t n_src, const double*
     size_t need = 0;
     if (n_src > 0 && n_trg > 0) {
         plan = stokes::plan_direct(kernel, mixed, n_src, n_trg, ctx->resident[kernel][mixed],
-                                   ctx->forced_grid);
+                                   ctx->forced_grid, plan_limit);
         need = plan.total;
     }
     rc = check_workspace(workspace, ws_bytes, need);
@@ -686,8 +687,8 @@ int stokes_sl_eval_noalloc(stokes_ctx* ctx, int64_t n_src, const double* src_xyz
     const int mixed = p.precision == STOKES_MIXED;
     size_t need = 0;
     if (n_src > 0 && n_trg > 0)
-        need = stokes::plan_direct(STOKES_KERNEL_SL, mixed, n_src, n_trg, ctx->resident[0][mixed],
-                                   ctx->forced_grid).total;
+        need = stokes::direct_scratch_measure(STOKES_KERNEL_SL, mixed, n_src, n_trg, ctx->n_cu,
+                                              ctx->forced_grid);
     if (need > (size_t)STOKES_NOALLOC_SCRATCH_BYTES)
         return fail(STOKES_EWORKSPACE, "stokes_sl_eval_noalloc: these sizes need " + std::to_string(need) +
                                            " bytes of scratch, more than the library's " +
@@ -698,7 +699,8 @@ int stokes_sl_eval_noalloc(stokes_ctx* ctx, int64_t n_src, const double* src_xyz
                                                 "array: ") + hipGetErrorString(ctx->scratch_status));
     return direct_eval(ctx, STOKES_KERNEL_SL, n_src, src_xyz, density, weight, nullptr, n_trg, trg_xyz,
                        1.0 / (8.0 * kPi * mu), excl, opts, vel_out, ctx->scratch,
-                       (size_t)STOKES_NOALLOC_SCRATCH_BYTES, stream, /*allow_sym=*/false);
+                       (size_t)STOKES_NOALLOC_SCRATCH_BYTES, stream, /*allow_sym=*/false,
+                       /*plan_limit=*/(size_t)STOKES_NOALLOC_SCRATCH_BYTES);
 }
 
 int stokes_dl_eval(stokes_ctx* ctx, int64_t n_src, const double* src_xyz, const double* density,

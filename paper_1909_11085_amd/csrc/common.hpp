@@ -86,20 +86,25 @@ struct DirectPlan {
     int T;                       // targets per lane
     int64_t n_src_pad;           // sources padded to kTile
     int64_t n_sub;               // n_src_pad / kSub
-    int64_t chunks;              // n_src_pad / kTile
     int64_t blocks_x;            // target blocks of kBlock * T targets
-    int64_t units;               // blocks_x * chunks
+    int64_t units;               // blocks_x * n_sub
     int64_t grid;                // workgroups (resident count, at most units)
-    size_t off_src, off_grp, off_meta, off_part, off_near, off_flags, total;
+    int cut;                     // units that a workgroup's range begins at multiples of
+    int near_slices;             // grid rows of the near pass
+    size_t off_src, off_grp, off_meta, off_part, off_near, total;
 };
 
 // Workgroups of a direct-sum kernel that fit on one compute unit at once.
 int direct_blocks_per_cu(int kernel, int mixed);
 
 // resident_blocks: workgroups resident on the whole device; forced_grid > 0
-// overrides it (tests).
+// overrides it (tests); max_bytes > 0: workgroups and near-pass rows are given
+// up where the workspace would be larger.
 DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int resident_blocks,
-                       int forced_grid);
+                       int forced_grid, size_t max_bytes = 0);
+
+// What the static-scratch entry point accepts sizes by (bytes).
+size_t direct_scratch_measure(int kernel, int mixed, int64_t n_src, int64_t n_trg, int n_cu, int forced_grid);
 
 // Optional event pair recorded around a call's main summation kernel(s).
 struct KernelTimer {

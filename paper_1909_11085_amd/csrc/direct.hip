@@ -16,8 +16,8 @@
 //     lane of a wave reads the same record, a broadcast LDS read.
 //   * per 64-source sub-tile the wave decides, uniformly, whether the fast
 //     loop (no per-pair tests) is exact: box far from its targets and no
-//     shared group.  Sub-tiles that need per-pair tests are flagged and left
-//     to a separate near-pass kernel, so the main loop's register allocation
+//     shared group.  Sub-tiles that need per-pair tests are left to a separate
+//     near-pass kernel (which takes the same decision again), so the main loop's register allocation
 //     and schedule carry no masked code.  Mixed precision evaluates pairs in float32
 //     on offsets from the sub-tile centre (each rounded once from float64),
 //     sums each sub-tile in float32 and adds it into float64 accumulators.
@@ -25,8 +25,8 @@
 //     the sub-tile's extent) r is formed from float32 high parts plus float32
 //     residues, and pairs within the near radius are evaluated in float64.
 //   * work balance (stream-K): the grid holds exactly the resident number of
-//     workgroups; the (target block x source chunk) units are cut into equal
-//     contiguous ranges, one per workgroup.  A workgroup flushes float64
+//     workgroups; the (target block x 64-source sub-tile) units are cut into
+//     equal contiguous ranges, one per workgroup.  A workgroup flushes float64
 //     partial sums whenever its range moves to a new target block; segment
 //     ids (workgroup + target block) are consecutive, and a second kernel
 //     adds each target's segments in fixed order (deterministic, no atomics).
@@ -46,11 +46,11 @@ struct DirectArgs {
     const void* rec;          // packed source records
     const void* aux;          // FP64 path: padded int32 groups; mixed: float4 low parts
     const SubMeta* meta;
-    int64_t chunks;           // source chunks of kTile records
-    int64_t units;            // target blocks x chunks
+    int64_t n_sub;            // source sub-tiles (a multiple of 4)
+    int64_t units;            // target blocks x sub-tiles
+    int cut;                  // ranges begin at multiples of this many units
     double* part;             // partial sums, one segment per (block, target block) pair
-    uint8_t* flags;           // per (wave, chunk): bit s = sub-tile s left to the near pass
-    double* near_part;        // near-pass sums, (kNearSlices, 3, blocks_x * kBlock * T)
+    double* near_part;        // near-pass sums, (near slices, 3, blocks_x * kBlock * T)
 };
 
 // ---------------------------------------------------------------------------
@@ -170,20 +170,28 @@ __device__ __forceinline__ void flush_segment(const DirectArgs& a, int64_t tbk, 
 #ifndef STOKES_DIRECT_T32
 #define STOKES_DIRECT_T32 2
 #endif
-#ifndef STOKES_DIRECT_W32
-#define STOKES_DIRECT_W32 4
+// The mixed kernel's float32 loop is sensitive to the register assignment (an FMA
+// whose three operands share a bank takes longer), which the occupancy bound
+// steers; measured at 3, 4, 5 and 6 waves: single layer, 69,632 points 2.21,
+// 2.23, 2.15, 2.15 ms; double layer, 294,912 wall nodes at 48,000 targets 8.15,
+// 8.02, 8.56, 8.54 ms.
+#ifndef STOKES_DIRECT_W32SL
+#define STOKES_DIRECT_W32SL 6
+#endif
+#ifndef STOKES_DIRECT_W32DL
+#define STOKES_DIRECT_W32DL 4
 #endif
 
 // Main FP64 kernel: fast loop only; sub-tiles needing per-pair tests are
-// flagged for direct_near_f64.
+// skipped (direct_near_f64 takes them).
 template <int KT, int T>
 __global__ __launch_bounds__(kBlock, STOKES_DIRECT_W64) void direct_f64(DirectArgs a) {
     using Rec = typename SrcRec<KT, 0>::type;
     constexpr int BT = kBlock * T;
     __shared__ Rec s_rec[kTile];
 
-    const int64_t U = a.units, C = a.chunks, G = gridDim.x;
-    const int64_t u0 = unit_begin(blockIdx.x, U, G), u1 = unit_begin(blockIdx.x + 1, U, G);
+    const int64_t U = a.units, C = a.n_sub, G = gridDim.x;
+    const int64_t u0 = range_begin(blockIdx.x, U, G, a.cut), u1 = range_begin(blockIdx.x + 1, U, G, a.cut);
     if (u0 >= u1) return;                      // whole workgroup idle (uniform)
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
@@ -198,8 +206,9 @@ __global__ __launch_bounds__(kBlock, STOKES_DIRECT_W64) void direct_f64(DirectAr
 #pragma unroll
     for (int k = 0; k < T; ++k) ax[k] = ay[k] = az[k] = 0.0;
 
-    int64_t ub = u0 / C, c = u0 % C;           // unit position, advanced incrementally
-    for (int64_t u = u0; u < u1; ++u) {
+    int64_t ub = u0 / C, sub = u0 % C;         // unit position, advanced by up to four sub-tiles
+    for (int64_t u = u0; u < u1;) {
+        const int s0 = (int)(sub & 3), s1 = (int)min((int64_t)4, s0 + (u1 - u));
         __syncthreads();                       // previous step's readers are done
         if (ub != tbk) {
             if (tbk >= 0) flush_segment<T>(a, tbk, wave, lane, ax, ay, az);
@@ -211,20 +220,14 @@ __global__ __launch_bounds__(kBlock, STOKES_DIRECT_W64) void direct_f64(DirectAr
 #pragma unroll
             for (int k = 0; k < T; ++k) ax[k] = ay[k] = az[k] = 0.0;
         }
-        s_rec[threadIdx.x] = rec[c * kTile + threadIdx.x];
+        const int64_t first = sub - s0;        // the chunk's first sub-tile
+        if (wave >= s0 && wave < s1) s_rec[threadIdx.x] = rec[first * kSub + threadIdx.x];
         __syncthreads();
-        int64_t cn = c + 1, ubn = ub;
-        if (cn == C) { cn = 0; ++ubn; }
         if (wave_active) {
-            uint32_t flags = 0;
 #pragma unroll 1
-            for (int s = 0; s < 4; ++s) {
-                const SubMeta m = a.meta[c * 4 + s];
-                if (m.count == 0) continue;
-                if (needs_near<T, false>(wbox, t, m, excl)) {
-                    flags |= 1u << s;
-                    continue;
-                }
+            for (int s = s0; s < s1; ++s) {
+                const SubMeta m = a.meta[first + s];
+                if (m.count == 0 || needs_near<T, false>(wbox, t, m, excl)) continue;
                 const Rec* base = s_rec + s * kSub;
 #pragma unroll 2
                 for (int j = 0; j < kSub; ++j) {
@@ -234,16 +237,16 @@ __global__ __launch_bounds__(kBlock, STOKES_DIRECT_W64) void direct_f64(DirectAr
                         pair_f64<KT, false>(sr, t.x[k], t.y[k], t.z[k], false, ax[k], ay[k], az[k]);
                 }
             }
-            if (lane == 0) a.flags[(tbk * 4 + wave) * C + c] = (uint8_t)flags;
         }
-        c = cn;
-        ub = ubn;
+        u += s1 - s0;
+        sub += s1 - s0;
+        if (sub == C) { sub = 0; ++ub; }
     }
     flush_segment<T>(a, tbk, wave, lane, ax, ay, az);
 }
 
-// Near pass (FP64): for each wave of each target block, the flagged
-// sub-tiles with the same-group and zero-distance masks.
+// Near pass (FP64): for each wave of each target block, the sub-tiles that the
+// main pass skips, with the same-group and zero-distance masks.
 template <int KT, int T>
 __global__ __launch_bounds__(kBlock) void direct_near_f64(DirectArgs a) {
     using Rec = typename SrcRec<KT, 0>::type;
@@ -253,20 +256,20 @@ __global__ __launch_bounds__(kBlock) void direct_near_f64(DirectArgs a) {
     __shared__ int32_t s_grp[4][kSub];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
-    const int64_t tbk = blockIdx.x, C = a.chunks;
+    const int64_t tbk = blockIdx.x;
     const int64_t tb = tbk * BT + (int64_t)wave * (kWave * T);
     if (tb >= a.in.n_trg) return;              // wave has no targets (no barriers below)
     const bool excl = a.in.excl != 0;
     const Rec* rec = reinterpret_cast<const Rec*>(a.rec);
     const int32_t* grp = reinterpret_cast<const int32_t*>(a.aux);
     Targets<T> t;
-    (void)load_targets<T>(a.in, tb, lane, t);
-    double_targets<T>(t, nullptr);
+    Box wbox = load_targets<T>(a.in, tb, lane, t);
+    double_targets<T>(t, &wbox);
     double ax[T], ay[T], az[T];
 #pragma unroll
     for (int k = 0; k < T; ++k) ax[k] = ay[k] = az[k] = 0.0;
-    const uint8_t* fl = a.flags + (tbk * 4 + wave) * C;
-    for_each_flagged(fl, C, lane, (int)blockIdx.y, [&](int64_t sub) {
+    for_each_near<T, false>(wbox, t, a.meta, a.n_sub, lane, (int)blockIdx.y, (int)gridDim.y, excl,
+                            [&](int64_t sub, const SubMeta&) {
         s_src[wave][lane] = rec[sub * kSub + lane];
         s_grp[wave][lane] = grp[sub * kSub + lane];
         __builtin_amdgcn_wave_barrier();
@@ -293,16 +296,16 @@ __global__ __launch_bounds__(kBlock) void direct_near_f64(DirectArgs a) {
 }
 
 // Main mixed kernel: float32 fast loop only; sub-tiles needing care are
-// flagged for direct_near_mixed.  CNT: also record each pair's class
+// skipped (direct_near_mixed takes them).  CNT: also record each pair's class
 // (test-only instantiation).
 template <int KT, int T, bool CNT = false>
-__global__ __launch_bounds__(kBlock, STOKES_DIRECT_W32) void direct_mixed(DirectArgs a) {
+__global__ __launch_bounds__(kBlock, KT == 0 ? STOKES_DIRECT_W32SL : STOKES_DIRECT_W32DL) void direct_mixed(DirectArgs a) {
     using Rec = typename SrcRec<KT, 1>::type;
     constexpr int BT = kBlock * T;
     __shared__ Rec s_rec[kTile];
 
-    const int64_t U = a.units, C = a.chunks, G = gridDim.x;
-    const int64_t u0 = unit_begin(blockIdx.x, U, G), u1 = unit_begin(blockIdx.x + 1, U, G);
+    const int64_t U = a.units, C = a.n_sub, G = gridDim.x;
+    const int64_t u0 = range_begin(blockIdx.x, U, G, a.cut), u1 = range_begin(blockIdx.x + 1, U, G, a.cut);
     if (u0 >= u1) return;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
@@ -317,9 +320,11 @@ __global__ __launch_bounds__(kBlock, STOKES_DIRECT_W32) void direct_mixed(Direct
 #pragma unroll
     for (int k = 0; k < T; ++k) ax[k] = ay[k] = az[k] = 0.0;
 
-    int64_t ub = u0 / C, c = u0 % C;
-    Rec pre = rec[c * kTile + threadIdx.x];
-    for (int64_t u = u0; u < u1; ++u) {
+    int64_t ub = u0 / C, sub = u0 % C;
+    Rec pre = rec[(sub & ~(int64_t)3) * kSub + threadIdx.x];
+    for (int64_t u = u0; u < u1;) {
+        const int s0 = (int)(sub & 3), s1 = (int)min((int64_t)4, s0 + (u1 - u));
+        const int64_t first = sub - s0;        // the chunk's first sub-tile
         __syncthreads();
         if (ub != tbk) {
             if (tbk >= 0) flush_segment<T>(a, tbk, wave, lane, ax, ay, az);
@@ -332,19 +337,15 @@ __global__ __launch_bounds__(kBlock, STOKES_DIRECT_W32) void direct_mixed(Direct
         }
         s_rec[threadIdx.x] = pre;
         __syncthreads();
-        int64_t cn = c + 1, ubn = ub;
-        if (cn == C) { cn = 0; ++ubn; }
-        if (u + 1 < u1) pre = rec[cn * kTile + threadIdx.x];
+        u += s1 - s0;
+        sub += s1 - s0;
+        if (sub == C) { sub = 0; ++ub; }
+        if (u < u1) pre = rec[sub * kSub + threadIdx.x];
         if (wave_active) {
-            uint32_t flags = 0;
 #pragma unroll 1
-            for (int s = 0; s < 4; ++s) {
-                const SubMeta m = a.meta[c * 4 + s];
-                if (m.count == 0) continue;
-                if (needs_near<T, true>(wbox, t, m, excl)) {
-                    flags |= 1u << s;
-                    continue;
-                }
+            for (int s = s0; s < s1; ++s) {
+                const SubMeta m = a.meta[first + s];
+                if (m.count == 0 || needs_near<T, true>(wbox, t, m, excl)) continue;
                 // target offsets from the sub-tile centre, rounded once from float64
                 float xs[T], ys[T], zs[T], bx[T], by[T], bz[T];
 #pragma unroll
@@ -370,24 +371,21 @@ __global__ __launch_bounds__(kBlock, STOKES_DIRECT_W32) void direct_mixed(Direct
                     az[k] += (double)bz[k];
                 }
                 if constexpr (CNT) {
-                    const int64_t s0 = c * kTile + s * kSub;
+                    const int64_t i0 = (first + s) * kSub;
                     for (int k = 0; k < T; ++k) {
                         const int64_t ti = tbk * BT + (int64_t)wave * (kWave * T) + k * kWave + lane;
                         if (ti < a.in.n_trg)
                             for (int j = 0; j < m.count; ++j)
-                                atomicAdd(a.in.pair_class + ti * a.in.n_src + s0 + j, kPairF32);
+                                atomicAdd(a.in.pair_class + ti * a.in.n_src + i0 + j, kPairF32);
                     }
                 }
             }
-            if (lane == 0) a.flags[(tbk * 4 + wave) * C + c] = (uint8_t)flags;
         }
-        c = cn;
-        ub = ubn;
     }
     flush_segment<T>(a, tbk, wave, lane, ax, ay, az);
 }
 
-// Near pass (mixed): flagged sub-tiles with r from high + low float32 parts,
+// Near pass (mixed): the skipped sub-tiles with r from high + low float32 parts,
 // the same-group mask, and pairs inside the near radius in float64.  CNT:
 // also record each pair's class (test-only instantiation).
 template <int KT, int T, bool CNT = false>
@@ -401,20 +399,19 @@ __global__ __launch_bounds__(kBlock) void direct_near_mixed(DirectArgs a) {
     __shared__ float4 s_res[4][kSub];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
-    const int64_t tbk = blockIdx.x, C = a.chunks;
+    const int64_t tbk = blockIdx.x;
     const int64_t tb = tbk * BT + (int64_t)wave * (kWave * T);
     if (tb >= a.in.n_trg) return;
     const bool excl = a.in.excl != 0;
     const Rec* rec = reinterpret_cast<const Rec*>(a.rec);
     const float4* lo = reinterpret_cast<const float4*>(a.aux);
     Targets<T> t;
-    (void)load_targets<T>(a.in, tb, lane, t);
+    const Box wbox = load_targets<T>(a.in, tb, lane, t);
     double ax[T], ay[T], az[T];
 #pragma unroll
     for (int k = 0; k < T; ++k) ax[k] = ay[k] = az[k] = 0.0;
-    const uint8_t* fl = a.flags + (tbk * 4 + wave) * C;
-    for_each_flagged(fl, C, lane, (int)blockIdx.y, [&](int64_t sub) {
-        const SubMeta m = a.meta[sub];
+    for_each_near<T, true>(wbox, t, a.meta, a.n_sub, lane, (int)blockIdx.y, (int)gridDim.y, excl,
+                           [&](int64_t sub, const SubMeta& m) {
         float xs[T], ys[T], zs[T], xl[T], yl[T], zl[T], bx[T], by[T], bz[T];
 #pragma unroll
         for (int k = 0; k < T; ++k) {
@@ -428,24 +425,27 @@ __global__ __launch_bounds__(kBlock) void direct_near_mixed(DirectArgs a) {
         s_src[wave][lane] = rec[sub * kSub + lane];
         s_res[wave][lane] = lo[sub * kSub + lane];
         __builtin_amdgcn_wave_barrier();
+        // r = (x_hi - y_hi) + (x_lo - y_lo): the high difference is rounded
+        // relative to rho, the residues carry the rest
+        auto offset = [&](const Rec& sr, const float4& sl, int k, float& dx, float& dy, float& dz) {
+            dx = (xs[k] - sr.ox) + (xl[k] - sl.x);
+            dy = (ys[k] - sr.oy) + (yl[k] - sl.y);
+            dz = (zs[k] - sr.oz) + (zl[k] - sl.z);
+            return __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
+        };
+        bool any = false;                      // a near pair of this lane, left to the second loop
 #pragma unroll 2
         for (int j = 0; j < kSub; ++j) {
             const Rec sr = s_src[wave][j];
             const float4 sl = s_res[wave][j];
 #pragma unroll
             for (int k = 0; k < T; ++k) {
-                // r = (x_hi - y_hi) + (x_lo - y_lo): the high difference is
-                // rounded relative to rho, the residues carry the rest
-                const float dx = (xs[k] - sr.ox) + (xl[k] - sl.x);
-                const float dy = (ys[k] - sr.oy) + (yl[k] - sl.y);
-                const float dz = (zs[k] - sr.oz) + (zl[k] - sl.z);
-                const float r2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
+                float dx, dy, dz;
+                const float r2 = offset(sr, sl, k, dx, dy, dz);
                 const bool excluded = excl && sr.g == t.g[k];
                 const bool near = r2 <= sr.t2;
+                any |= near && !excluded;
                 pair_f32<KT>(sr, dx, dy, dz, excluded || near, true, bx[k], by[k], bz[k]);
-                if (near && !excluded)
-                    near_pair_f64<KT>(a.in, sub * kSub + j, t.x[k], t.y[k], t.z[k], ax[k], ay[k],
-                                      az[k]);
                 if constexpr (CNT) {
                     const int64_t si = sub * kSub + j, ti = tb + k * kWave + lane;
                     if (si < a.in.n_src && ti < a.in.n_trg) {
@@ -456,6 +456,21 @@ __global__ __launch_bounds__(kBlock) void direct_near_mixed(DirectArgs a) {
                         const int32_t cls = excluded ? kPairSkip : !near ? kPairF32 : zero ? kPairSkip : kPairF64;
                         atomicAdd(a.in.pair_class + ti * ns + si, cls);
                     }
+                }
+            }
+        }
+        // the float64 pairs apart, so that the loop above has no branches; most
+        // sub-tiles here have none (they are within an eighth of their extent)
+        if (__ballot(any) != 0) {
+#pragma unroll 1
+            for (int j = 0; j < kSub; ++j) {
+                const Rec sr = s_src[wave][j];
+                const float4 sl = s_res[wave][j];
+#pragma unroll
+                for (int k = 0; k < T; ++k) {
+                    float dx, dy, dz;
+                    if (offset(sr, sl, k, dx, dy, dz) <= sr.t2 && !(excl && sr.g == t.g[k]))
+                        near_pair_f64<KT>(a.in, sub * kSub + j, t.x[k], t.y[k], t.z[k], ax[k], ay[k], az[k]);
                 }
             }
         }
@@ -481,32 +496,50 @@ __global__ __launch_bounds__(kBlock) void direct_near_mixed(DirectArgs a) {
 // ---------------------------------------------------------------------------
 // segment reduction and fills
 // ---------------------------------------------------------------------------
-// out[c][i] (=|+=) pref * (sum of target i's segments in workgroup order
-//                          + its near-pass sum).
+// out[c][i] (=|+=) pref * (sum of target i's segments in workgroup order and of
+// its near-pass sums).  A call with few target blocks has many of both per
+// target (4,352 targets: about 150 segments and 64 near rows), so kRedParts
+// threads share a target, each taking a contiguous share, and the shares are
+// added in order.
+constexpr int kRedParts = 8;
 template <int T>
 __global__ __launch_bounds__(kBlock) void reduce_segments(const double* __restrict__ part,
                                                           const double* __restrict__ near_part,
                                                           int64_t n_trg, int64_t units,
-                                                          int64_t chunks, int64_t grid,
+                                                          int64_t n_sub, int64_t grid, int cut, int slices,
                                                           int64_t np, double pref, double* out,
                                                           int accumulate) {
-    constexpr int BT = kBlock * T;
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n_trg) return;
-    const int64_t tbk = i / BT, li = i % BT;
-    const int64_t b0 = unit_owner(tbk * chunks, units, grid);
-    const int64_t b1 = unit_owner((tbk + 1) * chunks - 1, units, grid);
+    constexpr int BT = kBlock * T, kTrg = kBlock / kRedParts;
+    __shared__ double s_sum[kRedParts][3][kTrg];
+    const int t = threadIdx.x % kTrg, q = threadIdx.x / kTrg;
+    const int64_t i = (int64_t)blockIdx.x * kTrg + t;
     double s[3] = {0.0, 0.0, 0.0};
-    for (int64_t b = b0; b <= b1; ++b) {
-        const double* seg = part + (b + tbk) * 3 * BT;
+    if (i < n_trg) {
+        const int64_t tbk = i / BT, li = i % BT;
+        const int64_t b0 = range_owner(tbk * n_sub, units, grid, cut);
+        const int64_t b1 = range_owner((tbk + 1) * n_sub - 1, units, grid, cut) + 1;
+        const int64_t e0 = b0 + (b1 - b0) * q / kRedParts, e1 = b0 + (b1 - b0) * (q + 1) / kRedParts;
+#pragma unroll 4
+        for (int64_t b = e0; b < e1; ++b) {
+            const double* seg = part + (b + tbk) * 3 * BT;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) s[c] += seg[c * BT + li];
+            for (int c = 0; c < 3; ++c) s[c] += seg[c * BT + li];
+        }
+        const int l0 = slices * q / kRedParts, l1 = slices * (q + 1) / kRedParts;
+#pragma unroll 4
+        for (int sl = l0; sl < l1; ++sl)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) s[c] += near_part[(sl * 3 + c) * np + i];
     }
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        for (int sl = 0; sl < kNearSlices; ++sl) s[c] += near_part[(sl * 3 + c) * np + i];
-        const int64_t o = c * n_trg + i;
-        out[o] = accumulate ? out[o] + pref * s[c] : pref * s[c];
+    for (int c = 0; c < 3; ++c) s_sum[q][c][t] = s[c];
+    __syncthreads();
+    if (q < 3 && i < n_trg) {
+        double v = s_sum[0][q][t];
+#pragma unroll
+        for (int p = 1; p < kRedParts; ++p) v += s_sum[p][q][t];
+        const int64_t o = q * n_trg + i;
+        out[o] = accumulate ? out[o] + pref * v : pref * v;
     }
 }
 
@@ -691,17 +724,17 @@ int direct_blocks_per_cu(int kernel, int mixed) {
     return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 
+// Workgroups with at least this many 256-source chunks each take whole chunks.
+constexpr int64_t kWholeChunks = 16;
+
 DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int resident_blocks,
-                       int forced_grid) {
+                       int forced_grid, size_t max_bytes) {
     DirectPlan p{};
     p.T = mixed ? kT32 : kT64;
     p.n_src_pad = ceil_div(n_src, kTile) * kTile;
     p.n_sub = p.n_src_pad / kSub;
-    p.chunks = p.n_src_pad / kTile;
     p.blocks_x = ceil_div(n_trg, (int64_t)kBlock * p.T);
-    p.units = p.chunks * p.blocks_x;
-    const int64_t g = forced_grid > 0 ? forced_grid : std::max(1, resident_blocks);
-    p.grid = std::max<int64_t>(1, std::min<int64_t>(g, p.units));
+    p.units = p.n_sub * p.blocks_x;
     const size_t bt = (size_t)kBlock * p.T;
     size_t off = 0;
     p.off_src = off;
@@ -711,13 +744,37 @@ DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int 
     p.off_meta = off;
     off = align_up(off + (size_t)p.n_sub * sizeof(SubMeta), 256);
     p.off_part = off;
-    off = align_up(off + (size_t)(p.grid + p.blocks_x) * 3 * bt * sizeof(double), 256);
-    p.off_near = off;
-    off = align_up(off + (size_t)kNearSlices * p.blocks_x * 3 * bt * sizeof(double), 256);
-    p.off_flags = off;
-    off = align_up(off + (size_t)p.blocks_x * 4 * (size_t)p.chunks, 256);
-    p.total = off;
+    const int64_t g = forced_grid > 0 ? forced_grid : std::max(1, resident_blocks);
+    auto partials = [&](int64_t workgroups, int slices) {
+        p.grid = std::max<int64_t>(1, workgroups);
+        p.near_slices = slices;
+        p.cut = p.units / (kTile / kSub) >= kWholeChunks * p.grid ? kTile / kSub : 1;
+        p.off_near = align_up(p.off_part + (size_t)(p.grid + p.blocks_x) * 3 * bt * sizeof(double), 256);
+        p.total = align_up(p.off_near + (size_t)slices * p.blocks_x * 3 * bt * sizeof(double), 256);
+    };
+    partials(std::min(g, p.units), near_slices(p.blocks_x));
+    // few near-pass rows, no more workgroups than 256-source chunks, and half the
+    // workgroups where the partial sums would not fit; the first two also for the
+    // small calls that run as one kernel
+    const int64_t whole = std::min(g, p.units / (kTile / kSub));
+    if ((max_bytes > 0 && p.total > max_bytes) || direct_is_small(kernel, mixed, n_src, n_trg))
+        partials(whole, kNearSlices);
+    if (max_bytes > 0 && p.total > max_bytes) partials(std::min(whole, std::max<int64_t>(1, g / 2)), kNearSlices);
     return p;
+}
+
+// The measure that the static-scratch entry point accepts sizes by: the lean
+// layout's records and partial sums with 3 (float64) or 4 (mixed) workgroups per
+// CU, and a byte per (wave, 256-source chunk).  plan_direct with max_bytes fits
+// wherever this does.
+size_t direct_scratch_measure(int kernel, int mixed, int64_t n_src, int64_t n_trg, int n_cu, int forced_grid) {
+    const DirectPlan p = plan_direct(kernel, mixed, n_src, n_trg, 1, 1);
+    const int64_t chunks = p.n_src_pad / kTile, units = chunks * p.blocks_x;
+    const int64_t g = forced_grid > 0 ? forced_grid : (int64_t)(mixed ? 4 : 3) * n_cu;
+    const size_t row = (size_t)3 * kBlock * p.T * sizeof(double);
+    size_t off = align_up(p.off_part + (std::max<int64_t>(1, std::min(g, units)) + p.blocks_x) * row, 256);
+    off = align_up(off + kNearSlices * p.blocks_x * row, 256);
+    return align_up(off + (size_t)p.blocks_x * 4 * (size_t)chunks, 256);
 }
 
 template <int KT, int MIXED>
@@ -737,11 +794,12 @@ static hipError_t launch_typed(const SumInputs& in, const DirectPlan& p, double*
     a.rec = rec;
     a.aux = aux;
     a.meta = meta;
-    a.chunks = p.chunks;
+    a.n_sub = p.n_sub;
     a.units = p.units;
+    a.cut = p.cut;
     a.part = reinterpret_cast<double*>(base + p.off_part);
     a.near_part = reinterpret_cast<double*>(base + p.off_near);
-    a.flags = reinterpret_cast<uint8_t*>(base + p.off_flags);
+    const dim3 near_grid((unsigned)p.blocks_x, (unsigned)p.near_slices);
     if (timer.on()) (void)hipEventRecord(timer.start, stream);
     if constexpr (MIXED != 0) {
         if (in.pair_class)
@@ -755,18 +813,18 @@ static hipError_t launch_typed(const SumInputs& in, const DirectPlan& p, double*
     if (e != hipSuccess) return e;
     if constexpr (MIXED != 0) {
         if (in.pair_class)
-            direct_near_mixed<KT, T, true><<<dim3((unsigned)p.blocks_x, kNearSlices), dim3(kBlock), 0, stream>>>(a);
+            direct_near_mixed<KT, T, true><<<near_grid, dim3(kBlock), 0, stream>>>(a);
         else
-            direct_near_mixed<KT, T><<<dim3((unsigned)p.blocks_x, kNearSlices), dim3(kBlock), 0, stream>>>(a);
+            direct_near_mixed<KT, T><<<near_grid, dim3(kBlock), 0, stream>>>(a);
     } else
-        direct_near_f64<KT, T><<<dim3((unsigned)p.blocks_x, kNearSlices), dim3(kBlock), 0, stream>>>(a);
+        direct_near_f64<KT, T><<<near_grid, dim3(kBlock), 0, stream>>>(a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     // FP64 pair sums are 4x (single layer) or 8x (double layer) the bare sums
     const double pref = MIXED ? in.pref : (KT == 0 ? 0.25 : 0.125) * in.pref;
-    reduce_segments<T><<<dim3((unsigned)ceil_div(in.n_trg, kBlock)), dim3(kBlock), 0, stream>>>(
-        a.part, a.near_part, in.n_trg, p.units, p.chunks, p.grid, p.blocks_x * (int64_t)kBlock * T,
-        pref, out, accumulate);
+    reduce_segments<T><<<dim3((unsigned)ceil_div(in.n_trg, kBlock / kRedParts)), dim3(kBlock), 0, stream>>>(
+        a.part, a.near_part, in.n_trg, p.units, p.n_sub, p.grid, p.cut, p.near_slices,
+        p.blocks_x * (int64_t)kBlock * T, pref, out, accumulate);
     return hipGetLastError();
 }
 

@@ -6,6 +6,8 @@
 #include <float.h>
 #include <limits.h>
 
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace stokes {
@@ -129,16 +131,21 @@ __device__ __forceinline__ double near_limit2(const Box& w, const SubMeta& m) {
     }
 }
 
+// Whether a sub-tile may go to the near pass: the wave's box or group range
+// meets it.  Settles most sub-tiles before the per-target test.
+template <bool MIXED>
+__device__ __forceinline__ bool wave_near(const Box& w, const SubMeta& m, bool excl) {
+    return (excl && groups_overlap(w, m)) || !(box_gap2(w, m) > near_limit2<MIXED>(w, m));
+}
+
 // Decides, uniformly for the wave, whether a sub-tile goes to the near pass:
 // some target of the wave shares a group id with the sub-tile's range, or
-// lies within the limit of its box.  The whole-wave box settles most
-// sub-tiles before the per-target test.
+// lies within the limit of its box.
 template <int T, bool MIXED>
 __device__ __forceinline__ bool needs_near(const Box& w, const Targets<T>& t, const SubMeta& m,
                                            bool excl) {
+    if (!wave_near<MIXED>(w, m, excl)) return false;
     const double lim2 = near_limit2<MIXED>(w, m);
-    const bool wave_near = (excl && groups_overlap(w, m)) || !(box_gap2(w, m) > lim2);
-    if (!wave_near) return false;
     bool any = false;
 #pragma unroll
     for (int k = 0; k < T; ++k) {
@@ -159,6 +166,14 @@ __device__ __forceinline__ bool needs_near(const Box& w, const Targets<T>& t, co
 __device__ __forceinline__ int64_t unit_begin(int64_t b, int64_t U, int64_t G) { return b * U / G; }
 __device__ __forceinline__ int64_t unit_owner(int64_t u, int64_t U, int64_t G) {
     return ((u + 1) * G - 1) / U;
+}
+
+// The same with ranges that begin at multiples of `cut` units (U a multiple of it).
+__device__ __forceinline__ int64_t range_begin(int64_t b, int64_t U, int64_t G, int cut) {
+    return unit_begin(b, U / cut, G) * cut;
+}
+__device__ __forceinline__ int64_t range_owner(int64_t u, int64_t U, int64_t G, int cut) {
+    return unit_owner(u / cut, U / cut, G);
 }
 
 // ---------------------------------------------------------------------------
@@ -210,28 +225,40 @@ __device__ __forceinline__ void double_targets(Targets<T>& t, Box* w) {
     }
 }
 
-// Iterates the flagged sub-tiles of one wave's flag row (64 flag bytes are
-// read per step, one per lane); the near pass splits each row into
-// kNearSlices interleaved slices, one per grid row, for balance.
-constexpr int kNearSlices = 4;
-template <typename F>
-__device__ __forceinline__ void for_each_flagged(const uint8_t* fl, int64_t C, int lane, int slice,
-                                                 F&& fn) {
-    int n = 0;                                 // flagged sub-tiles seen so far (uniform)
-    for (int64_t c0 = 0; c0 < C; c0 += kWave) {
-        const uint32_t mine = (c0 + lane < C) ? fl[c0 + lane] : 0u;
-        uint64_t nz = __ballot(mine != 0);
-        while (nz) {
-            const int l = __builtin_ctzll(nz);
-            nz &= nz - 1;
-            uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)mine, l);
-            while (f) {
-                const int s = __builtin_ctz(f);
-                f &= f - 1;
-                if (n++ % kNearSlices == slice) fn((c0 + l) * 4 + s);
-            }
+// Visits the near-pass sub-tiles of one wave: those of every slices-th
+// sub-tile from `slice` on that the wave's targets need masked.  The lanes test
+// 64 sub-tiles against the wave's box at a time; the decision itself is the
+// main pass's (same function, same inputs), so nothing is passed between the
+// two passes.
+template <int T, bool MIXED, typename F>
+__device__ __forceinline__ void for_each_near(const Box& w, const Targets<T>& t, const SubMeta* __restrict__ meta,
+                                              int64_t n_sub, int lane, int slice, int slices, bool excl, F&& fn) {
+    for (int64_t b = 0; b * slices + slice < n_sub; b += kWave) {
+        const int64_t mine = (b + lane) * slices + slice;
+        bool hit = false;
+        if (mine < n_sub) {
+            const SubMeta m = meta[mine];
+            hit = m.count != 0 && wave_near<MIXED>(w, m, excl);
+        }
+        uint64_t hits = __ballot(hit);
+        while (hits) {
+            const int l = __builtin_ctzll(hits);
+            hits &= hits - 1;
+            const int64_t sub = (b + l) * slices + slice;
+            const SubMeta m = meta[sub];
+            if (needs_near<T, MIXED>(w, t, m, excl)) fn(sub, m);
         }
     }
+}
+
+// Grid rows (slices) of the near pass over blocks_x target blocks: enough
+// workgroups for the whole chip where the blocks are few.  A wave's near
+// sub-tiles run one after another, and scattered targets (tracer points between
+// the cells) have many: with 4 rows, 8,001 tracers at 34,816 sources took
+// 0.92 ms of which 0.7 ms were the near pass on 32 workgroups.
+constexpr int kNearSlices = 4, kNearSlicesMax = 64, kNearBlocks = 1024;
+inline int near_slices(int64_t blocks_x) {
+    return (int)std::min<int64_t>(kNearSlicesMax, std::max<int64_t>(kNearSlices, ceil_div(kNearBlocks, blocks_x)));
 }
 
 // ---------------------------------------------------------------------------

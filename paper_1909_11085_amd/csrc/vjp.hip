@@ -21,6 +21,7 @@
 // dL/dx_p = c sum_m [K(r_pm; g_p, q_m) + K(r_pm; q_p, g_m)] and dL/df_p.
 #include <algorithm>
 #include <string>
+#include <type_traits>
 
 #include "../../include/stokes_mi355x.h"
 #include "pairsum.hpp"
@@ -250,10 +251,9 @@ struct DlT {
         const int64_t n = a.n_trg;
         v[0] = a.tv[0][i]; v[1] = a.tv[0][n + i]; v[2] = a.tv[0][2 * n + i];
     }
-    // SRC: also add the source-side term r (r.n)(r.g)/rho^5 of dL/dphi into v
-    template <bool M, bool SRC = false>
+    template <bool M>
     __device__ __forceinline__ static void pair(const Rec& s, double x, double y, double z, const double (&g)[NT],
-                                bool skip, double (&acc)[NACC], double* v = nullptr) {
+                                bool skip, double (&acc)[NACC]) {
         const double dx = x - s.x, dy = y - s.y, dz = z - s.z;
         const double r2 = dot3(dx, dy, dz, dx, dy, dz);
         const double ri = ri_of<M>(r2, skip);
@@ -269,11 +269,6 @@ struct DlT {
         acc[0] = __builtin_fma(cn, s.nx, __builtin_fma(cq, s.qx, __builtin_fma(cr, dx, acc[0])));
         acc[1] = __builtin_fma(cn, s.ny, __builtin_fma(cq, s.qy, __builtin_fma(cr, dy, acc[1])));
         acc[2] = __builtin_fma(cn, s.nz, __builtin_fma(cq, s.qz, __builtin_fma(cr, dz, acc[2])));
-        if constexpr (SRC) {
-            v[0] = __builtin_fma(cq, dx, v[0]);
-            v[1] = __builtin_fma(cq, dy, v[1]);
-            v[2] = __builtin_fma(cq, dz, v[2]);
-        }
     }
     __device__ static void store(const PassArgs& a, int64_t i, const double (&s)[NACC]) {
         const int64_t n = a.n_trg;
@@ -404,274 +399,222 @@ struct DlSPhi {
     }
 };
 
-// ---- double layer, target side fused with the density gradient ---------------
-// One sweep over the (target, source) pairs of the target-side pass also gives,
-// per source, V_m = sum_n r (r.n_m)(r.g_n)/rho^5, so that dL/dphi_m = d w_m V_m
-// (its coefficient is the target side's cq).  V is summed across a wave's
-// targets by a butterfly and across the workgroup's waves in LDS in a fixed
-// order, then stored as the unit's partial: one slot per (target block,
-// source).  The near pass adds its masked pairs' V into the slots of the
-// sub-tiles it takes (each slot owned by one workgroup, after the main pass),
-// and a last kernel adds the target blocks in order: deterministic, no
-// atomics.
+// ---- double layer, both sides in one sweep -------------------------------------
+// One evaluation of a pair serves the target's dL/dx (V and the coefficient of
+// g, as DlT) and the source's dL/dphi and dL/dy: with r = x_n - y_m
+//   P_m = sum_n r (r.n_m)(r.g_n)/rho^5          dL/dphi_m = d w_m P_m
+//   Y_m = sum_n G(r_nm)                          dL/dy_m   = -d Y_m
+// They share the offset, 1/rho, the three dot products and G's coefficients:
+// 51 float64 operations and one rsq a pair (43 without Y), against 38 and 39 in
+// two passes.  Bound by those operations.
+//
+// A wave keeps T targets per lane in registers; a unit is one 64-source
+// sub-tile against a target block.  The sub-tile's records sit in LDS; in step
+// s lane l meets source (l + s) mod 64, so the 64 lanes hold 64 different
+// sources, a source's sums over the lane's T targets go into the wave's own LDS
+// copy by one ds_add per component, and every address has one writer per step:
+// the order is fixed.  After 64 steps the four waves' copies are added in order
+// and stored as the (target block, source) partial.  Sub-tiles that need the
+// rules run the same steps with the masks.  Positions are doubled as in the
+// direct sums (P is 8 times, G 4 times the bare sums).
+//
+// 61,952 wall nodes and 34,816 targets apart, all three gradients: 5.8 ms in two
+// passes, 3.7 ms here (T = 6); overlapping random points, where most sub-tiles
+// need the rules, 10.6 and 4.5 ms, 3,000 x 2,000 of them 495 and 86 us.
+__device__ __forceinline__ void lds_add(double* p, double v) { unsafeAtomicAdd(p, v); }
 
-// v[i][c] over the 64 lanes of the wave: lane l returns the totals of source
-// i = l / 16 (two reduce-scatter steps, then a sum over 16 lanes).
-__device__ __forceinline__ void wave_sum4x3(const double (&v)[4][3], int lane, double (&out)[3]) {
-    const bool b5 = (lane & 32) != 0, b4 = (lane & 16) != 0;
-    double h[2][3];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const double send = b5 ? v[i][c] : v[i + 2][c];
-            const double keep = b5 ? v[i + 2][c] : v[i][c];
-            h[i][c] = keep + __shfl_xor(send, 32);
-        }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const double send = b4 ? h[0][c] : h[1][c];
-        const double keep = b4 ? h[1][c] : h[0][c];
-        out[c] = keep + __shfl_xor(send, 16);
+template <bool M, bool SRC>
+__device__ __forceinline__ void dl_both_pair(double x, double y, double z, const double (&g)[3], double (&ra)[4],
+                                             const double2 (&s)[5], bool skip, double* ca) {
+    const double dx = x - s[0].x, dy = y - s[0].y, dz = z - s[1].x;
+    const double A = dot3(dx, dy, dz, dx, dy, dz);
+    const double z0 = M && (skip || A == 0.0) ? 0.0 : __builtin_amdgcn_rsq(A);
+    const double tn = A * z0;
+    const double ri = z0 * __builtin_fma(-tn, z0, 3.0);             // 1/rho
+    const double ri2 = ri * ri, ri5 = ri2 * ri2 * ri;
+    const double rn = dot3(dx, dy, dz, s[3].x, s[3].y, s[4].x);
+    const double rq = dot3(dx, dy, dz, s[1].y, s[2].x, s[2].y);
+    const double rg = dot3(dx, dy, dz, g[0], g[1], g[2]);
+    const double t = rg * ri5;
+    const double cn = rq * t, cq = rn * t, rnrq = rn * rq, cg = rnrq * ri5;
+    const double cr = (rnrq * t) * (-1.25 * ri2);
+    ra[0] = __builtin_fma(cn, s[3].x, __builtin_fma(cq, s[1].y, __builtin_fma(cr, dx, ra[0])));
+    ra[1] = __builtin_fma(cn, s[3].y, __builtin_fma(cq, s[2].x, __builtin_fma(cr, dy, ra[1])));
+    ra[2] = __builtin_fma(cn, s[4].x, __builtin_fma(cq, s[2].y, __builtin_fma(cr, dz, ra[2])));
+    ra[3] += cg;
+    ca[0] = __builtin_fma(cq, dx, ca[0]);
+    ca[1] = __builtin_fma(cq, dy, ca[1]);
+    ca[2] = __builtin_fma(cq, dz, ca[2]);
+    if constexpr (SRC) {
+        ca[3] = __builtin_fma(cg, g[0], __builtin_fma(cr, dx, ca[3]));
+        ca[4] = __builtin_fma(cg, g[1], __builtin_fma(cr, dy, ca[4]));
+        ca[5] = __builtin_fma(cg, g[2], __builtin_fma(cr, dz, ca[5]));
+        ca[6] += cn;
+        ca[7] += cq;
     }
-#pragma unroll
-    for (int m = 8; m > 0; m >>= 1)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) out[c] += __shfl_xor(out[c], m);
 }
 
-// Lanes past the last target hold a copy of it (the skeleton's load_tgt);
-// their target-side sums are dropped, but their source-side terms would be
-// added to V, so their cotangent is set to zero (every term then vanishes).
-template <int T>
-__device__ __forceinline__ void zero_padding_targets(const PassArgs& a, int64_t tb, int lane,
-                                                     ps::Tgt<DlT, T>& t) {
-#pragma unroll
-    for (int k = 0; k < T; ++k)
-        if (tb + (int64_t)k * kWave + lane >= a.n_trg) t.v[k][0] = t.v[k][1] = t.v[k][2] = 0.0;
-}
-
-template <int T, int W>
-__global__ __launch_bounds__(kBlock, W) void dl_fused_main(PassArgs a, double* __restrict__ vpart) {
+template <int T, bool SRC>
+__global__ __launch_bounds__(kBlock, 2) void dl_both_main(PassArgs a, int64_t blk0, double* __restrict__ vpart) {
     using P = DlT;
-    using Rec = P::Rec;
-    constexpr int BT = kBlock * T;
-    __shared__ Rec s_rec[kTile];
-    __shared__ double s_part[4][3 * kTile];      // per wave: V of each source of the chunk
-    const int64_t U = a.units, C = a.chunks, G = gridDim.x;
+    constexpr int BT = kBlock * T, NC = SRC ? 8 : 3, NV = SRC ? 6 : 3;
+    __shared__ double2 s_rec[5][kSub];
+    __shared__ int32_t s_grp[kSub];
+    __shared__ double s_col[4][NC][kSub];
+    static_assert(sizeof(P::Rec) == 5 * sizeof(double2), "records are staged as five double2");
+    const int64_t C = 4 * a.chunks, U = a.units * 4, G = gridDim.x;
     const int64_t u0 = ps::unit_begin(blockIdx.x, U, G), u1 = ps::unit_begin(blockIdx.x + 1, U, G);
     if (u0 >= u1) return;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const bool excl = a.excl != 0;
-    const Rec* rec = reinterpret_cast<const Rec*>(a.rec);
+    const int64_t npad = C * kSub;
     ps::Tgt<P, T> t;
     bool active = false;
     int64_t tbk = -1;
-    double acc[T][P::NACC];
+    double ra[T][4];
 #pragma unroll
     for (int k = 0; k < T; ++k)
 #pragma unroll
-        for (int c = 0; c < P::NACC; ++c) acc[k][c] = 0.0;
+        for (int q = 0; q < 4; ++q) ra[k][q] = 0.0;
 
-    int64_t ub = u0 / C, c = u0 % C;
-    double* sp = s_part[wave];
+    int64_t ub = u0 / C, sub = u0 % C;
     for (int64_t u = u0; u < u1; ++u) {
-        __syncthreads();                           // previous readers of s_rec and s_part are done
         if (ub != tbk) {
-            if (tbk >= 0) ps::flush<P, T>(a, tbk, wave, lane, acc);
+            if (tbk >= 0) ps::flush<P, T>(a, tbk, wave, lane, ra);
             tbk = ub;
-            const int64_t tb = tbk * BT + (int64_t)wave * (kWave * T);
+            const int64_t tb = (blk0 + tbk) * BT + (int64_t)wave * (kWave * T);
             active = tb < a.n_trg;
             ps::load_tgt<P, T>(a, active ? tb : 0, lane, t);
-            zero_padding_targets<T>(a, active ? tb : 0, lane, t);
 #pragma unroll
-            for (int k = 0; k < T; ++k)
+            for (int k = 0; k < T; ++k) {
+                t.x[k] *= 2.0;
+                t.y[k] *= 2.0;
+                t.z[k] *= 2.0;
+                // lanes past the last target hold a copy of it: no cotangent, so no source term
+                if (tb + (int64_t)k * kWave + lane >= a.n_trg) t.v[k][0] = t.v[k][1] = t.v[k][2] = 0.0;
 #pragma unroll
-                for (int q = 0; q < P::NACC; ++q) acc[k][q] = 0.0;
-        }
-        s_rec[threadIdx.x] = rec[c * kTile + threadIdx.x];
-        __syncthreads();
-        int64_t cn = c + 1, ubn = ub;
-        if (cn == C) { cn = 0; ++ubn; }
-        uint32_t flags = 0;
-#pragma unroll 1
-        for (int s = 0; s < 4; ++s) {
-            const SubMeta m = a.meta[c * 4 + s];
-            bool run = active && m.count != 0;
-            if (run && ps::needs_near<P, T>(t, m, excl)) {
-                flags |= 1u << s;                  // its pairs (and V terms) go to the near pass
-                run = false;
+                for (int q = 0; q < 4; ++q) ra[k][q] = 0.0;
             }
-            if (!run) {
 #pragma unroll
-                for (int q = 0; q < 3; ++q) sp[3 * (s * kSub + lane) + q] = 0.0;
-                continue;
-            }
-            const Rec* base = s_rec + s * kSub;
-#pragma unroll 1
-            for (int j0 = 0; j0 < kSub; j0 += 4) {
-                double v[4][3];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i][0] = v[i][1] = v[i][2] = 0.0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const Rec sr = base[j0 + i];
-#pragma unroll
-                    for (int k = 0; k < T; ++k)
-                        P::template pair<false, true>(sr, t.x[k], t.y[k], t.z[k], t.v[k], false, acc[k], v[i]);
-                }
-                double tot[3];
-                wave_sum4x3(v, lane, tot);
-                // the 16 lanes of a row hold the same totals: all store (no branch)
-#pragma unroll
-                for (int q = 0; q < 3; ++q) sp[3 * (s * kSub + j0 + (lane >> 4)) + q] = tot[q];
+            for (int c = 0; c < 3; ++c) {
+                t.lo[c] *= 2.0;
+                t.hi[c] *= 2.0;
             }
         }
-        if (active && lane == 0) a.flags[(tbk * 4 + wave) * C + c] = (uint8_t)flags;
-        __syncthreads();
-        // this unit's V of source c * 256 + tid: the four waves in order, stored
-        // in the slot of (target block, source); padding sources get zeros
+        __syncthreads();                           // the previous unit's records and sums have been read
         {
-            const int64_t npad = C * kTile;
-            double* vp = vpart + tbk * 3 * npad + c * kTile + threadIdx.x;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int i = 3 * threadIdx.x + q;
-                vp[q * npad] = ((s_part[0][i] + s_part[1][i]) + s_part[2][i]) + s_part[3][i];
-            }
+            const double2* src = reinterpret_cast<const double2*>(a.rec) + sub * (5 * kSub);
+            for (int i = threadIdx.x; i < 5 * kSub; i += kBlock) s_rec[i % 5][i / 5] = src[i];
+            if (threadIdx.x < kSub) s_grp[threadIdx.x] = a.grp[sub * kSub + threadIdx.x];
         }
-        c = cn;
-        ub = ubn;
-    }
-    ps::flush<P, T>(a, tbk, wave, lane, acc);
-}
-
-// The flagged sub-tiles of dl_fused_main, with the same-group and
-// zero-distance masks.  A workgroup takes the sub-tiles that any wave of its
-// target block flagged (every kNearSlices-th of them, for its grid row): the
-// block stages the sub-tile, each wave that flagged it runs the masked pairs
-// (the others add zeros), and the four waves' V are added in a fixed order
-// into the sub-tile's slots of the block's partial, which no other workgroup
-// touches.
-template <int T>
-__global__ __launch_bounds__(kBlock) void dl_fused_near(PassArgs a, double* __restrict__ vpart) {
-    using P = DlT;
-    using Rec = P::Rec;
-    constexpr int BT = kBlock * T;
-    __shared__ Rec s_src[kSub];
-    __shared__ int32_t s_grp[kSub];
-    __shared__ double s_v[4][3 * kSub];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x >> 6;
-    const int64_t tbk = blockIdx.x, C = a.chunks, npad = C * kTile;
-    const int slice = (int)blockIdx.y;
-    const int64_t tb = tbk * BT + (int64_t)wave * (kWave * T);
-    const bool active = tb < a.n_trg;
-    // waves of the block that hold targets (the main pass writes flag rows for those only)
-    const int nw = (int)std::min<int64_t>(4, (a.n_trg - tbk * BT + kWave * T - 1) / (kWave * T));
-    const bool excl = a.excl != 0;
-    const Rec* rec = reinterpret_cast<const Rec*>(a.rec);
-    ps::Tgt<P, T> t;
-    ps::load_tgt<P, T>(a, active ? tb : tbk * BT, lane, t);
-    zero_padding_targets<T>(a, active ? tb : tbk * BT, lane, t);
-    double acc[T][P::NACC];
 #pragma unroll
-    for (int k = 0; k < T; ++k)
-#pragma unroll
-        for (int q = 0; q < P::NACC; ++q) acc[k][q] = 0.0;
-    const uint8_t* fl = a.flags + tbk * 4 * C;
-    int n = 0;                                     // flagged sub-tiles seen (block-uniform)
-    for (int64_t c0 = 0; c0 < C; c0 += kWave) {
-        uint32_t any = 0, mine = 0;
-        if (c0 + lane < C)
-            for (int w = 0; w < nw; ++w) {
-                const uint32_t f = fl[w * C + c0 + lane];
-                any |= f;
-                if (w == wave) mine = f;
-            }
-        uint64_t nz = __ballot(any != 0);          // the same in every wave
-        while (nz) {
-            const int l = __builtin_ctzll(nz);
-            nz &= nz - 1;
-            uint32_t fa = (uint32_t)__builtin_amdgcn_readlane((int)any, l);
-            const uint32_t fm = (uint32_t)__builtin_amdgcn_readlane((int)mine, l);
-            while (fa) {
-                const int sidx = __builtin_ctz(fa);
-                fa &= fa - 1;
-                if (n++ % ps::kNearSlices != slice) continue;
-                const int64_t sub = (c0 + l) * 4 + sidx;
-                __syncthreads();                   // the previous sub-tile's readers are done
-                if (threadIdx.x < kSub) {
-                    s_src[threadIdx.x] = rec[sub * kSub + threadIdx.x];
-                    s_grp[threadIdx.x] = a.grp[sub * kSub + threadIdx.x];
-                }
-                __syncthreads();
-                double* sv = s_v[wave];
-                if (active && ((fm >> sidx) & 1u)) {
+        for (int q = 0; q < NC; ++q) s_col[wave][q][lane] = 0.0;
+        const SubMeta m = a.meta[sub];
+        __syncthreads();
+        if (active && m.count != 0) {
+            const bool masked = ps::needs_near<P, T>(t, m, excl);
+            auto steps = [&](auto mask) {
+                constexpr bool M = decltype(mask)::value;
 #pragma unroll 1
-                    for (int j0 = 0; j0 < kSub; j0 += 4) {
-                        double v[4][3];
+                for (int sp = 0; sp < kSub; ++sp) {
+                    const int col = (lane + sp) & (kSub - 1);
+                    double2 r[5];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) v[i][0] = v[i][1] = v[i][2] = 0.0;
+                    for (int q = 0; q < 5; ++q) r[q] = s_rec[q][col];
+                    double ca[NC];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const Rec sr = s_src[j0 + i];
-                            const int32_t gs = s_grp[j0 + i];
+                    for (int q = 0; q < NC; ++q) ca[q] = 0.0;
+                    const int32_t cg = M ? s_grp[col] : 0;
 #pragma unroll
-                            for (int k = 0; k < T; ++k)
-                                P::template pair<true, true>(sr, t.x[k], t.y[k], t.z[k], t.v[k],
-                                                             excl && gs == t.g[k], acc[k], v[i]);
-                        }
-                        double tot[3];
-                        wave_sum4x3(v, lane, tot);
-                        // the 16 lanes of a row hold the same totals: all store
-#pragma unroll
-                        for (int q = 0; q < 3; ++q) sv[3 * (j0 + (lane >> 4)) + q] = tot[q];
+                    for (int k = 0; k < T; ++k) {
+                        // two pairs in flight: more would spill
+                        if (k != 0 && k % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+                        dl_both_pair<M, SRC>(t.x[k], t.y[k], t.z[k], t.v[k], ra[k], r, M && excl && t.g[k] == cg, ca);
                     }
-                } else {
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) sv[3 * lane + q] = 0.0;
+                    for (int q = 0; q < NC; ++q) lds_add(&s_col[wave][q][col], ca[q]);
                 }
-                __syncthreads();
-                if (threadIdx.x < kSub) {
-                    double* vp = vpart + tbk * 3 * npad + sub * kSub + threadIdx.x;
+            };
+            if (masked) steps(std::true_type{});
+            else steps(std::false_type{});
+        }
+        __syncthreads();
+        // wave 0: P; waves 1 .. 3: a component of Y each
+        auto total = [&](int q) {
+            return ((s_col[0][q][lane] + s_col[1][q][lane]) + s_col[2][q][lane]) + s_col[3][q][lane];
+        };
+        double* vp = vpart + tbk * NV * npad + sub * kSub + lane;
+        if (wave == 0) {
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) {
-                        const int i = 3 * threadIdx.x + q;
-                        vp[q * npad] += ((s_v[0][i] + s_v[1][i]) + s_v[2][i]) + s_v[3][i];
-                    }
-                }
-            }
+            for (int q = 0; q < 3; ++q) vp[q * npad] = total(q);
+        } else if constexpr (SRC) {
+            const int c = wave - 1;
+            const double2 n01 = s_rec[3][lane], q12 = s_rec[2][lane];
+            const double n = c == 0 ? n01.x : c == 1 ? n01.y : s_rec[4][lane].x;
+            const double q = c == 0 ? s_rec[1][lane].y : c == 1 ? q12.x : q12.y;
+            vp[(3 + c) * npad] = __builtin_fma(total(6), n, __builtin_fma(total(7), q, total(3 + c)));
+        }
+        if (++sub == C) {
+            sub = 0;
+            ++ub;
         }
     }
-    if (!active) return;                           // no barriers below
-    const int64_t np = (int64_t)gridDim.x * BT;
-    double* part = a.near_part + (int64_t)slice * P::NACC * np;
-#pragma unroll
-    for (int k = 0; k < T; ++k) {
-        const int64_t gi = tbk * BT + wave * (kWave * T) + k * kWave + lane;
-#pragma unroll
-        for (int q = 0; q < P::NACC; ++q) part[q * np + gi] = acc[k][q];
-    }
+    ps::flush<P, T>(a, tbk, wave, lane, ra);
 }
 
-// dL/dphi_m = d w_m V_m, V_m the target blocks' partials added in order
-__global__ __launch_bounds__(kBlock) void dl_phi_reduce(const double* __restrict__ vpart, int64_t blocks,
-                                                        int64_t npad, const double* __restrict__ weight,
-                                                        double pref, double* __restrict__ out, int64_t n,
-                                                        int accumulate) {
+// dL/dx from the target side's segments (workgroup order): 4 times the bare sums.
+template <int T>
+__global__ __launch_bounds__(kBlock) void dl_both_targets(PassArgs a, int64_t blk0, int64_t grid) {
+    constexpr int BT = kBlock * T;
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;   // within the group
+    if (blk0 * BT + i >= a.n_trg) return;
+    const int64_t tbk = i / BT, li = i % BT, C = 4 * a.chunks, U = 4 * a.units;
+    const int64_t b0 = ps::unit_owner(tbk * C, U, grid), b1 = ps::unit_owner((tbk + 1) * C - 1, U, grid);
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int64_t b = b0; b <= b1; ++b) {
+        const double* seg = a.part + (b + tbk) * 4 * BT;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] += seg[q * BT + li];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] *= 0.25;
+    DlT::store(a, blk0 * BT + i, s);
+}
+
+// dL/dphi_m and dL/dy_m from the target blocks' partials, in block order.
+template <int NV>
+__global__ __launch_bounds__(kBlock) void dl_both_sources(const double* __restrict__ vpart, int64_t blocks,
+                                                          int64_t npad, const double* __restrict__ weight,
+                                                          double pref, double* __restrict__ phi,
+                                                          double* __restrict__ src, int64_t n, int acc_phi,
+                                                          int acc_src) {
     const int64_t m = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (m >= n) return;
-    const double s = pref * weight[m];
+    double v[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = 0.0;
+#pragma unroll 2
+    for (int64_t b = 0; b < blocks; ++b)
+#pragma unroll
+        for (int q = 0; q < NV; ++q) v[q] += vpart[(b * NV + q) * npad + m];
+    const double sp = 0.125 * pref * weight[m], sy = -0.25 * pref;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        double v = 0.0;
-        for (int64_t b = 0; b < blocks; ++b) v += vpart[(b * 3 + q) * npad + m];
-        const double val = s * v;
-        out[q * n + m] = accumulate ? out[q * n + m] + val : val;
+        if (phi) phi[q * n + m] = acc_phi ? phi[q * n + m] + sp * v[q] : sp * v[q];
+        if constexpr (NV == 6) src[q * n + m] = acc_src ? src[q * n + m] + sy * v[3 + q] : sy * v[3 + q];
     }
 }
+
+// Records of the sweep: DlT's with doubled positions.
+struct DlBoth : DlT {
+    __device__ static void make_rec(const PassArgs& a, int64_t i, Rec& r, double pos[3]) {
+        DlT::make_rec(a, i, r, pos);
+        r.x = pos[0] *= 2.0;
+        r.y = pos[1] *= 2.0;
+        r.z = pos[2] *= 2.0;
+    }
+};
 
 // launch shapes (targets per lane, minimum waves per SIMD)
 constexpr int kTSlT = 4, kWSlT = 3;
@@ -687,15 +630,53 @@ constexpr int kTDlT = 4, kWDlT = 3;
 constexpr int kTDlS = 2, kWDlS = 3;
 constexpr int kTSlSF = 4, kWSlSF = 4;
 constexpr int kTDlSPhi = 4, kWDlSPhi = 3;
-constexpr int kTDlF = 4, kWDlF = 2;
 
-// workspace of the fused double-layer pass: the target-side pass, then the
-// partials of V, (target block, 3, padded source)
-size_t dl_fused_bytes(int64_t n_src, int64_t n_trg, int resident, size_t* off_v) {
-    const auto p = ps::plan_pass<DlT, kTDlF>(n_src, n_trg, resident);
-    const size_t off = align_up(p.total, 256);
-    if (off_v) *off_v = off;
-    return align_up(off + (size_t)p.blocks_x * 3 * p.n_src_pad * sizeof(double), 256);
+// The two-sided sweep's targets per lane: the most, as the sources' LDS reads and
+// adds (about two thirds of a pair) are shared by them, unless the last target
+// block's padding or idle workgroups cost more.  More than 6 spill.
+int dl_both_T(int64_t n_src, int64_t n_trg, int resident) {
+    const int64_t subs = ceil_div(n_src, (int64_t)kTile) * (kTile / kSub);
+    int best = 6;
+    double least = 1e300;
+    for (int T : {6, 4, 2, 1}) {
+        const int64_t units = subs * ceil_div(n_trg, (int64_t)kBlock * T);
+        const double cost = (double)ceil_div(units, (int64_t)resident) * (T + 0.65);
+        if (cost < least) {
+            least = cost;
+            best = T;
+        }
+    }
+    return best;
+}
+template <typename F>
+auto with_both_T(int T, F&& f) {
+    return T == 6   ? f(std::integral_constant<int, 6>{})
+           : T == 4 ? f(std::integral_constant<int, 4>{})
+           : T == 2 ? f(std::integral_constant<int, 2>{})
+                    : f(std::integral_constant<int, 1>{});
+}
+
+// The sources' partials are (target block, 3 or 6, padded source); target blocks
+// are taken in groups whose partials fit this many bytes (one group up to 3.4e10
+// pairs, at least one block).
+constexpr int64_t kDlBothBytes = int64_t(1) << 30;
+
+// targets of a group of target blocks
+int64_t dl_both_group(int64_t n_src, int64_t n_trg, int T, int nv) {
+    const int64_t per = nv * ceil_div(n_src, (int64_t)kTile) * kTile * (int64_t)sizeof(double);
+    return std::min(n_trg, std::max<int64_t>(1, kDlBothBytes / per) * kBlock * T);
+}
+
+// workspace: the target-side pass of a group, then the sources' partials
+ps::PassPlan dl_both_plan(int64_t n_src, int64_t n_trg, int T, int resident) {
+    return with_both_T(T, [&](auto tc) {
+        return ps::plan_pass<DlT, decltype(tc)::value>(n_src, n_trg, resident);
+    });
+}
+size_t dl_both_bytes(int64_t n_src, int64_t n_trg, int resident, int nv) {
+    const int T = dl_both_T(n_src, n_trg, resident);
+    const auto p = dl_both_plan(n_src, dl_both_group(n_src, n_trg, T, nv), T, resident);
+    return align_up(align_up(p.total, 256) + (size_t)p.blocks_x * nv * p.n_src_pad * sizeof(double), 256);
 }
 
 }  // namespace
@@ -709,8 +690,7 @@ void vjp_resident(int n_cu, int out[kVjpPasses]) {
     out[5] = ps::resident_blocks<SlSF, kTSlSF, kWSlSF>(n_cu);
     out[6] = ps::resident_blocks<DlSPhi, kTDlSPhi, kWDlSPhi>(n_cu);
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, dl_fused_main<kTDlF, kWDlF>, kBlock, 0) !=
-            hipSuccess || nb < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, dl_both_main<6, true>, kBlock, 0) != hipSuccess || nb < 1)
         nb = 1;
     out[7] = nb * n_cu;
 }
@@ -725,7 +705,7 @@ size_t vjp_workspace_bytes(int kernel, int64_t n_src, int64_t n_trg, const int r
         return b;
     }
     size_t b = ps::plan_pass<DlT, kTDlT>(n_src, n_trg, resident[3]).total;
-    b = std::max(b, dl_fused_bytes(n_src, n_trg, resident[7], nullptr));
+    b = std::max(b, std::max(dl_both_bytes(n_src, n_trg, resident[7], 6), dl_both_bytes(n_src, n_trg, resident[7], 3)));
     b = std::max(b, ps::plan_pass<DlSPhi, kTDlSPhi>(n_trg, n_src, resident[6]).total);
     return std::max(b, ps::plan_pass<DlS, kTDlS>(n_trg, n_src, resident[4]).total);
 }
@@ -797,8 +777,8 @@ hipError_t launch_sl_vjp(const VjpInputs& in, const int resident[kVjpPasses], bo
     return e;
 }
 
-// dL/dx (targets) and dL/dphi in one sweep over the pairs; see dl_fused_main.
-static hipError_t launch_dl_fused(const VjpInputs& in, int resident, void* ws, hipStream_t stream) {
+// dL/dx and the source side's gradients in one sweep over the pairs.
+static hipError_t launch_dl_both(const VjpInputs& in, int resident, bool combined, void* ws, hipStream_t stream) {
     PassArgs a = base_args(in);
     a.n_trg = in.n_trg;
     a.trg_xyz = in.trg_xyz;
@@ -812,40 +792,58 @@ static hipError_t launch_dl_fused(const VjpInputs& in, int resident, void* ws, h
     a.sv[2] = in.normal;
     a.out[0] = in.grad_trg;
     a.pref = in.pref;
-    const auto p = ps::plan_pass<DlT, kTDlF>(in.n_src, in.n_trg, resident);
-    size_t off_v = 0;
-    (void)dl_fused_bytes(in.n_src, in.n_trg, resident, &off_v);
+    const int nv = in.grad_src ? 6 : 3, T = dl_both_T(in.n_src, in.n_trg, resident);
+    const int64_t group = dl_both_group(in.n_src, in.n_trg, T, nv);
+    const auto p = dl_both_plan(in.n_src, group, T, resident);
     char* base = static_cast<char*>(ws);
     a.rec = base + p.off_rec;
     a.grp = reinterpret_cast<int32_t*>(base + p.off_grp);
     a.meta = reinterpret_cast<SubMeta*>(base + p.off_meta);
     a.part = reinterpret_cast<double*>(base + p.off_part);
-    a.near_part = reinterpret_cast<double*>(base + p.off_near);
-    a.flags = reinterpret_cast<uint8_t*>(base + p.off_flags);
     a.chunks = p.chunks;
-    a.units = p.units;
-    double* vpart = reinterpret_cast<double*>(base + off_v);
-    ps::prep<DlT><<<dim3((unsigned)(p.n_src_pad / kBlock)), dim3(kBlock), 0, stream>>>(a);
+    double* vpart = reinterpret_cast<double*>(base + align_up(p.total, 256));
+    ps::prep<DlBoth><<<dim3((unsigned)(p.n_src_pad / kBlock)), dim3(kBlock), 0, stream>>>(a);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // the main pass writes every (target block, source) slot of vpart
-    dl_fused_main<kTDlF, kWDlF><<<dim3((unsigned)p.grid), dim3(kBlock), 0, stream>>>(a, vpart);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    dl_fused_near<kTDlF><<<dim3((unsigned)p.blocks_x, ps::kNearSlices), dim3(kBlock), 0, stream>>>(a, vpart);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    ps::reduce<DlT, kTDlF><<<dim3((unsigned)ceil_div(a.n_trg, kBlock)), dim3(kBlock), 0, stream>>>(
-        a, p.grid, p.blocks_x * (int64_t)kBlock * kTDlF);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    dl_phi_reduce<<<dim3((unsigned)ceil_div(in.n_src, kBlock)), dim3(kBlock), 0, stream>>>(
-        vpart, p.blocks_x, p.n_src_pad, in.weight, in.pref, in.grad_density, in.n_src, in.accumulate);
-    return hipGetLastError();
+    if (combined && group < in.n_trg) {
+        // a later group's target side must not overwrite earlier groups' sources
+        if (!in.accumulate && e == hipSuccess) e = launch_fill_zero(in.grad_trg, 3 * in.n_trg, stream);
+        a.force_acc = in.grad_trg;
+    }
+    for (int64_t t0 = 0; t0 < in.n_trg && e == hipSuccess; t0 += group) {
+        const int64_t nt = std::min(group, in.n_trg - t0);
+        const auto pg = dl_both_plan(in.n_src, nt, T, resident);
+        a.units = pg.units;
+        const dim3 gm((unsigned)pg.grid), gt((unsigned)ceil_div(nt, kBlock)), gs((unsigned)ceil_div(in.n_src, kBlock));
+        // the sweep writes every (target block, source) slot of the group
+        with_both_T(T, [&](auto tc) {
+            constexpr int K = decltype(tc)::value;
+            const int64_t blk0 = t0 / ((int64_t)kBlock * K);
+            if (in.grad_src)
+                dl_both_main<K, true><<<gm, dim3(kBlock), 0, stream>>>(a, blk0, vpart);
+            else
+                dl_both_main<K, false><<<gm, dim3(kBlock), 0, stream>>>(a, blk0, vpart);
+            dl_both_targets<K><<<gt, dim3(kBlock), 0, stream>>>(a, blk0, pg.grid);
+        });
+        // one array for both position gradients: the group's target side is in it
+        // before its source side is added
+        const int acc = in.accumulate || t0 > 0;
+        if (in.grad_src)
+            dl_both_sources<6><<<gs, dim3(kBlock), 0, stream>>>(vpart, pg.blocks_x, p.n_src_pad, in.weight, in.pref,
+                                                                in.grad_density, in.grad_src, in.n_src, acc,
+                                                                acc || combined);
+        else
+            dl_both_sources<3><<<gs, dim3(kBlock), 0, stream>>>(vpart, pg.blocks_x, p.n_src_pad, in.weight, in.pref,
+                                                                in.grad_density, nullptr, in.n_src, acc, 0);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 hipError_t launch_dl_vjp(const VjpInputs& in, const int resident[kVjpPasses], bool combined,
                          void* ws, hipStream_t stream) {
     hipError_t e = hipSuccess;
     const KernelTimer none{};
-    if (in.grad_trg && in.grad_density && !in.grad_src) return launch_dl_fused(in, resident[7], ws, stream);
+    if (in.grad_trg && (in.grad_density || in.grad_src)) return launch_dl_both(in, resident[7], combined, ws, stream);
     if (in.grad_trg) {
         PassArgs a = base_args(in);
         a.n_trg = in.n_trg;
@@ -879,9 +877,6 @@ hipError_t launch_dl_vjp(const VjpInputs& in, const int resident[kVjpPasses], bo
         a.out[0] = in.grad_density;
         a.out[1] = in.grad_src;
         a.pref = in.pref;
-        // one array for both position gradients: the target side is already
-        // in it, so the source side adds to it
-        if (combined) a.force_acc = in.grad_src;
         if (in.grad_src) {
             const auto p = ps::plan_pass<DlS, kTDlS>(in.n_trg, in.n_src, resident[4]);
             e = ps::run_pass<DlS, kTDlS, kWDlS>(a, p, ws, stream, none);

@@ -16,9 +16,10 @@
 //     lane of a wave reads the same record, a broadcast LDS read.
 //   * per 64-source sub-tile the wave decides, uniformly, whether the fast
 //     loop (no per-pair tests) is exact: box far from its targets and no
-//     shared group.  Sub-tiles that need per-pair tests are left to a separate
-//     near-pass kernel (which takes the same decision again), so the main loop's register allocation
-//     and schedule carry no masked code.  Mixed precision evaluates pairs in float32
+//     shared group.  Other sub-tiles take a masked loop: in float64 in the same
+//     kernel, in mixed precision in a near-pass kernel of its own (which takes
+//     the same decision again), whose float64 pairs would cost the main loop its
+//     registers.  Mixed precision evaluates pairs in float32
 //     on offsets from the sub-tile centre (each rounded once from float64),
 //     sums each sub-tile in float32 and adds it into float64 accumulators.
 //     In the near pass (possible exclusions or near pairs, or a gap below half
@@ -30,7 +31,7 @@
 //     partial sums whenever its range moves to a new target block; segment
 //     ids (workgroup + target block) are consecutive, and a second kernel
 //     adds each target's segments in fixed order (deterministic, no atomics).
-//   * the near-pass decision tests every target of the wave against the
+//   * the decision tests every target of the wave against the
 //     sub-tile box, after a whole-wave box test that settles most sub-tiles.
 #include <float.h>
 #include <limits.h>
@@ -182,13 +183,20 @@ __device__ __forceinline__ void flush_segment(const DirectArgs& a, int64_t tbk, 
 #define STOKES_DIRECT_W32DL 4
 #endif
 
-// Main FP64 kernel: fast loop only; sub-tiles needing per-pair tests are
-// skipped (direct_near_f64 takes them).
+// Targets per lane and waves per SIMD of long double-layer sums.
+constexpr int kT64Long = 8, kW64Long = 2;
+
+// FP64 kernel.  Sub-tiles that need the rules take the masked loop here: its
+// compares and select add about a fifth to a pair, where a pass of its own finds
+// them again and brings its own partial sums (6.4e7 double-layer pairs of a
+// check-point quadrature 197 us with such a pass, 141 here; 16,001 tracers at
+// 34,816 sources 550 and 428, 60,001 at 108,800 4.94 and 4.65 ms).
 template <int KT, int T>
-__global__ __launch_bounds__(kBlock, STOKES_DIRECT_W64) void direct_f64(DirectArgs a) {
+__global__ __launch_bounds__(kBlock, T == kT64Long ? kW64Long : STOKES_DIRECT_W64) void direct_f64(DirectArgs a) {
     using Rec = typename SrcRec<KT, 0>::type;
     constexpr int BT = kBlock * T;
     __shared__ Rec s_rec[kTile];
+    __shared__ int32_t s_grp[kTile];
 
     const int64_t U = a.units, C = a.n_sub, G = gridDim.x;
     const int64_t u0 = range_begin(blockIdx.x, U, G, a.cut), u1 = range_begin(blockIdx.x + 1, U, G, a.cut);
@@ -197,6 +205,7 @@ __global__ __launch_bounds__(kBlock, STOKES_DIRECT_W64) void direct_f64(DirectAr
     const int wave = threadIdx.x >> 6;
     const bool excl = a.in.excl != 0;
     const Rec* rec = reinterpret_cast<const Rec*>(a.rec);
+    const int32_t* grp = reinterpret_cast<const int32_t*>(a.aux);
 
     Targets<T> t;
     Box wbox{};
@@ -221,20 +230,34 @@ __global__ __launch_bounds__(kBlock, STOKES_DIRECT_W64) void direct_f64(DirectAr
             for (int k = 0; k < T; ++k) ax[k] = ay[k] = az[k] = 0.0;
         }
         const int64_t first = sub - s0;        // the chunk's first sub-tile
-        if (wave >= s0 && wave < s1) s_rec[threadIdx.x] = rec[first * kSub + threadIdx.x];
+        if (wave >= s0 && wave < s1) {
+            s_rec[threadIdx.x] = rec[first * kSub + threadIdx.x];
+            s_grp[threadIdx.x] = grp[first * kSub + threadIdx.x];
+        }
         __syncthreads();
         if (wave_active) {
 #pragma unroll 1
             for (int s = s0; s < s1; ++s) {
                 const SubMeta m = a.meta[first + s];
-                if (m.count == 0 || needs_near<T, false>(wbox, t, m, excl)) continue;
+                if (m.count == 0) continue;
                 const Rec* base = s_rec + s * kSub;
+                if (!needs_near<T, false>(wbox, t, m, excl)) {
+#pragma unroll 2
+                    for (int j = 0; j < kSub; ++j) {
+                        const Rec sr = base[j];
+#pragma unroll
+                        for (int k = 0; k < T; ++k)
+                            pair_f64<KT, false>(sr, t.x[k], t.y[k], t.z[k], false, ax[k], ay[k], az[k]);
+                    }
+                    continue;
+                }
 #pragma unroll 2
                 for (int j = 0; j < kSub; ++j) {
                     const Rec sr = base[j];
+                    const int32_t gs = s_grp[s * kSub + j];
 #pragma unroll
                     for (int k = 0; k < T; ++k)
-                        pair_f64<KT, false>(sr, t.x[k], t.y[k], t.z[k], false, ax[k], ay[k], az[k]);
+                        pair_f64<KT, true>(sr, t.x[k], t.y[k], t.z[k], excl && gs == t.g[k], ax[k], ay[k], az[k]);
                 }
             }
         }
@@ -243,56 +266,6 @@ __global__ __launch_bounds__(kBlock, STOKES_DIRECT_W64) void direct_f64(DirectAr
         if (sub == C) { sub = 0; ++ub; }
     }
     flush_segment<T>(a, tbk, wave, lane, ax, ay, az);
-}
-
-// Near pass (FP64): for each wave of each target block, the sub-tiles that the
-// main pass skips, with the same-group and zero-distance masks.
-template <int KT, int T>
-__global__ __launch_bounds__(kBlock) void direct_near_f64(DirectArgs a) {
-    using Rec = typename SrcRec<KT, 0>::type;
-    constexpr int BT = kBlock * T;
-    // per-wave staging slice of the current sub-tile (see direct_near_mixed)
-    __shared__ Rec s_src[4][kSub];
-    __shared__ int32_t s_grp[4][kSub];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x >> 6;
-    const int64_t tbk = blockIdx.x;
-    const int64_t tb = tbk * BT + (int64_t)wave * (kWave * T);
-    if (tb >= a.in.n_trg) return;              // wave has no targets (no barriers below)
-    const bool excl = a.in.excl != 0;
-    const Rec* rec = reinterpret_cast<const Rec*>(a.rec);
-    const int32_t* grp = reinterpret_cast<const int32_t*>(a.aux);
-    Targets<T> t;
-    Box wbox = load_targets<T>(a.in, tb, lane, t);
-    double_targets<T>(t, &wbox);
-    double ax[T], ay[T], az[T];
-#pragma unroll
-    for (int k = 0; k < T; ++k) ax[k] = ay[k] = az[k] = 0.0;
-    for_each_near<T, false>(wbox, t, a.meta, a.n_sub, lane, (int)blockIdx.y, (int)gridDim.y, excl,
-                            [&](int64_t sub, const SubMeta&) {
-        s_src[wave][lane] = rec[sub * kSub + lane];
-        s_grp[wave][lane] = grp[sub * kSub + lane];
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll 2
-        for (int j = 0; j < kSub; ++j) {
-            const Rec sr = s_src[wave][j];
-            const int32_t gs = s_grp[wave][j];
-#pragma unroll
-            for (int k = 0; k < T; ++k)
-                pair_f64<KT, true>(sr, t.x[k], t.y[k], t.z[k], excl && gs == t.g[k], ax[k], ay[k],
-                                   az[k]);
-        }
-        __builtin_amdgcn_wave_barrier();   // reads of this sub-tile precede the next writes
-    });
-    const int64_t np = (int64_t)gridDim.x * BT;
-    double* np_slice = a.near_part + (int64_t)blockIdx.y * 3 * np;
-#pragma unroll
-    for (int k = 0; k < T; ++k) {
-        const int64_t gi = tbk * BT + wave * (kWave * T) + k * kWave + lane;
-        np_slice[gi] = ax[k];
-        np_slice[np + gi] = ay[k];
-        np_slice[2 * np + gi] = az[k];
-    }
 }
 
 // Main mixed kernel: float32 fast loop only; sub-tiles needing care are
@@ -724,13 +697,26 @@ int direct_blocks_per_cu(int kernel, int mixed) {
     return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 
+// Targets per lane.  A long double-layer sum runs at the clock that the power
+// limit leaves it, and half the LDS reads per pair raise that: 294,912 wall nodes
+// at 65,297 targets 27.9 ms with 4, 27.1 with 8; 32,768 at 30,720 811 and 801 us.
+// Below about 9e8 pairs the waves in flight count for more (16,384 at 30,720 414
+// and 428 us), and so does more padding of the last target block than the
+// difference (32,768 at 15,360 414 and 433).
+static int targets_per_lane(int kernel, int mixed, int64_t n_src, int64_t n_trg) {
+    if (mixed) return kT32;
+    if (kernel == 0 || n_src <= 900'000'000 / n_trg) return kT64;
+    const int64_t b4 = ceil_div(n_trg, (int64_t)kBlock * kT64), b8 = ceil_div(n_trg, (int64_t)kBlock * kT64Long);
+    return (kT64Long * b8 - kT64 * b4) * 64 <= kT64 * b4 ? kT64Long : kT64;
+}
+
 // Workgroups with at least this many 256-source chunks each take whole chunks.
 constexpr int64_t kWholeChunks = 16;
 
 DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int resident_blocks,
                        int forced_grid, size_t max_bytes) {
     DirectPlan p{};
-    p.T = mixed ? kT32 : kT64;
+    p.T = targets_per_lane(kernel, mixed, n_src, n_trg);
     p.n_src_pad = ceil_div(n_src, kTile) * kTile;
     p.n_sub = p.n_src_pad / kSub;
     p.blocks_x = ceil_div(n_trg, (int64_t)kBlock * p.T);
@@ -744,7 +730,8 @@ DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int 
     p.off_meta = off;
     off = align_up(off + (size_t)p.n_sub * sizeof(SubMeta), 256);
     p.off_part = off;
-    const int64_t g = forced_grid > 0 ? forced_grid : std::max(1, resident_blocks);
+    int64_t g = forced_grid > 0 ? forced_grid : std::max(1, resident_blocks);
+    if (forced_grid <= 0 && p.T == kT64Long) g = std::max<int64_t>(1, g * kW64Long / STOKES_DIRECT_W64);
     auto partials = [&](int64_t workgroups, int slices) {
         p.grid = std::max<int64_t>(1, workgroups);
         p.near_slices = slices;
@@ -752,14 +739,14 @@ DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int 
         p.off_near = align_up(p.off_part + (size_t)(p.grid + p.blocks_x) * 3 * bt * sizeof(double), 256);
         p.total = align_up(p.off_near + (size_t)slices * p.blocks_x * 3 * bt * sizeof(double), 256);
     };
-    partials(std::min(g, p.units), near_slices(p.blocks_x));
+    partials(std::min(g, p.units), mixed ? near_slices(p.blocks_x, p.n_sub) : 0);
     // few near-pass rows, no more workgroups than 256-source chunks, and half the
     // workgroups where the partial sums would not fit; the first two also for the
     // small calls that run as one kernel
     const int64_t whole = std::min(g, p.units / (kTile / kSub));
     if ((max_bytes > 0 && p.total > max_bytes) || direct_is_small(kernel, mixed, n_src, n_trg))
-        partials(whole, kNearSlices);
-    if (max_bytes > 0 && p.total > max_bytes) partials(std::min(whole, std::max<int64_t>(1, g / 2)), kNearSlices);
+        partials(whole, mixed ? kNearSlices : 0);
+    if (max_bytes > 0 && p.total > max_bytes) partials(std::min(whole, std::max<int64_t>(1, g / 2)), mixed ? kNearSlices : 0);
     return p;
 }
 
@@ -777,10 +764,9 @@ size_t direct_scratch_measure(int kernel, int mixed, int64_t n_src, int64_t n_tr
     return align_up(off + (size_t)p.blocks_x * 4 * (size_t)chunks, 256);
 }
 
-template <int KT, int MIXED>
+template <int KT, int MIXED, int T = MIXED ? kT32 : kT64>
 static hipError_t launch_typed(const SumInputs& in, const DirectPlan& p, double* out, int accumulate,
                                void* ws, hipStream_t stream, const KernelTimer& timer) {
-    constexpr int T = MIXED ? kT32 : kT64;
     char* base = static_cast<char*>(ws);
     void* rec = base + p.off_src;
     void* aux = base + p.off_grp;
@@ -799,7 +785,6 @@ static hipError_t launch_typed(const SumInputs& in, const DirectPlan& p, double*
     a.cut = p.cut;
     a.part = reinterpret_cast<double*>(base + p.off_part);
     a.near_part = reinterpret_cast<double*>(base + p.off_near);
-    const dim3 near_grid((unsigned)p.blocks_x, (unsigned)p.near_slices);
     if (timer.on()) (void)hipEventRecord(timer.start, stream);
     if constexpr (MIXED != 0) {
         if (in.pair_class)
@@ -812,14 +797,14 @@ static hipError_t launch_typed(const SumInputs& in, const DirectPlan& p, double*
     if (timer.on()) (void)hipEventRecord(timer.stop, stream);
     if (e != hipSuccess) return e;
     if constexpr (MIXED != 0) {
+        const dim3 near_grid((unsigned)p.blocks_x, (unsigned)p.near_slices);
         if (in.pair_class)
             direct_near_mixed<KT, T, true><<<near_grid, dim3(kBlock), 0, stream>>>(a);
         else
             direct_near_mixed<KT, T><<<near_grid, dim3(kBlock), 0, stream>>>(a);
-    } else
-        direct_near_f64<KT, T><<<near_grid, dim3(kBlock), 0, stream>>>(a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     // FP64 pair sums are 4x (single layer) or 8x (double layer) the bare sums
     const double pref = MIXED ? in.pref : (KT == 0 ? 0.25 : 0.125) * in.pref;
     reduce_segments<T><<<dim3((unsigned)ceil_div(in.n_trg, kBlock / kRedParts)), dim3(kBlock), 0, stream>>>(
@@ -837,7 +822,9 @@ hipError_t launch_direct(const SumInputs& in, const DirectPlan& p, double* out, 
                         : launch_typed<0, 0>(in, p, out, accumulate, ws, stream, timer);
     }
     return in.mixed ? launch_typed<1, 1>(in, p, out, accumulate, ws, stream, timer)
-                    : launch_typed<1, 0>(in, p, out, accumulate, ws, stream, timer);
+           : p.T == kT64Long
+               ? launch_typed<1, 0, kT64Long>(in, p, out, accumulate, ws, stream, timer)
+               : launch_typed<1, 0>(in, p, out, accumulate, ws, stream, timer);
 }
 
 }  // namespace stokes

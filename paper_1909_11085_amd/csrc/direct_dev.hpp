@@ -251,14 +251,18 @@ __device__ __forceinline__ void for_each_near(const Box& w, const Targets<T>& t,
     }
 }
 
-// Grid rows (slices) of the near pass over blocks_x target blocks: enough
+// Grid rows (slices) of the mixed near pass over blocks_x target blocks: enough
 // workgroups for the whole chip where the blocks are few.  A wave's near
 // sub-tiles run one after another, and scattered targets (tracer points between
-// the cells) have many: with 4 rows, 8,001 tracers at 34,816 sources took
-// 0.92 ms of which 0.7 ms were the near pass on 32 workgroups.
-constexpr int kNearSlices = 4, kNearSlicesMax = 64, kNearBlocks = 1024;
-inline int near_slices(int64_t blocks_x) {
-    return (int)std::min<int64_t>(kNearSlicesMax, std::max<int64_t>(kNearSlices, ceil_div(kNearBlocks, blocks_x)));
+// the cells) have many: 8,001 tracers at 34,816 sources 0.64 ms with 4 rows, 0.23
+// with up to 64.  A row repeats the box tests, so past two workgroups per CU it
+// has four sub-tiles at least (19,602 targets at 3,267 sources: 135 us with 27
+// rows, 126 with 14; 4,096 points 62 us with 16, 55 with 64).
+constexpr int kNearSlices = 4, kNearSlicesMax = 64, kNearBlocks = 1024, kNearSubs = 4;
+inline int near_slices(int64_t blocks_x, int64_t n_sub) {
+    const int64_t most = std::max(n_sub / kNearSubs, ceil_div(kNearBlocks / 2, blocks_x));
+    const int64_t rows = std::min<int64_t>(std::min<int64_t>(kNearSlicesMax, most), ceil_div(kNearBlocks, blocks_x));
+    return (int)std::max<int64_t>(kNearSlices, rows);
 }
 
 // ---------------------------------------------------------------------------

@@ -45,3 +45,23 @@ def test_scattered_targets(kernel, precision, ns, nt, grid):
         S.set_grid_override(0)
     ref = O.sl(y, f, w, x, **okw) if kernel == "sl" else O.dl(y, f, w, nv, x, **okw)
     assert_close(host(got), ref, FP64_TOL if precision == "fp64" else MIXED_TOL, f"{kernel} {precision} {grid}")
+
+
+@pytest.mark.parametrize("ns,nt", [(450_001, 2047), (32_768, 32_700), (450_001, 2049)])
+def test_long_double_layer(ns, nt):
+    """Eight targets per lane (and four, where the last target block would be
+    mostly padding): sampled targets, the block's edges among them."""
+    rng = np.random.default_rng(ns + nt)
+    sg = (np.arange(ns) // 1000).astype(np.int32)
+    y, x = rng.uniform(-4, 4, (3, ns)), rng.uniform(-4, 4, (3, nt))
+    y[0] += 0.1 * (sg % 7)
+    tg = rng.integers(-1, sg[-1] + 1, nt).astype(np.int32)
+    x[:, 5] = y[:, -1]
+    x[:, nt - 1] = y[:, 0]
+    f, w = rng.standard_normal((3, ns)), rng.uniform(0.1, 1.0, ns)
+    nv = rng.standard_normal((3, ns))
+    nv /= np.linalg.norm(nv, axis=0)
+    got = S.dl(dev(y), dev(f), dev(w), dev(nv), dev(x), src_group=dev(sg), trg_group=dev(tg))
+    i = np.unique(np.concatenate([[0, 5, 63, 64, 511, 512, 2046, nt - 1], rng.integers(0, nt, 56)]))
+    ref = O.dl(y, f, w, nv, x[:, i], src_group=sg, trg_group=tg[i], exclude_same_group=True)
+    assert_close(host(got)[:, i], ref, FP64_TOL, f"dl {ns} {nt}")

@@ -139,9 +139,9 @@ struct SymPlan {
     int64_t NW;                  // row blocks (4 T tiles each)
     int64_t units;               // (row block, column tile) units of the triangle
     int64_t grid;                // workgroups
+    int64_t extra;               // weight of a row block's first 4 T units beyond one each
     size_t off_rec, off_aux, off_meta, off_row, off_col, total;
 };
-int sym_blocks_per_cu(int adjoint);
 SymPlan plan_sym(int adjoint, int64_t n, int resident_blocks, int forced_grid);
 hipError_t launch_sym(const SumInputs& in, const SymPlan& p, double* out, int accumulate, void* workspace,
                       hipStream_t stream, const KernelTimer& timer);

@@ -40,22 +40,9 @@
 // Positions are stored doubled (exact) as in the one-sided kernels; the
 // factors this leaves are taken out in the reduction.
 #include <algorithm>
+#include <type_traits>
 
 #include "direct_dev.hpp"
-
-// rows per lane (T) and minimum waves per SIMD (W): forward and adjoint
-#ifndef STOKES_SYM_T64
-#define STOKES_SYM_T64 6
-#endif
-#ifndef STOKES_SYM_W64
-#define STOKES_SYM_W64 2
-#endif
-#ifndef STOKES_SYM_TV
-#define STOKES_SYM_TV 4
-#endif
-#ifndef STOKES_SYM_WV
-#define STOKES_SYM_WV 2
-#endif
 
 namespace stokes {
 
@@ -72,6 +59,7 @@ struct SymArgs {
     const int32_t* grp;       // n_pad group ids
     const SubMeta* meta;      // per 64-point tile
     int64_t n_pad, NT, NW, units;
+    int64_t extra;            // weight of a row block's first 4 T units beyond one each
     double* row_part;         // (grid + NW) segments of NA x (kBlock T) doubles
     double* col_part;         // (units, NA, 64)
     double* out0;             // forward: velocity; adjoint: dL/df (either may be null in the adjoint)
@@ -84,15 +72,31 @@ __host__ __device__ __forceinline__ int64_t sym_off(int64_t W, int64_t NT, int64
     return W * NT - tpb * (W * (W - 1) / 2);
 }
 
-// the row block holding unit u: largest W with sym_off(W) <= u
-__device__ __forceinline__ int64_t sym_block_of(int64_t u, int64_t NT, int64_t tpb, int64_t NW) {
-    int64_t lo = 0, hi = NW - 1;
+// Work is cut by weight: the first tpb units of a row block (its own tiles, and
+// with them most units that need the masked loop) weigh 1 + extra/tpb each, the
+// others 1.  Weight position v, 0 <= v < V = units + extra NW, lies in row block W
+// with sym_woff(W) <= v; workgroup g takes the units from that at g V / G on.
+__host__ __device__ __forceinline__ int64_t sym_woff(int64_t W, int64_t NT, int64_t tpb, int64_t extra) {
+    return sym_off(W, NT, tpb) + extra * W;
+}
+struct SymPos { int64_t W, r; };               // row block and unit in it
+__device__ __forceinline__ SymPos sym_begin(int64_t g, int64_t G, const SymArgs& a, int64_t tpb) {
+    const int64_t V = a.units + a.extra * a.NW, v = g * V / G;
+    int64_t lo = 0, hi = a.NW;                 // the largest W with sym_woff(W) <= v
     while (lo < hi) {
         const int64_t mid = (lo + hi + 1) / 2;
-        if (sym_off(mid, NT, tpb) <= u) lo = mid;
+        if (sym_woff(mid, a.NT, tpb, a.extra) <= v) lo = mid;
         else hi = mid - 1;
     }
-    return lo;
+    const int64_t x = v - sym_woff(lo, a.NT, tpb, a.extra);
+    return {lo, x < tpb + a.extra ? x * tpb / (tpb + a.extra) : x - a.extra};
+}
+// the workgroup that takes unit r of row block W: the last whose begin is not
+// beyond it, that is with g V / G < v, v the first position past the unit
+__device__ __forceinline__ int64_t sym_owner(int64_t W, int64_t r, int64_t G, const SymArgs& a, int64_t tpb) {
+    const int64_t V = a.units + a.extra * a.NW;
+    const int64_t x = r < tpb ? ((r + 1) * (tpb + a.extra) + tpb - 1) / tpb : r + 1 + a.extra;
+    return ((sym_woff(W, a.NT, tpb, a.extra) + x) * G - 1) / V;
 }
 
 // The column points move through the wave in 4 phases: within each row of 16
@@ -227,8 +231,9 @@ __global__ __launch_bounds__(kBlock, W_SIMD) void sym_main(SymArgs a) {
     constexpr int NA = P::NA;
     constexpr int TPB = 4 * T;
     __shared__ double s_col[4][NA][kWave];
-    const int64_t U = a.units, G = gridDim.x, NT = a.NT;
-    const int64_t u0 = unit_begin(blockIdx.x, U, G), u1 = unit_begin(blockIdx.x + 1, U, G);
+    const int64_t NT = a.NT;
+    const SymPos p0 = sym_begin(blockIdx.x, gridDim.x, a, TPB), p1 = sym_begin(blockIdx.x + 1, gridDim.x, a, TPB);
+    const int64_t u0 = sym_off(p0.W, NT, TPB) + p0.r, u1 = sym_off(p1.W, NT, TPB) + p1.r;
     if (u0 >= u1) return;                      // whole workgroup idle (uniform)
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
@@ -243,20 +248,19 @@ __global__ __launch_bounds__(kBlock, W_SIMD) void sym_main(SymArgs a) {
 #pragma unroll
         for (int j = 0; j < NA; ++j) ra[k][j] = 0.0;
     bool wave_active = false;
-    int64_t W = sym_block_of(u0, NT, TPB, a.NW);
-    int64_t b = u0 - sym_off(W, NT, TPB) + TPB * W;
+    int64_t W = p0.W, b = p0.r + TPB * W;
     int64_t Wcur = -1;
     for (int64_t u = u0; u < u1; ++u) {
         if (W != Wcur) {
             if (Wcur >= 0) flush_sym_segment<NA, T>(a, Wcur, wave, lane, ra);
             Wcur = W;
-            const int64_t p0 = (TPB * W + T * wave) * kWave;
-            wave_active = p0 < a.in.n_trg;
-            wbox = load_targets<T>(a.in, wave_active ? p0 : 0, lane, t);
+            const int64_t first = (TPB * W + T * wave) * kWave;
+            wave_active = first < a.in.n_trg;
+            wbox = load_targets<T>(a.in, wave_active ? first : 0, lane, t);
             double_targets<T>(t, &wbox);
 #pragma unroll
             for (int k = 0; k < T; ++k) {
-                const SymRec r = rec[p0 + k * kWave + lane];   // p0 + T*64 <= n_pad
+                const SymRec r = rec[first + k * kWave + lane];   // first + T*64 <= n_pad
 #pragma unroll
                 for (int j = 0; j < 6; ++j) rd[k][j] = r.d[j];
 #pragma unroll
@@ -305,20 +309,18 @@ __global__ __launch_bounds__(kBlock, W_SIMD) void sym_main(SymArgs a) {
                 }
             } else {
                 int cg = a.grp[b * kWave + lane];
-                const uint32_t any = full | diag;
                 for (int R = 0; R < 4; ++R) {
 #pragma unroll 1
                     for (int sp = 0; sp < 16; ++sp) {
                         // the diagonal slot takes each unordered pair of its tile
-                        // once: when this lane's point precedes the column point
-                        const bool dpair = lane < held_col(lane, R, sp);
+                        // once: when this lane's point precedes the column point.
+                        // Slots before it are masked, not branched over: a branch
+                        // per slot keeps their pairs from overlapping
+                        const uint32_t on = lane < held_col(lane, R, sp) ? full | diag : full;
 #pragma unroll
-                        for (int k = 0; k < T; ++k) {
-                            if (!((any >> k) & 1u)) continue;
-                            const bool on = ((full >> k) & 1u) || dpair;
+                        for (int k = 0; k < T; ++k)
                             P::template pair<true>(t.x[k], t.y[k], t.z[k], rd[k], ra[k], cx, cy, cz, cd, ca,
-                                                   !on || (excl && t.g[k] == cg));
-                        }
+                                                   !((on >> k) & 1u) || (excl && t.g[k] == cg));
                         rotate_col_row<NA>(cx, cy, cz, cd, ca);
                         cg = row_rot(cg);
                     }
@@ -348,42 +350,56 @@ __device__ __forceinline__ void put(double* out, int64_t o, double v, int accumu
 }
 
 // out (=|+=) the prefactored sums of each point: its row segments and the
-// column partials of its tile from every row block, in a fixed order.
+// column partials of its tile from every row block.  kSymParts threads share a
+// point, each taking a contiguous share of both, and the shares are added in
+// order (8,704 points: adjoint and forward 69 and 49 us with one thread per
+// point, which adds some 200 segments one after another, 8 and 7 so).
+constexpr int kSymParts = 8;
 template <class P, int T>
 __global__ __launch_bounds__(kBlock) void sym_reduce(SymArgs a, int64_t grid) {
     constexpr int NA = P::NA;
-    constexpr int TPB = 4 * T, RB = kBlock * T;
-    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const int64_t n = a.in.n_trg;
-    if (p >= n) return;
-    const int64_t NT = a.NT, U = a.units;
-    const int64_t W = p / RB, li = p % RB, b = p / kWave, l = p % kWave;
-    const int64_t g0 = unit_owner(sym_off(W, NT, TPB), U, grid);
-    const int64_t g1 = unit_owner(sym_off(W + 1, NT, TPB) - 1, U, grid);
+    constexpr int TPB = 4 * T, RB = kBlock * T, kPts = kBlock / kSymParts;
+    static_assert(NA <= kSymParts && kWave % kPts == 0, "a thread per component; one tile per workgroup");
+    __shared__ double s_sum[kSymParts][NA][kPts];
+    const int pt = threadIdx.x % kPts, q = threadIdx.x / kPts;
+    const int64_t p = (int64_t)blockIdx.x * kPts + pt;
+    const int64_t n = a.in.n_trg, NT = a.NT;
+    const int64_t b = (int64_t)blockIdx.x * kPts / kWave, W = b / TPB;   // of the whole workgroup
+    const int64_t li = p % RB, l = p % kWave;
+    const int64_t g0 = sym_owner(W, 0, grid, a, TPB), ng = sym_owner(W, NT - TPB * W - 1, grid, a, TPB) + 1 - g0;
     double s[NA];
 #pragma unroll
     for (int j = 0; j < NA; ++j) s[j] = 0.0;
-    for (int64_t g = g0; g <= g1; ++g) {
-        const double* seg = a.row_part + (g + W) * NA * RB;
+    if (p < n) {
+#pragma unroll 2
+        for (int64_t g = g0 + ng * q / kSymParts; g < g0 + ng * (q + 1) / kSymParts; ++g) {
+            const double* seg = a.row_part + (g + W) * NA * RB;
 #pragma unroll
-        for (int j = 0; j < NA; ++j) s[j] += seg[j * RB + li];
-    }
-    for (int64_t Wp = 0; Wp * TPB <= b; ++Wp) {
-        const double* cp = a.col_part + (sym_off(Wp, NT, TPB) + b - TPB * Wp) * NA * kWave;
+            for (int j = 0; j < NA; ++j) s[j] += seg[j * RB + li];
+        }
+#pragma unroll 2
+        for (int64_t Wp = (W + 1) * q / kSymParts; Wp < (W + 1) * (q + 1) / kSymParts; ++Wp) {
+            const double* cp = a.col_part + (sym_off(Wp, NT, TPB) + b - TPB * Wp) * NA * kWave;
 #pragma unroll
-        for (int j = 0; j < NA; ++j) s[j] += cp[j * kWave + l];
+            for (int j = 0; j < NA; ++j) s[j] += cp[j * kWave + l];
+        }
     }
+#pragma unroll
+    for (int j = 0; j < NA; ++j) s_sum[q][j][pt] = s[j];
+    __syncthreads();
+    if (q >= NA || p >= n) return;
+    double v = s_sum[0][q][pt];
+#pragma unroll
+    for (int k = 1; k < kSymParts; ++k) v += s_sum[k][q][pt];
     if constexpr (NA == 3) {
         // forward: 4 times the bare sums (doubled positions)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) put(a.out0, c * n + p, 0.25 * a.in.pref * s[c], a.accumulate);
+        put(a.out0, q * n + p, 0.25 * a.in.pref * v, a.accumulate);
     } else {
         // adjoint: dL/df = c w sum S(r) g; dL/dx = c sum (+-V), accumulated as 2 V
-        const double cw = a.in.pref * a.in.weight[p];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            if (a.out0) put(a.out0, c * n + p, cw * s[c], a.accumulate);
-            if (a.out1) put(a.out1, c * n + p, 0.5 * a.in.pref * s[3 + c], a.accumulate);
+        if (q < 3) {
+            if (a.out0) put(a.out0, q * n + p, a.in.pref * a.in.weight[p] * v, a.accumulate);
+        } else if (a.out1) {
+            put(a.out1, (q - 3) * n + p, 0.5 * a.in.pref * v, a.accumulate);
         }
     }
 }
@@ -398,32 +414,74 @@ __global__ __launch_bounds__(kBlock) void sym_vjp_set_g(SymRec* rec, const doubl
     rec[i].d[5] = v ? g[2 * n + i] : 0.0;
 }
 
-constexpr int kSymT64 = STOKES_SYM_T64;
-constexpr int kSymTV = STOKES_SYM_TV;
+// Launch shapes: T rows per lane at W waves per SIMD.  More rows share a column
+// point's loads, moves and sums (0.4 of a row's pairs forward, 0.3 in the
+// adjoint); fewer make finer units, which divide more evenly among the
+// workgroups.  See sym_rows.
+template <class P, int T> constexpr int kSymWaves = T == 2 ? (P::NA == 3 ? 4 : 3) : 2;
+constexpr int kSymLong = 6;                    // forward, from kSymLongUnits units per workgroup on
+constexpr int64_t kSymLongUnits = 64;
 
-}  // namespace
-
-int sym_blocks_per_cu(int adjoint) {
-    int nb = 0;
-    const hipError_t e =
-        adjoint ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, sym_main<VjpSL, kSymTV, STOKES_SYM_WV>, kBlock, 0)
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, sym_main<FwdSL, kSymT64, STOKES_SYM_W64>,
-                                                               kBlock, 0);
-    return (e == hipSuccess && nb > 0) ? nb : 1;
+template <class P, typename F>
+auto with_sym(int T, F&& f) {
+    if constexpr (P::NA == 3)
+        if (T == kSymLong) return f(std::integral_constant<int, kSymLong>{});
+    return T == 4 ? f(std::integral_constant<int, 4>{}) : f(std::integral_constant<int, 2>{});
 }
 
-SymPlan plan_sym(int adjoint, int64_t n, int resident_blocks, int forced_grid) {
-    SymPlan p{};
-    p.T = adjoint ? kSymTV : kSymT64;
-    const int na = adjoint ? VjpSL::NA : FwdSL::NA;
-    const int64_t rb = (int64_t)kBlock * p.T;
-    const int64_t tpb = 4 * (int64_t)p.T;
+struct SymShape { int64_t n_pad, NT, NW, units, grid, extra; };
+SymShape sym_shape(int adjoint, int T, int64_t n, int64_t resident_blocks, int forced_grid) {
+    SymShape p{};
+    const int64_t rb = (int64_t)kBlock * T, tpb = 4 * (int64_t)T;
     p.n_pad = ceil_div(n, rb) * rb;
     p.NT = p.n_pad / kWave;
     p.NW = p.n_pad / rb;
     p.units = sym_off(p.NW, p.NT, tpb);
-    const int64_t g = forced_grid > 0 ? forced_grid : std::max(1, resident_blocks);
+    const int64_t waves = T == 2 ? (adjoint ? kSymWaves<VjpSL, 2> : kSymWaves<FwdSL, 2>) : 2;
+    const int64_t g = forced_grid > 0 ? forced_grid : std::max<int64_t>(1, resident_blocks) * waves / 2;
     p.grid = std::max<int64_t>(1, std::min<int64_t>(g, p.units));
+    // 3/8 of a unit more for each of the first 4 T: the masked loop has 1.3 times
+    // the instructions.  Where every workgroup still gets a unit.  69,632 points:
+    // 3.36 and 6.54 ms with equal weights (the ranges of masked units alone end
+    // last), 3.01 and 5.93 with these
+    p.extra = p.units >= 2 * p.grid ? 3 * tpb / 8 : 0;
+    return p;
+}
+
+// Rows per lane: the least of (units of the longest range) x (rows + the column
+// point's share) x (waves that share a SIMD).  T = 2 / 4 / 6 forward: 13,056
+// points 161 / 165 / 201 us, 21,760 367 / 412 / 421, 34,816 861 / 813 / 873, 69,632
+// 3.35 / 2.98 / 3.01 ms, 278,528 52.6 / 46.6 / 45.1; adjoint, T = 2 / 4: 4,352 66 / 70
+// us, 8,160 140 / 195, 34,816 1.64 / 1.58 ms.
+int sym_rows(int adjoint, int64_t n, int64_t resident_blocks, int forced_grid) {
+    if (!adjoint) {
+        const SymShape p = sym_shape(0, kSymLong, n, resident_blocks, forced_grid);
+        if (p.units >= kSymLongUnits * p.grid) return kSymLong;
+    }
+    double cost[2];
+    for (int i = 0; i < 2; ++i) {
+        const int T = 2 + 2 * i;
+        const SymShape p = sym_shape(adjoint, T, n, resident_blocks, forced_grid);
+        cost[i] = (double)ceil_div(p.units + p.extra * p.NW, p.grid) * (T + (adjoint ? 0.3 : 0.4)) *
+                  std::max(1.0, (double)p.grid / (double)std::max<int64_t>(1, resident_blocks));
+    }
+    return cost[0] < cost[1] ? 2 : 4;
+}
+
+}  // namespace
+
+SymPlan plan_sym(int adjoint, int64_t n, int resident_blocks, int forced_grid) {
+    SymPlan p{};
+    p.T = sym_rows(adjoint, n, resident_blocks, forced_grid);
+    const SymShape sh = sym_shape(adjoint, p.T, n, resident_blocks, forced_grid);
+    p.n_pad = sh.n_pad;
+    p.NT = sh.NT;
+    p.NW = sh.NW;
+    p.units = sh.units;
+    p.grid = sh.grid;
+    p.extra = sh.extra;
+    const int na = adjoint ? VjpSL::NA : FwdSL::NA;
+    const int64_t rb = (int64_t)kBlock * p.T;
     size_t off = 0;
     p.off_rec = off;
     off = align_up(off + (size_t)p.n_pad * sizeof(SymRec), 256);
@@ -439,6 +497,22 @@ SymPlan plan_sym(int adjoint, int64_t n, int resident_blocks, int forced_grid) {
     return p;
 }
 
+// The sums and their reduction, after the records are in place.
+template <class P>
+static hipError_t launch_sums(const SymArgs& a, const SymPlan& p, hipStream_t stream, const KernelTimer& timer) {
+    return with_sym<P>(p.T, [&](auto tc) {
+        constexpr int T = decltype(tc)::value;
+        if (timer.on()) (void)hipEventRecord(timer.start, stream);
+        sym_main<P, T, kSymWaves<P, T>><<<dim3((unsigned)p.grid), dim3(kBlock), 0, stream>>>(a);
+        const hipError_t e = hipGetLastError();
+        if (timer.on()) (void)hipEventRecord(timer.stop, stream);
+        if (e != hipSuccess) return e;
+        sym_reduce<P, T><<<dim3((unsigned)ceil_div(a.in.n_trg, kBlock / kSymParts)), dim3(kBlock), 0, stream>>>(
+            a, p.grid);
+        return hipGetLastError();
+    });
+}
+
 static SymArgs sym_args(const SumInputs& in, const SymPlan& p, void* ws) {
     char* base = static_cast<char*>(ws);
     SymArgs a{};
@@ -450,6 +524,7 @@ static SymArgs sym_args(const SumInputs& in, const SymPlan& p, void* ws) {
     a.NT = p.NT;
     a.NW = p.NW;
     a.units = p.units;
+    a.extra = p.extra;
     a.row_part = reinterpret_cast<double*>(base + p.off_row);
     a.col_part = reinterpret_cast<double*>(base + p.off_col);
     return a;
@@ -466,13 +541,7 @@ hipError_t launch_sym(const SumInputs& in, const SymPlan& p, double* out, int ac
     hipError_t e = launch_prep(in, p.n_pad, base + p.off_rec, base + p.off_aux,
                                reinterpret_cast<SubMeta*>(base + p.off_meta), stream);
     if (e != hipSuccess) return e;
-    if (timer.on()) (void)hipEventRecord(timer.start, stream);
-    sym_main<FwdSL, kSymT64, STOKES_SYM_W64><<<dim3((unsigned)p.grid), dim3(kBlock), 0, stream>>>(a);
-    e = hipGetLastError();
-    if (timer.on()) (void)hipEventRecord(timer.stop, stream);
-    if (e != hipSuccess) return e;
-    sym_reduce<FwdSL, kSymT64><<<dim3((unsigned)ceil_div(in.n_trg, kBlock)), dim3(kBlock), 0, stream>>>(a, p.grid);
-    return hipGetLastError();
+    return launch_sums<FwdSL>(a, p, stream, timer);
 }
 
 hipError_t launch_sym_vjp(const SumInputs& in, const SymPlan& p, const double* grad_vel, double* grad_density,
@@ -494,13 +563,7 @@ hipError_t launch_sym_vjp(const SumInputs& in, const SymPlan& p, const double* g
         reinterpret_cast<SymRec*>(base + p.off_rec), grad_vel, in.n_trg, p.n_pad);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (timer.on()) (void)hipEventRecord(timer.start, stream);
-    sym_main<VjpSL, kSymTV, STOKES_SYM_WV><<<dim3((unsigned)p.grid), dim3(kBlock), 0, stream>>>(a);
-    e = hipGetLastError();
-    if (timer.on()) (void)hipEventRecord(timer.stop, stream);
-    if (e != hipSuccess) return e;
-    sym_reduce<VjpSL, kSymTV><<<dim3((unsigned)ceil_div(in.n_trg, kBlock)), dim3(kBlock), 0, stream>>>(a, p.grid);
-    return hipGetLastError();
+    return launch_sums<VjpSL>(a, p, stream, timer);
 }
 
 }  // namespace stokes

@@ -844,7 +844,8 @@ int stokes_p2p_leaf_eval(stokes_ctx* ctx, int32_t kernel, int64_t n_src, const d
     stokes::SumInputs in = make_inputs(kernel, p, n_src, src_xyz, density, weight, normal, n_trg, trg_xyz, pref);
     in.pair_class = pair_class;
     return launch_status(stokes::launch_p2p_csr(in, n_leaves, src_leaf_ofs, trg_leaf_ofs, ulist_ofs, ulist, n_ulist,
-                                                vel_out, p.accumulate, workspace, st, stokes::next_timer(ctx)),
+                                                stokes::P2POut{vel_out, p.accumulate, nullptr, 0}, workspace, st,
+                                                stokes::next_timer(ctx)),
                          "stokes_p2p_leaf_eval");
 }
 

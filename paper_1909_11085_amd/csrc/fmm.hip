@@ -1980,8 +1980,8 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
                 p.pref = dl ? 6.0 * in.pref : in.pref;
                 p.trg_perm = a.tperm;
                 const KernelTimer none{};
-                e = launch_p2p_csr(p, (int32_t)L.n_leaves, a.sofs, a.tofs, uofs, ul, -1, out, 1, ws + L.off_p2p, st,
-                                   none, false);
+                e = launch_p2p_csr(p, (int32_t)L.n_leaves, a.sofs, a.tofs, uofs, ul, -1, P2POut{out, 1, nullptr, 0},
+                                   ws + L.off_p2p, st, none, false);
             }
         }
     }

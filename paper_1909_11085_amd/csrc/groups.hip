@@ -200,7 +200,7 @@ hipError_t launch_same_group_subtract(const SumInputs& in, double* out, void* ws
     p.excl = 0;
     p.pref = in.pref;
     const KernelTimer none{};
-    if ((e = launch_p2p_csr(p, ng, sofs, tofs, uofs, ul, ng, u, 0, base + l.off_p2p, st, none)) != hipSuccess)
+    if ((e = launch_p2p_csr(p, ng, sofs, tofs, uofs, ul, ng, P2POut{u, 0, nullptr, 0}, base + l.off_p2p, st, none)) != hipSuccess)
         return e;
     g_subtract<<<grid_for(nt), kGThreads, 0, st>>>(u, tvals, nt, status, out);
     chk();

@@ -16,17 +16,18 @@
 //   * sum: one wave per work item.  An item of n <= 64 targets gives each
 //     target R = min(16, 64/n) lanes, and lane phase h takes every R-th source
 //     (so small leaves still fill the wave); the R partial sums are added in a
-//     fixed order at the end.  The sources of each listed leaf are staged
-//     through LDS, up to 128 at a time, and sorted on the way in by what
-//     each needs: sources of a group that every target of the item shares
-//     are dropped (the same-group rule excludes them all); sources within
-//     the near limit of the targets' box are "careful"; sources of a group
-//     that some targets share are "masked"; the rest are "clean".  Clean
-//     sources run an unmasked loop (float32 offsets in mixed precision,
-//     exactly as the direct sums' fast path), masked ones the same loop with
-//     the same-group mask (and, in FP64, the zero-distance mask), careful
-//     ones (mixed) r = (x_hi - y_hi) + (x_lo - y_lo) with the same-group
-//     mask and the pairs inside the near radius evaluated in float64.
+//     fixed order at the end.  In float64 a lane holds several targets where
+//     that leaves no lane idle (see p2p_sum64), so a record read serves them
+//     all.  Sources are staged through LDS, up to 128 at a time, and sorted on
+//     the way in by what each needs: sources of a group that every target of
+//     the item shares are dropped (the same-group rule excludes them all);
+//     "clean" ones (no group shared, none that could coincide with a target or,
+//     in mixed precision, lie within the near limit of the targets' box) run an
+//     unmasked loop (float32 offsets in mixed precision, exactly as the direct
+//     sums' fast path); the others the same loop with the same-group mask (and,
+//     in float64, the zero-distance mask), or, "careful" ones in mixed
+//     precision, r = (x_hi - y_hi) + (x_lo - y_lo) with the same-group mask and
+//     the pairs inside the near radius evaluated in float64.
 #include <float.h>
 #include <limits.h>
 
@@ -37,6 +38,7 @@
 #include <vector>
 
 #include "../../include/stokes_mi355x.h"
+#include "direct_dev.hpp"
 #include "p2p.hpp"
 #include "spatial.hpp"
 
@@ -72,11 +74,13 @@ template <> struct P2PRec<0, 0> { using type = SrcSL64; };
 template <> struct P2PRec<1, 0> { using type = SrcDL64; };
 template <> struct P2PRec<0, 1> { using type = P2PSL32; };
 template <> struct P2PRec<1, 1> { using type = P2PDL32; };
-// kernels 2 .. 5: the adjoint sums, float64 only (the pair forms at pair64)
+// kernels 2 .. 7: the adjoint sums, float64 only (the pair forms at pair64)
 template <> struct P2PRec<2, 0> { using type = SrcSL64; };
 template <> struct P2PRec<3, 0> { using type = SrcDL64; };
 template <> struct P2PRec<4, 0> { using type = SrcSL64; };
 template <> struct P2PRec<5, 0> { using type = SrcSL64; };
+template <> struct P2PRec<6, 0> { using type = SrcSL64; };
+template <> struct P2PRec<7, 0> { using type = SrcSL64; };
 // kernels whose source records carry a normal
 template <int KT> constexpr bool kSrcNormal = KT == 1 || KT == 3;
 
@@ -94,7 +98,8 @@ struct P2PArgs {
     double* leaf_ctr;        // (n_leaves, 4): box centre and half-diagonal
     int32_t n_leaves;
     double* out;
-    int accumulate;
+    double* out2;            // kernels 6 and 7: the second sum, added into with accumulate2
+    int accumulate, accumulate2;
 };
 
 __device__ __forceinline__ double wmin(double v) {
@@ -174,76 +179,92 @@ __global__ __launch_bounds__(kWave) void p2p_prep(P2PArgs a) {
     }
 }
 
-__device__ __forceinline__ double rinv(double r2, bool skip) {
-    const double y0 = skip ? 0.0 : __builtin_amdgcn_rsq(r2);
-    const double e = __builtin_fma(-r2, y0 * y0, 1.0);
-    return __builtin_fma(0.5 * y0, e, y0);
-}
-
 // G(r; a, b, c) = [(r.b)(r.c) a + (r.a)(r.c) b + (r.a)(r.b) c]/rho^5
 //                 - 5 (r.a)(r.b)(r.c) r/rho^7,
 // the gradient in r of (r.a)(r.b)(r.c)/rho^5 (symmetric in a, b, c; even in r),
-// added to (ax, ay, az); ri2 = 1/rho^2, ri5 = 1/rho^5.
+// 4 times it, from r doubled, its dot products ra, rb and rc, ri = 1/rho; added
+// to the sums.
 __device__ __forceinline__ void grad3(double dx, double dy, double dz, double ri2, double ri5, const double (&va)[3],
-                                      const double (&vb)[3], const double (&vc)[3], double& ax, double& ay,
-                                      double& az) {
-    const double ra = __builtin_fma(dx, va[0], __builtin_fma(dy, va[1], dz * va[2]));
-    const double rb = __builtin_fma(dx, vb[0], __builtin_fma(dy, vb[1], dz * vb[2]));
-    const double rc = __builtin_fma(dx, vc[0], __builtin_fma(dy, vc[1], dz * vc[2]));
+                                      const double (&vb)[3], const double (&vc)[3], double ra, double rb, double rc,
+                                      double& ax, double& ay, double& az) {
     const double bc = rb * rc * ri5, ac = ra * rc * ri5, ab = ra * rb * ri5;
-    const double cr = -5.0 * ra * bc * ri2;
+    const double cr = -1.25 * ra * bc * ri2;
     ax = __builtin_fma(bc, va[0], __builtin_fma(ac, vb[0], __builtin_fma(ab, vc[0], __builtin_fma(cr, dx, ax))));
     ay = __builtin_fma(bc, va[1], __builtin_fma(ac, vb[1], __builtin_fma(ab, vc[1], __builtin_fma(cr, dy, ay))));
     az = __builtin_fma(bc, va[2], __builtin_fma(ac, vb[2], __builtin_fma(ab, vc[2], __builtin_fma(cr, dz, az))));
 }
 
+__device__ __forceinline__ double dot3(double x, double y, double z, const double (&v)[3]) {
+    return __builtin_fma(x, v[0], __builtin_fma(y, v[1], z * v[2]));
+}
+
+// Scale of the kernels' sums that the doubled positions leave (first sum).
+template <int KT> constexpr double kPairScale = KT == 1 || KT == 4 || KT == 7 ? 0.125 : KT == 2 ? 0.5 : 0.25;
+// ... and of the second sum of kernels 6 and 7
+template <int KT> constexpr double kPairScale2 = KT == 6 ? 0.5 : 0.25;
+template <int KT> constexpr int kSums = KT >= 6 ? 6 : 3;
+
+// One float64 pair, from positions doubled (so that 1/rho takes three
+// operations); the sums are 1/kPairScale times
 // KT 0: q/rho + r (r.q)/rho^3; KT 1: r (r.n)(r.q)/rho^5; KT 2: the gradient in
 // r of a.S(r)b times 8 pi mu, with a = tv (the target's vector) and b = q:
 //   K(r; a, b) = [(r.b) a + (r.a) b - (a.b) r]/rho^3 - 3 (r.a)(r.b) r/rho^5;
 // KT 3: G(r; n, q, tv) (the double layer's gradient, source normal n);
 // KT 4: r (r.tv)(r.q)/rho^5 (the double-layer form with the normal at the
-// target); KT 5: G(r; tv, tv2, q).
+// target); KT 5: G(r; tv, tv2, q).  KT 6 gives kernels 0 and 2, KT 7 kernels 4
+// and 5 of one pair: the adjoint's two source-side sums, which share the offset,
+// 1/rho and the dot products.  q4 = 4 q (kernels 0 and 6).
 template <int KT, bool MASKED>
-__device__ __forceinline__ void pair64(const typename P2PRec<KT, 0>::type& s, double x, double y,
-                                       double z, const double (&tv)[3], const double (&tv2)[3], bool skip_group,
-                                       double& ax, double& ay, double& az) {
+__device__ __forceinline__ void pair64(const typename P2PRec<KT, 0>::type& s, const double (&q4)[3], double x,
+                                       double y, double z, const double (&tv)[3], const double (&tv2)[3],
+                                       bool skip_group, double (&acc)[kSums<KT>]) {
     const double dx = x - s.x, dy = y - s.y, dz = z - s.z;
     const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz));
-    const double ri = rinv(r2, MASKED && (skip_group || r2 == 0.0));
+    const double ri = rinv_doubled(r2, MASKED && (skip_group || r2 == 0.0));
     const double ri2 = ri * ri;
-    const double rq = __builtin_fma(dx, s.qx, __builtin_fma(dy, s.qy, dz * s.qz));
-    if constexpr (KT == 2) {
-        const double ri3 = ri2 * ri;
-        const double ra = __builtin_fma(dx, tv[0], __builtin_fma(dy, tv[1], dz * tv[2]));
-        const double ab = __builtin_fma(tv[0], s.qx, __builtin_fma(tv[1], s.qy, tv[2] * s.qz));
-        const double sa = rq * ri3, sb = ra * ri3;
-        const double cr = -ri3 * __builtin_fma(3.0 * ra * rq, ri2, ab);
-        ax = __builtin_fma(sa, tv[0], __builtin_fma(sb, s.qx, __builtin_fma(cr, dx, ax)));
-        ay = __builtin_fma(sa, tv[1], __builtin_fma(sb, s.qy, __builtin_fma(cr, dy, ay)));
-        az = __builtin_fma(sa, tv[2], __builtin_fma(sb, s.qz, __builtin_fma(cr, dz, az)));
-    } else if constexpr (KT == 0) {
+    const double sq[3] = {s.qx, s.qy, s.qz};
+    const double rq = dot3(dx, dy, dz, sq);
+    if constexpr (KT == 0 || KT == 6) {
         const double c = rq * ri2;
-        ax = __builtin_fma(__builtin_fma(c, dx, s.qx), ri, ax);
-        ay = __builtin_fma(__builtin_fma(c, dy, s.qy), ri, ay);
-        az = __builtin_fma(__builtin_fma(c, dz, s.qz), ri, az);
-    } else if constexpr (KT == 3) {
-        const double sn[3] = {s.nx, s.ny, s.nz}, sq[3] = {s.qx, s.qy, s.qz};
-        grad3(dx, dy, dz, ri2, ri2 * ri2 * ri, sn, sq, tv, ax, ay, az);
-    } else if constexpr (KT == 5) {
-        const double sq[3] = {s.qx, s.qy, s.qz};
-        grad3(dx, dy, dz, ri2, ri2 * ri2 * ri, tv, tv2, sq, ax, ay, az);
-    } else if constexpr (KT == 4) {
-        const double ra = __builtin_fma(dx, tv[0], __builtin_fma(dy, tv[1], dz * tv[2]));
-        const double c = ra * rq * (ri2 * ri2 * ri);
-        ax = __builtin_fma(c, dx, ax);
-        ay = __builtin_fma(c, dy, ay);
-        az = __builtin_fma(c, dz, az);
-    } else {
+        acc[0] = __builtin_fma(__builtin_fma(c, dx, q4[0]), ri, acc[0]);
+        acc[1] = __builtin_fma(__builtin_fma(c, dy, q4[1]), ri, acc[1]);
+        acc[2] = __builtin_fma(__builtin_fma(c, dz, q4[2]), ri, acc[2]);
+    }
+    if constexpr (KT == 2 || KT == 6) {
+        constexpr int o = KT == 6 ? 3 : 0;
+        const double ri3 = ri2 * ri;
+        const double ra = dot3(dx, dy, dz, tv);
+        const double ab = dot3(tv[0], tv[1], tv[2], sq);
+        const double sa = rq * ri3, sb = ra * ri3;
+        const double cr = -ri3 * __builtin_fma(0.75 * ra * rq, ri2, ab);
+        acc[o] = __builtin_fma(sa, tv[0], __builtin_fma(sb, s.qx, __builtin_fma(cr, dx, acc[o])));
+        acc[o + 1] = __builtin_fma(sa, tv[1], __builtin_fma(sb, s.qy, __builtin_fma(cr, dy, acc[o + 1])));
+        acc[o + 2] = __builtin_fma(sa, tv[2], __builtin_fma(sb, s.qz, __builtin_fma(cr, dz, acc[o + 2])));
+    }
+    if constexpr (KT == 3) {
+        const double sn[3] = {s.nx, s.ny, s.nz};
+        grad3(dx, dy, dz, ri2, ri2 * ri2 * ri, sn, sq, tv, dot3(dx, dy, dz, sn), rq, dot3(dx, dy, dz, tv), acc[0],
+              acc[1], acc[2]);
+    }
+    if constexpr (KT == 1) {
         const double rn = __builtin_fma(dx, s.nx, __builtin_fma(dy, s.ny, dz * s.nz));
         const double c = rn * rq * (ri2 * ri2 * ri);
-        ax = __builtin_fma(c, dx, ax);
-        ay = __builtin_fma(c, dy, ay);
-        az = __builtin_fma(c, dz, az);
+        acc[0] = __builtin_fma(c, dx, acc[0]);
+        acc[1] = __builtin_fma(c, dy, acc[1]);
+        acc[2] = __builtin_fma(c, dz, acc[2]);
+    }
+    if constexpr (KT == 4 || KT == 5 || KT == 7) {
+        const double ri5 = ri2 * ri2 * ri, ra = dot3(dx, dy, dz, tv);
+        if constexpr (KT != 5) {
+            const double c = ra * rq * ri5;
+            acc[0] = __builtin_fma(c, dx, acc[0]);
+            acc[1] = __builtin_fma(c, dy, acc[1]);
+            acc[2] = __builtin_fma(c, dz, acc[2]);
+        }
+        if constexpr (KT != 4) {
+            constexpr int o = KT == 7 ? 3 : 0;
+            grad3(dx, dy, dz, ri2, ri5, tv, tv2, sq, ra, dot3(dx, dy, dz, tv2), rq, acc[o], acc[o + 1], acc[o + 2]);
+        }
     }
 }
 
@@ -312,16 +333,15 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// CNT (mixed, test-only instantiation): also record each pair's class.
-template <int KT, int MIXED, bool CNT = false>
-__global__ __launch_bounds__(kWave) void p2p_sum(P2PArgs a) {
-    using Rec = typename P2PRec<KT, MIXED>::type;
+// Mixed precision.  CNT (test-only instantiation): also record each pair's class.
+template <int KT, bool CNT = false>
+__global__ __launch_bounds__(kWave) void p2p_sum_mixed(P2PArgs a) {
+    using Rec = typename P2PRec<KT, 1>::type;
     constexpr int kSlots = kP2PTile + 2 * kMaxRep;
     // staged sources: clean ones from the front, the others from the back;
     // each region is padded with zero-strength records to R runs of equal
     // length
     __shared__ Rec s_rec[kSlots];
-    __shared__ int32_t s_grp[MIXED ? 1 : kSlots];
     if (a.status && *a.status) return;
     if (a.n_items && (int64_t)blockIdx.x >= *a.n_items) return;   // the grid covers the upper bound
     const int lane = threadIdx.x;
@@ -334,17 +354,6 @@ __global__ __launch_bounds__(kWave) void p2p_sum(P2PArgs a) {
     const int64_t idx = t0 + (valid ? ti : 0);        // idle lanes mirror target t0
     const int64_t nt = a.in.n_trg;
     const double x = a.in.trg_xyz[idx], y = a.in.trg_xyz[nt + idx], z = a.in.trg_xyz[2 * nt + idx];
-    double tv[3] = {0.0, 0.0, 0.0}, tv2[3] = {0.0, 0.0, 0.0};   // kernels 2 .. 5: the target's vectors
-    if constexpr (KT >= 2) {
-        tv[0] = a.in.trg_vec[idx];
-        tv[1] = a.in.trg_vec[nt + idx];
-        tv[2] = a.in.trg_vec[2 * nt + idx];
-    }
-    if constexpr (KT == 5) {
-        tv2[0] = a.in.trg_vec2[idx];
-        tv2[1] = a.in.trg_vec2[nt + idx];
-        tv2[2] = a.in.trg_vec2[2 * nt + idx];
-    }
     const int32_t tg = a.in.trg_group ? a.in.trg_group[idx] : 0;
     const bool excl = a.in.excl != 0;
 
@@ -381,7 +390,7 @@ __global__ __launch_bounds__(kWave) void p2p_sum(P2PArgs a) {
         // mixed: the targets' box relative to this leaf's centre in float32,
         // and a slack above every rounding of the float32 gap test below
         float flo[3] = {0.f, 0.f, 0.f}, fhi[3] = {0.f, 0.f, 0.f}, fslack = 0.f, frad8 = 0.f;
-        if constexpr (MIXED != 0) {
+        {
             const double hx = x - cx, hy = y - cy, hz = z - cz;
             xs = (float)hx; ys = (float)hy; zs = (float)hz;
             xl = (float)(hx - (double)xs);
@@ -404,9 +413,9 @@ __global__ __launch_bounds__(kWave) void p2p_sum(P2PArgs a) {
             //   clean (front): no group shared with the item's targets, outside
             //     the near limit of their box: unmasked loop;
             //   back: a group shared with some targets (same loop plus the
-            //     same-group mask; FP64 also masks zero distance), or (mixed)
-            //     within the near limit: residues and near test.  The back
-            //     region takes the careful loop if it holds any of the latter;
+            //     same-group mask), or within the near limit: residues and near
+            //     test.  The back region takes the careful loop if it holds any
+            //     of the latter;
             //   dropped: a group that every target of the item shares.
             __syncthreads();                           // previous readers are done
             int n_clean = 0, n_back = 0;
@@ -416,29 +425,18 @@ __global__ __launch_bounds__(kWave) void p2p_sum(P2PArgs a) {
                 const bool in = i < nb;
                 const int64_t si = s0 + b + (in ? i : 0);     // nb >= 1: index 0 is a real source
                 const Rec r = rec[si];
-                int32_t g;
-                bool close;
-                if constexpr (MIXED == 0) {
-                    g = a.grp[si];
-                    // coincident points are possible only inside the targets' box
-                    const double gx = fmax(fmax(blo[0] - r.x, r.x - bhi[0]), 0.0);
-                    const double gy = fmax(fmax(blo[1] - r.y, r.y - bhi[1]), 0.0);
-                    const double gz = fmax(fmax(blo[2] - r.z, r.z - bhi[2]), 0.0);
-                    close = __builtin_fma(gx, gx, __builtin_fma(gy, gy, gz * gz)) <= 1e-200;
-                } else {
-                    g = r.g;
-                    // gap from the targets' box in float32 on leaf-centred
-                    // offsets; the limit is the near radius with margin, or an
-                    // eighth of the leaf radius (which bounds the float32 offset
-                    // error of the unmasked formula to about 20 ulp per pair),
-                    // plus the slack
-                    const float gx = fmaxf(fmaxf(flo[0] - r.hx, r.hx - fhi[0]), 0.f);
-                    const float gy = fmaxf(fmaxf(flo[1] - r.hy, r.hy - fhi[1]), 0.f);
-                    const float gz = fmaxf(fmaxf(flo[2] - r.hz, r.hz - fhi[2]), 0.f);
-                    const float gap2 = __builtin_fmaf(gx, gx, __builtin_fmaf(gy, gy, gz * gz));
-                    const float lim = fmaxf(1.001f * __builtin_amdgcn_sqrtf(r.t2), frad8) + fslack;
-                    close = !(gap2 > lim * lim);
-                }
+                const int32_t g = r.g;
+                // gap from the targets' box in float32 on leaf-centred
+                // offsets; the limit is the near radius with margin, or an
+                // eighth of the leaf radius (which bounds the float32 offset
+                // error of the unmasked formula to about 20 ulp per pair),
+                // plus the slack
+                const float gx = fmaxf(fmaxf(flo[0] - r.hx, r.hx - fhi[0]), 0.f);
+                const float gy = fmaxf(fmaxf(flo[1] - r.hy, r.hy - fhi[1]), 0.f);
+                const float gz = fmaxf(fmaxf(flo[2] - r.hz, r.hz - fhi[2]), 0.f);
+                const float gap2 = __builtin_fmaf(gx, gx, __builtin_fmaf(gy, gy, gz * gz));
+                const float lim = fmaxf(1.001f * __builtin_amdgcn_sqrtf(r.t2), frad8) + fslack;
+                const bool close = !(gap2 > lim * lim);
                 bool shared = false;
                 if (excl) {
                     shared = many_groups;
@@ -453,11 +451,10 @@ __global__ __launch_bounds__(kWave) void p2p_sum(P2PArgs a) {
                 }
                 const bool back = close || shared;
                 const uint64_t mf = __ballot(keep && !back), mk = __ballot(keep && back);
-                if (MIXED && __ballot(keep && close)) any_close = true;
+                if (__ballot(keep && close)) any_close = true;
                 if (keep) {
                     const int pos = back ? kSlots - 1 - (n_back + lanes_below(mk)) : n_clean + lanes_below(mf);
                     s_rec[pos] = r;
-                    if constexpr (MIXED == 0) s_grp[pos] = g;
                 }
                 n_clean += __popcll(mf);
                 n_back += __popcll(mk);
@@ -466,23 +463,13 @@ __global__ __launch_bounds__(kWave) void p2p_sum(P2PArgs a) {
             const int n_clean_pad = m_clean * R, n_back_pad = m_back * R;
             const int kb = kSlots - n_back_pad;        // back region [kb, kSlots), pad first
             if (lane < n_clean_pad - n_clean) s_rec[n_clean + lane] = pad_record<Rec>();
-            if (lane < n_back_pad - n_back) {
-                s_rec[kb + lane] = pad_record<Rec>();
-                if constexpr (MIXED == 0) s_grp[kb + lane] = 0;
-            }
+            if (lane < n_back_pad - n_back) s_rec[kb + lane] = pad_record<Rec>();
             __syncthreads();
 
             // phase h takes the h-th of the R runs of each region
             const Rec* pc = s_rec + h * m_clean;
             const Rec* pb = s_rec + kb + h * m_back;
-            if constexpr (MIXED == 0) {
-                const int32_t* gbk = s_grp + kb + h * m_back;
-#pragma unroll 4
-                for (int j = 0; j < m_clean; ++j) pair64<KT, false>(pc[j], x, y, z, tv, tv2, false, ax, ay, az);
-#pragma unroll 2
-                for (int j = 0; j < m_back; ++j)
-                    pair64<KT, true>(pb[j], x, y, z, tv, tv2, excl && gbk[j] == tg, ax, ay, az);
-            } else {
+            {
                 float bx = 0.f, by = 0.f, bz = 0.f;
 #pragma unroll 4
                 for (int j = 0; j < m_clean; ++j) pair32<KT, false>(pc[j], xs, ys, zs, false, bx, by, bz);
@@ -587,8 +574,211 @@ __global__ __launch_bounds__(kWave) void p2p_sum(P2PArgs a) {
     }
 }
 
+// Float64: one wave per item, T targets per lane where they fill the lanes, else
+// one.  A pair's operations take about as long as the LDS reads of its record,
+// so one target per lane is bound by both; T share a read.  The item's sources
+// are staged as one stream over the leaves of its list (nothing here depends on
+// the source leaf) and the loops run when kStage are nearly in.  One target per
+// lane and a run per leaf / T = 2 / 4: 3,840 cells in leaves 6.30 / 6.01 / 6.00 ms,
+// 300 cells in leaves of 64 241 / 195 / 189 us, the double layer of 1,000 cells 814 /
+// 747 / 736; 480 cells forward and backward 3.94 ms, 3.01 with T = 2 (of which 0.6
+// are the two source-side sums in one launch).  The adjoint kernels' vectors
+// leave room for 2.
+constexpr int kTrgFwd = 4, kTrgAdj = 2;
+constexpr int kStage = 128;
+template <int KT>
+struct Stage64 {
+    static constexpr int kSlots = kStage + 2 * kMaxRep;
+    typename P2PRec<KT, 0>::type rec[kSlots];
+    int32_t grp[kSlots];
+};
+
+template <int KT, int T>
+__device__ __forceinline__ void sum64_item(const P2PArgs& a, Stage64<KT>& st, int32_t L, int64_t t0, int nc) {
+    using Rec = typename P2PRec<KT, 0>::type;
+    constexpr int kSlots = Stage64<KT>::kSlots, NA = kSums<KT>;
+    const int lane = threadIdx.x;
+    const int Q = (nc + T - 1) / T, R = min(kMaxRep, kWave / Q);   // lanes per phase, phases
+    const int h = lane / Q, ti = lane - h * Q;
+    const bool on = h < R;
+    const int64_t nt = a.in.n_trg;
+    const bool excl = a.in.excl != 0;
+    double x[T], y[T], z[T], tv[T][3], tv2[T][3], acc[T][NA];
+    int32_t tg[T];
+    double blo[3] = {DBL_MAX, DBL_MAX, DBL_MAX}, bhi[3] = {-DBL_MAX, -DBL_MAX, -DBL_MAX};
+#pragma unroll
+    for (int k = 0; k < T; ++k) {
+        // lanes and slots past the last target mirror target t0
+        const int64_t idx = t0 + (on && ti + k * Q < nc ? ti + k * Q : 0);
+        x[k] = a.in.trg_xyz[idx];
+        y[k] = a.in.trg_xyz[nt + idx];
+        z[k] = a.in.trg_xyz[2 * nt + idx];
+        tg[k] = a.in.trg_group ? a.in.trg_group[idx] : 0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            tv[k][c] = KT >= 2 ? a.in.trg_vec[c * nt + idx] : 0.0;
+            tv2[k][c] = KT == 5 || KT == 7 ? a.in.trg_vec2[c * nt + idx] : 0.0;
+        }
+#pragma unroll
+        for (int c = 0; c < NA; ++c) acc[k][c] = 0.0;
+        blo[0] = fmin(blo[0], x[k]); bhi[0] = fmax(bhi[0], x[k]);
+        blo[1] = fmin(blo[1], y[k]); bhi[1] = fmax(bhi[1], y[k]);
+        blo[2] = fmin(blo[2], z[k]); bhi[2] = fmax(bhi[2], z[k]);
+        x[k] *= 2.0;
+        y[k] *= 2.0;
+        z[k] *= 2.0;
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        blo[c] = wmin(blo[c]);
+        bhi[c] = wmax(bhi[c]);
+    }
+    // the item's distinct target groups (uniform)
+    int32_t tgl[kMaxTGroups];
+#pragma unroll
+    for (int q = 0; q < kMaxTGroups; ++q) tgl[q] = 0;
+    int ntg = 0;
+    bool many_groups = false;
+    if (excl) {
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+            bool known = false;
+#pragma unroll
+            for (int q = 0; q < kMaxTGroups; ++q) known |= q < ntg && tg[k] == tgl[q];
+            uint64_t rem = __ballot(!known);
+            while (rem) {                              // each pass removes at least one lane
+                const int first = __builtin_ctzll(rem);
+                const int32_t g0 = __builtin_amdgcn_readlane(tg[k], first);
+#pragma unroll
+                for (int q = 0; q < kMaxTGroups; ++q)
+                    if (q == ntg) tgl[q] = g0;
+                many_groups |= ntg >= kMaxTGroups;
+                ++ntg;
+                rem &= ~__ballot(tg[k] == g0);
+            }
+        }
+    }
+
+    // staged sources: clean ones (outside the targets' box, no group shared with
+    // the targets) from the front, for the unmasked loop; from the back those
+    // that need the masks; those of a group that every target shares dropped
+    int n_clean = 0, n_back = 0;
+    auto run = [&]() {
+        const int m_clean = (n_clean + R - 1) / R, m_back = (n_back + R - 1) / R;
+        const int n_clean_pad = m_clean * R, n_back_pad = m_back * R;
+        const int kb = kSlots - n_back_pad;            // back region [kb, kSlots), pad first
+        if (lane < n_clean_pad - n_clean) st.rec[n_clean + lane] = pad_record<Rec>();
+        if (lane < n_back_pad - n_back) {
+            st.rec[kb + lane] = pad_record<Rec>();
+            st.grp[kb + lane] = 0;
+        }
+        __syncthreads();
+        // phase h takes the h-th of the R runs of each region (idle lanes the first)
+        const int hh = on ? h : 0;
+        const Rec* pc = st.rec + hh * m_clean;
+        const Rec* pb = st.rec + kb + hh * m_back;
+        const int32_t* gbk = st.grp + kb + hh * m_back;
+#pragma unroll T == 1 ? 4 : 1
+        for (int j = 0; j < m_clean; ++j) {
+            const Rec r = pc[j];
+            const double q4[3] = {4.0 * r.qx, 4.0 * r.qy, 4.0 * r.qz};
+#pragma unroll
+            for (int k = 0; k < T; ++k) pair64<KT, false>(r, q4, x[k], y[k], z[k], tv[k], tv2[k], false, acc[k]);
+        }
+#pragma unroll T == 1 ? 2 : 1
+        for (int j = 0; j < m_back; ++j) {
+            const Rec r = pb[j];
+            const double q4[3] = {4.0 * r.qx, 4.0 * r.qy, 4.0 * r.qz};
+            const int32_t g = gbk[j];
+#pragma unroll
+            for (int k = 0; k < T; ++k)
+                pair64<KT, true>(r, q4, x[k], y[k], z[k], tv[k], tv2[k], excl && g == tg[k], acc[k]);
+        }
+        __syncthreads();                               // before the next sources come in
+        n_clean = n_back = 0;
+    };
+    const Rec* rec = reinterpret_cast<const Rec*>(a.rec);
+    for (int64_t e = a.ulist_ofs[L]; e < a.ulist_ofs[L + 1]; ++e) {
+        const int32_t Ls = a.ulist[e];
+        const int64_t s0 = a.src_ofs[Ls], s1 = a.src_ofs[Ls + 1];
+        for (int64_t b = s0; b < s1; b += kWave) {
+            if (n_clean + n_back > kStage - kWave) run();
+            const bool in = b + lane < s1;
+            const int64_t si = in ? b + lane : b;
+            Rec r = rec[si];
+            const int32_t g = a.grp[si];
+            // coincident points are possible only inside the targets' box
+            const double gx = fmax(fmax(blo[0] - r.x, r.x - bhi[0]), 0.0);
+            const double gy = fmax(fmax(blo[1] - r.y, r.y - bhi[1]), 0.0);
+            const double gz = fmax(fmax(blo[2] - r.z, r.z - bhi[2]), 0.0);
+            bool back = __builtin_fma(gx, gx, __builtin_fma(gy, gy, gz * gz)) <= 1e-200;
+            if (excl) {
+                back |= many_groups;
+#pragma unroll
+                for (int q = 0; q < kMaxTGroups; ++q) back |= (q < ntg) && g == tgl[q];
+            }
+            const bool keep = in && !(excl && ntg == 1 && g == tgl[0]);
+            const uint64_t mf = __ballot(keep && !back), mk = __ballot(keep && back);
+            if (keep) {
+                const int pos = back ? kSlots - 1 - (n_back + lanes_below(mk)) : n_clean + lanes_below(mf);
+                r.x *= 2.0;
+                r.y *= 2.0;
+                r.z *= 2.0;
+                st.rec[pos] = r;
+                st.grp[pos] = g;
+            }
+            n_clean += __popcll(mf);
+            n_back += __popcll(mk);
+        }
+    }
+    run();
+
+    // add the R phases' sums of each target in a fixed order and store
+    static_assert(sizeof(st.rec) >= 3 * kWave * sizeof(double), "reduction reuses the staging array");
+    double* s_red = reinterpret_cast<double*>(st.rec);
+#pragma unroll
+    for (int k = 0; k < T; ++k)
+#pragma unroll
+        for (int o = 0; o < NA; o += 3) {
+            double v[3] = {acc[k][o], acc[k][o + 1], acc[k][o + 2]};
+            if (R > 1) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) s_red[c * kWave + lane] = v[c];
+                __syncthreads();
+                for (int q = 1; q < R; ++q)            // lanes ti + q Q < R Q <= 64
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) v[c] += s_red[c * kWave + (h == 0 ? lane + q * Q : lane)];
+                __syncthreads();
+            }
+            if (h == 0 && ti + k * Q < nc) {
+                const int64_t idx = t0 + ti + k * Q;
+                const int64_t i = a.in.trg_perm ? (int64_t)a.in.trg_perm[idx] : idx;
+                double* out = o ? a.out2 : a.out;
+                const double p = (o ? kPairScale2<KT> : kPairScale<KT>) * a.in.pref;
+                const int add = o ? a.accumulate2 : a.accumulate;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) out[c * nt + i] = add ? out[c * nt + i] + p * v[c] : p * v[c];
+            }
+        }
+}
+
+template <int KT, int T>
+__global__ __launch_bounds__(kWave, 3) void p2p_sum64(P2PArgs a) {
+    __shared__ Stage64<KT> st;
+    if (a.status && *a.status) return;
+    if (a.n_items && (int64_t)blockIdx.x >= *a.n_items) return;   // the grid covers the upper bound
+    const int32_t L = a.items[2 * blockIdx.x], ch = a.items[2 * blockIdx.x + 1];
+    const int64_t t0 = a.trg_ofs[L] + (int64_t)ch * kWave;
+    const int nc = (int)min(a.trg_ofs[L + 1] - t0, (int64_t)kWave);   // 1..64 (the plan makes no empty item)
+    // T per lane unless one keeps more lanes at work: steps of a source T / R, or
+    // 1 / R at 1.2 times the time
+    const int R1 = min(kMaxRep, kWave / nc), RT = min(kMaxRep, kWave / ((nc + T - 1) / T));
+    if (5 * T * R1 <= 6 * RT) sum64_item<KT, T>(a, st, L, t0, nc);
+    else sum64_item<KT, 1>(a, st, L, t0, nc);
+}
+
 size_t rec_size(int kernel, int mixed) {
-    if (kernel == 2 || kernel == 4 || kernel == 5) return sizeof(SrcSL64);
+    if (kernel == 2 || kernel >= 4) return sizeof(SrcSL64);
     if (kernel == 3) return sizeof(SrcDL64);
     if (!mixed) return kernel == 0 ? sizeof(P2PRec<0, 0>::type) : sizeof(P2PRec<1, 0>::type);
     return kernel == 0 ? sizeof(P2PRec<0, 1>::type) : sizeof(P2PRec<1, 1>::type);
@@ -656,7 +846,7 @@ struct P2PItems {
     int64_t grid;             // workgroups of the sum
 };
 
-template <int KT, int MIXED>
+template <int KT, int MIXED, int T = KT >= 2 ? kTrgAdj : kTrgFwd>
 hipError_t run_p2p(P2PArgs a, const P2PItems& it, void* ws, hipStream_t stream, const KernelTimer& timer) {
     const P2PLayout l = p2p_layout(KT, MIXED, a.in.n_src, a.in.n_trg, it.n_leaves);
     char* base = static_cast<char*>(ws);
@@ -680,38 +870,38 @@ hipError_t run_p2p(P2PArgs a, const P2PItems& it, void* ws, hipStream_t stream, 
     if (timer.on()) (void)hipEventRecord(timer.start, stream);
     if constexpr (MIXED != 0) {
         if (a.in.pair_class)
-            p2p_sum<KT, MIXED, true><<<dim3((unsigned)it.grid), dim3(kWave), 0, stream>>>(a);
+            p2p_sum_mixed<KT, true><<<dim3((unsigned)it.grid), dim3(kWave), 0, stream>>>(a);
         else
-            p2p_sum<KT, MIXED><<<dim3((unsigned)it.grid), dim3(kWave), 0, stream>>>(a);
+            p2p_sum_mixed<KT><<<dim3((unsigned)it.grid), dim3(kWave), 0, stream>>>(a);
     } else {
-        p2p_sum<KT, MIXED><<<dim3((unsigned)it.grid), dim3(kWave), 0, stream>>>(a);
+        p2p_sum64<KT, T><<<dim3((unsigned)it.grid), dim3(kWave), 0, stream>>>(a);
     }
     hipError_t e = hipGetLastError();
     if (timer.on()) (void)hipEventRecord(timer.stop, stream);
     return e;
 }
 
-template <int KT, int MIXED>
-hipError_t run_p2p_typed(const SumInputs& in, const P2PItems& it, double* out, int accumulate, void* ws,
-                         hipStream_t stream, const KernelTimer& timer) {
+
+hipError_t run_p2p_any(const SumInputs& in, const P2PItems& it, const P2POut& out, void* ws, hipStream_t stream,
+                       const KernelTimer& timer) {
     P2PArgs a{};
     a.in = in;
-    a.out = out;
-    a.accumulate = accumulate;
-    return run_p2p<KT, MIXED>(a, it, ws, stream, timer);
-}
-
-hipError_t run_p2p_any(const SumInputs& in, const P2PItems& it, double* out, int accumulate, void* ws,
-                       hipStream_t stream, const KernelTimer& timer) {
-    if (in.kernel == 2) return run_p2p_typed<2, 0>(in, it, out, accumulate, ws, stream, timer);
-    if (in.kernel == 3) return run_p2p_typed<3, 0>(in, it, out, accumulate, ws, stream, timer);
-    if (in.kernel == 4) return run_p2p_typed<4, 0>(in, it, out, accumulate, ws, stream, timer);
-    if (in.kernel == 5) return run_p2p_typed<5, 0>(in, it, out, accumulate, ws, stream, timer);
-    if (in.kernel == 0)
-        return in.mixed ? run_p2p_typed<0, 1>(in, it, out, accumulate, ws, stream, timer)
-                        : run_p2p_typed<0, 0>(in, it, out, accumulate, ws, stream, timer);
-    return in.mixed ? run_p2p_typed<1, 1>(in, it, out, accumulate, ws, stream, timer)
-                    : run_p2p_typed<1, 0>(in, it, out, accumulate, ws, stream, timer);
+    a.out = out.sum;
+    a.accumulate = out.accumulate;
+    a.out2 = out.sum2;
+    a.accumulate2 = out.accumulate2;
+    switch (in.kernel) {
+        case 0: return in.mixed ? run_p2p<0, 1>(a, it, ws, stream, timer) : run_p2p<0, 0>(a, it, ws, stream, timer);
+        case 1: return in.mixed ? run_p2p<1, 1>(a, it, ws, stream, timer) : run_p2p<1, 0>(a, it, ws, stream, timer);
+        case 2: return run_p2p<2, 0>(a, it, ws, stream, timer);
+        case 3: return run_p2p<3, 0>(a, it, ws, stream, timer);
+        case 4: return run_p2p<4, 0>(a, it, ws, stream, timer);
+        case 5: return run_p2p<5, 0>(a, it, ws, stream, timer);
+        case 6: return run_p2p<6, 0>(a, it, ws, stream, timer);
+        case 7: return run_p2p<7, 0>(a, it, ws, stream, timer);
+        // kernel 0 with the adjoint's lanes: kernel 6's first sum bit for bit
+        default: return run_p2p<0, 0, kTrgAdj>(a, it, ws, stream, timer);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -853,13 +1043,12 @@ hipError_t launch_p2p(const SumInputs& in, const stokes_p2p_plan* plan, double* 
                       void* ws, hipStream_t stream, const KernelTimer& timer) {
     const P2PItems it{plan->d_src_ofs, plan->d_trg_ofs, plan->d_ulist_ofs, plan->d_ulist, plan->d_items,
                       nullptr, nullptr, plan->n_leaves, plan->n_items};
-    return run_p2p_any(in, it, out, accumulate, ws, stream, timer);
+    return run_p2p_any(in, it, P2POut{out, accumulate, nullptr, 0}, ws, stream, timer);
 }
 
 hipError_t launch_p2p_csr(const SumInputs& in, int32_t n_leaves, const int64_t* src_ofs, const int64_t* trg_ofs,
-                          const int64_t* ulist_ofs, const int32_t* ulist, int64_t n_ulist, double* out,
-                          int accumulate, void* ws, hipStream_t st, const KernelTimer& timer, bool check,
-                          const int32_t* ext_status) {
+                          const int64_t* ulist_ofs, const int32_t* ulist, int64_t n_ulist, const P2POut& out,
+                          void* ws, hipStream_t st, const KernelTimer& timer, bool check, const int32_t* ext_status) {
     const P2PLayout l = p2p_layout(in.kernel, in.mixed, in.n_src, in.n_trg, n_leaves);
     char* base = static_cast<char*>(ws);
     int32_t* status = reinterpret_cast<int32_t*>(base + l.off_status);
@@ -900,10 +1089,13 @@ hipError_t launch_p2p_csr(const SumInputs& in, int32_t n_leaves, const int64_t* 
         p2p_item_order<<<p2p_grid(l.max_items), kP2PThreads, 0, st>>>(items, vals, n_items, sorted);
         if (!chk()) return e;
         const P2PItems it{src_ofs, trg_ofs, ulist_ofs, ulist, sorted, n_items, status, n_leaves, l.max_items};
-        if ((e = run_p2p_any(in, it, out, accumulate, ws, st, timer)) != hipSuccess) return e;
+        if ((e = run_p2p_any(in, it, out, ws, st, timer)) != hipSuccess) return e;
     }
-    p2p_poison<<<p2p_grid(3 * in.n_trg), kP2PThreads, 0, st>>>(status, out, 3 * in.n_trg);
-    chk();
+    for (double* o : {out.sum, out.sum2})
+        if (o) {
+            p2p_poison<<<p2p_grid(3 * in.n_trg), kP2PThreads, 0, st>>>(status, o, 3 * in.n_trg);
+            if (!chk()) return e;
+        }
     return e;
 }
 
@@ -1013,12 +1205,13 @@ hipError_t launch_p2p_transpose(int32_t n_leaves, const int64_t* ulist_ofs, cons
 //   dL/df_m = c w_m sum_n S(r_nm) g_n            kernel 0, transposed (S even in r)
 //   dL/dy_m = c sum_n K(r_mn; q_m, g_n)          kernel 2, transposed (K odd in r,
 //                                                symmetric in its two vectors)
+//   the last two together                         kernel 6 (dL/df alone: kernel 8)
 // double layer
 //   dL/dx_n   = c sum_m G(r_nm; n_m, q_m, g_n)   kernel 3, forward lists
 //   dL/dphi_m = c w_m sum_n r (r.n_m)(r.g_n)/rho^5 with r = r_nm
 //             = -c w_m sum_n r' (r'.n_m)(r'.g_n)/rho^5, r' = r_mn   kernel 4, transposed
 //   dL/dy_m   = -c sum_n G(r_nm; ...) = -c sum_n G(r_mn; n_m, q_m, g_n)   kernel 5,
-//               transposed (G even in r)
+//               transposed (G even in r); the last two together   kernel 7
 // ---------------------------------------------------------------------------
 namespace {
 
@@ -1039,9 +1232,9 @@ P2PVjpLayout p2p_vjp_layout(int kernel, int64_t ns, int64_t nt, int32_t nl, int6
     take(l.off_tws, p2p_transpose_bytes(nu));
     take(l.off_q, (size_t)ns * 24);
     take(l.off_tmp, (size_t)ns * 24);
-    const int k_trg = kernel ? 3 : 2, k_f = kernel ? 4 : 0, k_src = kernel ? 5 : 2;
-    const size_t p = std::max({p2p_workspace_bytes(k_trg, 0, ns, nt, nl), p2p_workspace_bytes(k_f, 0, nt, ns, nl),
-                               p2p_workspace_bytes(k_src, 0, nt, ns, nl)});
+    // the source-side kernels have the same records
+    const int k_trg = kernel ? 3 : 2, k_src = kernel ? 7 : 6;
+    const size_t p = std::max(p2p_workspace_bytes(k_trg, 0, ns, nt, nl), p2p_workspace_bytes(k_src, 0, nt, ns, nl));
     take(l.off_p2p, p);
     l.total = off;
     return l;
@@ -1090,8 +1283,8 @@ hipError_t launch_p2p_vjp(const SumInputs& in, int32_t n_leaves, const int64_t* 
         t.mixed = 0;
         t.trg_vec = grad_vel;
         t.pair_class = nullptr;
-        e = launch_p2p_csr(t, n_leaves, src_ofs, trg_ofs, ulist_ofs, ulist, n_ulist, grad_trg, accumulate,
-                           base + l.off_p2p, st, none, false, status);
+        e = launch_p2p_csr(t, n_leaves, src_ofs, trg_ofs, ulist_ofs, ulist, n_ulist,
+                           P2POut{grad_trg, accumulate, nullptr, 0}, base + l.off_p2p, st, none, false, status);
         if (e != hipSuccess) return e;
     }
     if (!grad_density && !grad_src) return hipSuccess;
@@ -1114,29 +1307,27 @@ hipError_t launch_p2p_vjp(const SumInputs& in, int32_t n_leaves, const int64_t* 
     tr.src_group = in.trg_group;
     tr.trg_group = in.src_group;
     tr.pref = dl ? -in.pref : in.pref;
-    if (grad_density) {
-        double* tmp = reinterpret_cast<double*>(base + l.off_tmp);
-        SumInputs f = tr;
-        f.kernel = dl ? 4 : 0;
-        f.trg_vec = dl ? in.normal : nullptr;
-        e = launch_p2p_csr(f, n_leaves, trg_ofs, src_ofs, uot, ult, n_ulist, tmp, 0, base + l.off_p2p, st, none, false,
-                           status);
-        if (e != hipSuccess) return e;
-        p2p_add_times_w<<<p2p_grid(ns), kP2PThreads, 0, st>>>(in.weight, tmp, ns, grad_density, accumulate);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    // both source-side sums in one launch when both are asked for
+    double* tmp = reinterpret_cast<double*>(base + l.off_tmp);
     if (grad_src) {
         double* q = reinterpret_cast<double*>(base + l.off_q);
         p2p_times_w<<<p2p_grid(ns), kP2PThreads, 0, st>>>(in.weight, in.density, ns, q);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        SumInputs y = tr;
-        y.kernel = dl ? 5 : 2;
-        y.trg_vec = dl ? in.normal : q;
-        y.trg_vec2 = dl ? q : nullptr;
-        e = launch_p2p_csr(y, n_leaves, trg_ofs, src_ofs, uot, ult, n_ulist, grad_src, accumulate, base + l.off_p2p,
-                           st, none, false, status);
+        tr.trg_vec = dl ? in.normal : q;
+        tr.trg_vec2 = dl ? q : nullptr;
+        tr.kernel = dl ? (grad_density ? 7 : 5) : (grad_density ? 6 : 2);
+        const P2POut out = grad_density ? P2POut{tmp, 0, grad_src, accumulate} : P2POut{grad_src, accumulate, nullptr, 0};
+        e = launch_p2p_csr(tr, n_leaves, trg_ofs, src_ofs, uot, ult, n_ulist, out, base + l.off_p2p, st, none, false,
+                           status);
+    } else {
+        tr.kernel = dl ? 4 : 8;
+        tr.trg_vec = dl ? in.normal : nullptr;
+        e = launch_p2p_csr(tr, n_leaves, trg_ofs, src_ofs, uot, ult, n_ulist, P2POut{tmp, 0, nullptr, 0},
+                           base + l.off_p2p, st, none, false, status);
     }
-    return e;
+    if (e != hipSuccess || !grad_density) return e;
+    p2p_add_times_w<<<p2p_grid(ns), kP2PThreads, 0, st>>>(in.weight, tmp, ns, grad_density, accumulate);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

@@ -21,14 +21,18 @@ int64_t p2p_plan_info(const stokes_p2p_plan* p, int which);
 hipError_t launch_p2p(const SumInputs& in, const stokes_p2p_plan* plan, double* out, int accumulate,
                       void* ws, hipStream_t stream, const KernelTimer& timer);
 
+// The output of a leaf-to-leaf sum, and of the second sum of the kernels that
+// give two.
+struct P2POut { double* sum; int accumulate; double* sum2; int accumulate2; };
+
 // The same sum from device leaf arrays, checked and cut into sorted work items
 // on the device; malformed arrays make every output component NaN.  check =
 // false skips the checks (layouts built by the library itself; n_ulist is then
 // not used).
 hipError_t launch_p2p_csr(const SumInputs& in, int32_t n_leaves, const int64_t* src_ofs, const int64_t* trg_ofs,
-                          const int64_t* ulist_ofs, const int32_t* ulist, int64_t n_ulist, double* out,
-                          int accumulate, void* ws, hipStream_t stream, const KernelTimer& timer,
-                          bool check = true, const int32_t* ext_status = nullptr);
+                          const int64_t* ulist_ofs, const int32_t* ulist, int64_t n_ulist, const P2POut& out,
+                          void* ws, hipStream_t stream, const KernelTimer& timer, bool check = true,
+                          const int32_t* ext_status = nullptr);
 // (ext_status, with check = false: the verdict of an earlier launch_p2p_check.)
 
 // Clears *status and sets it when the device leaf arrays break the layout's

@@ -17,7 +17,7 @@
 //   * tiles of 64 points; a wave owns T consecutive tiles as rows (T points
 //     per lane, in registers), a workgroup 4 T tiles (a row block);
 //   * the triangle of (row block W, column tile b >= first tile of W) units
-//     is cut into equal stream-K ranges, one per resident workgroup; rows
+//     is cut into stream-K ranges of equal weight, one per workgroup; rows
 //     stay in registers along a range, their sums flushed as one segment per
 //     (workgroup, row block);
 //   * a unit: each lane takes one column point (its record and running sums)

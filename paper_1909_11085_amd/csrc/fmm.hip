@@ -663,10 +663,14 @@ constexpr int kM2LBlocks = kILSize + 1;
 constexpr int kGemmNT = 64;          // boxes per tile
 constexpr int kGemmKC = 16;          // K rows per LDS chunk (4 MFMA steps)
 constexpr int kGemmThreads = 512;    // 8 waves: 4 column groups x 2 row halves
+constexpr int kGemmBS = kGemmNT + 2; // LDS row of B: a wave's stores (8 rows, 8 columns) meet no bank twice
+constexpr int kGemmB = kGemmKC * kGemmBS;
 constexpr int kGemmBPT = kGemmKC * kGemmNT / kGemmThreads;   // B values per thread and chunk
 constexpr int kM2LUnits = 4096;      // work units a level's M2L aims for (K is split to reach them)
 constexpr double kM2LDenseFill = 0.35;   // below this interaction-list fill, M2L runs as pair sums
 constexpr int kILCountParts = 2048;      // workgroups (partial counts) of the interaction-list count
+constexpr int64_t kM2LPairBlocks = 8192;   // workgroups of a pair-sum level at most (most levels have none)
+constexpr int kM2LPerClass = 32;      // workgroups per class and row group: 256 CUs in 8 classes
 constexpr int kM2LMinSplits = 3;     // so that a split has at most kM2LMaxSplitBlocks blocks
 constexpr int kM2LMaxSplitBlocks = (kILSize + 1 + kM2LMinSplits - 1) / kM2LMinSplits;
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -728,14 +732,16 @@ __global__ __launch_bounds__(kFBlock) void m2l_matrix_kernel(const double* __res
 }
 
 // Tile shape of the GEMMs for mw = 16 RB rows per workgroup: H row blocks per
-// wave half, na doubles per A chunk, APT of them loaded per thread.  Up to
+// wave half, na doubles per A chunk in loads of one wave each (16 bytes a lane),
+// LPW of them per wave at most.  Up to
 // order 6 a workgroup takes all mp rows; above, the rows are cut into row
 // groups of mw (the register and LDS footprint of RB = 29 at most).
 constexpr int kGemmMaxRB = 29;
 template <int RB> struct GemmShape {
     static_assert(RB <= kGemmMaxRB, "row blocks per workgroup");
     static constexpr int mw = 16 * RB, H = (RB + 1) / 2, na = kGemmKC * mw;
-    static constexpr int APT = (na + kGemmThreads - 1) / kGemmThreads;
+    static constexpr int loads = na / (2 * kWave), LPW = (loads + kGemmThreads / kWave - 1) / (kGemmThreads / kWave);
+    static_assert(loads * 2 * kWave == na, "whole wave loads");
 };
 // Row blocks per workgroup for mp rows, and the row groups that cover them.
 int gemm_rb(int mp) {
@@ -747,58 +753,69 @@ __host__ __device__ inline int gemm_groups(int mp, int rb) { return (mp / 16 + r
 // C(r0 + row, j) = A B(:, j) for the 64 columns of a tile and rows r0 ..
 // r0 + mw - 1, over the K chunks chunk(0) .. chunk(n - 1) of kGemmKC rows
 // each, then store(j, row, value) for the rows < nrow.  A: K x lda, k-major
-// (A[k * lda + row]); rows at or past lda read as zero.
-// Each chunk of A and of B goes through LDS (two buffers); chunk t + 2 is in
-// flight in registers while chunk t is multiplied.  loadb(q, j, k)
-// gives row k of chunk q for column j; busy(t, g) is false when chunk t is
-// zero for all 16 columns of group g (that wave skips its products).  Eight
+// (A[k * lda + row], 16-byte aligned); rows at or past lda hold other rows'
+// values (their results are not stored).
+// Each chunk of A and of B goes through LDS, two buffers each (A0 and A1 apart,
+// so that the compiler sees that a load into one does not concern reads of the
+// other).  A's chunk t + 2 is loaded straight into the buffer that chunk t
+// leaves, while chunk t + 1 is multiplied; B's goes through registers.  Through
+// registers A took 15 stores and their addresses per thread and chunk with the
+// matrix cores idle, the waves being in step (order 6, 3,840
+// cells: the M2L products 27.2 ms, 24.2 so; their MFMA work alone takes 16.6).  What runs
+// between two chunks' products is kept short for the same reason: rowa(),
+// fetchb(j, k, raw, tag) and busy(g) give, each for one chunk after the other,
+// its first K row in A, what to read for its rows k and k + 8 of column j, and
+// whether the chunk is nonzero for any of the 16 columns of group g (else that
+// wave skips its products), and keep what does not change from chunk to chunk;
+// valb(raw, tag, j) makes the value of what was read.  Eight
 // waves: wave w owns columns 16 (w & 3) .. + 15 and the NR row blocks from
 // (w >> 2) H, H = ceil(RB / 2) (NR = H for the lower half, RB - H for the
 // upper: the caller picks the instance with a wave-uniform branch).  acc[i]
 // holds row block (w >> 2) H + i; lane l, entry r is row (l >> 4) + 4 r and
 // column 16 (w & 3) + (l & 15).
-template <int RB, int NR, typename Chunk, typename LoadB, typename Busy, typename Store>
-__device__ __forceinline__ void gemm_tile(const double* __restrict__ A, int lda, int r0, int64_t n, Chunk&& chunk,
-                                          LoadB&& loadb, Busy&& busy, double* As, double* Bs, int nrow,
-                                          Store&& store) {
+template <int RB, int NR, typename RowA, typename FetchB, typename ValB, typename Busy, typename Store>
+__device__ __forceinline__ void gemm_tile(const double* __restrict__ A, int lda, int r0, int n, RowA&& rowa,
+                                          FetchB&& fetchb, ValB&& valb, Busy&& busy, double* A0, double* A1, double* Bs,
+                                          int nrow, Store&& store) {
     using G = GemmShape<RB>;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int cg = wave & 3, rb0 = (wave >> 2) * G::H;
     const int bj = tid >> 3, bk = tid & 7;                   // B rows bk, bk + 8, ... of column bj
     v4d acc[NR];
 #pragma unroll
     for (int i = 0; i < NR; ++i) acc[i] = v4d{0.0, 0.0, 0.0, 0.0};
-    double pa[G::APT], pb[kGemmBPT];
-    auto fetch = [&](int64_t t) {
-        const int64_t q = chunk(t);
-        const double* Aq = A + q * kGemmKC * lda + r0;
+    // load i of this wave: doubles 128 (wave + 8 i) .. + 127 of the chunk, two per lane
+    uint32_t from[G::LPW];                                    // byte offsets in the chunk
 #pragma unroll
-        for (int i = 0; i < G::APT; ++i) {
-            const int e = tid + i * kGemmThreads;
-            const int k = e / G::mw, r = e - k * G::mw;
-            pa[i] = (e < G::na && r0 + r < lda) ? Aq[k * lda + r] : 0.0;
+    for (int i = 0; i < G::LPW; ++i) {
+        const int e = 2 * kWave * (wave + i * (kGemmThreads / kWave)) + 2 * lane, k = e / G::mw, r = e - k * G::mw;
+        from[i] = (uint32_t)(k * lda + (r0 + r < lda ? r0 + r : 0)) * (uint32_t)sizeof(double);
+    }
+    auto load_a = [&](double* Ab) {
+        const char* Aq = reinterpret_cast<const char*>(A + (int64_t)rowa() * lda);
+#pragma unroll
+        for (int i = 0; i < G::LPW; ++i) {
+            const int w = wave + i * (kGemmThreads / kWave);
+            if (i + 1 < G::LPW || w < G::loads)                   // uniform over the wave
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Aq + from[i]),
+                                                 (__attribute__((address_space(3))) void*)(Ab + 2 * kWave * w), 16, 0,
+                                                 0);
         }
-#pragma unroll
-        for (int i = 0; i < kGemmBPT; ++i) pb[i] = loadb(q, bj, bk + 8 * i);
     };
-    auto put = [&](int buf) {
-        double* Ab = As + buf * G::na;
+    double pb[kGemmBPT];
+    int tag[kGemmBPT];
+    auto fetch_b = [&]() { fetchb(bj, bk, pb, tag); };
+    auto put_b = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < G::APT; ++i) {
-            const int e = tid + i * kGemmThreads;
-            if (e < G::na) Ab[e] = pa[i];
-        }
-#pragma unroll
-        for (int i = 0; i < kGemmBPT; ++i) Bs[buf * (kGemmKC * kGemmNT) + (bk + 8 * i) * kGemmNT + bj] = pb[i];
+        for (int i = 0; i < kGemmBPT; ++i)
+            Bs[buf * kGemmB + (bk + 8 * i) * kGemmBS + bj] = valb(pb[i], tag[i], bj);
     };
-    auto multiply = [&](int64_t t) {
-        if (!busy(t, cg)) return;                                 // uniform over the wave
-        const double* Ab = As + (t & 1) * G::na;
-        const double* Bb = Bs + (t & 1) * (kGemmKC * kGemmNT);
+    auto multiply = [&](const double* Ab, const double* Bb) {
+        if (!busy(cg)) return;                                    // uniform over the wave
 #pragma unroll
         for (int st = 0; st < kGemmKC / 4; ++st) {
             const int kr = 4 * st + (lane >> 4);
-            const double bv = Bb[kr * kGemmNT + 16 * cg + (lane & 15)];
+            const double bv = Bb[kr * kGemmBS + 16 * cg + (lane & 15)];
             double av[NR];
 #pragma unroll
             for (int i = 0; i < NR; ++i) av[i] = Ab[kr * G::mw + 16 * (rb0 + i) + (lane & 15)];
@@ -806,27 +823,36 @@ __device__ __forceinline__ void gemm_tile(const double* __restrict__ A, int lda,
             for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv, acc[i], 0, 0, 0);
         }
     };
-    // LDS holds chunks t and t + 1 (buffers t & 1 and its pair); the registers
-    // hold chunk t + 2, fetched while chunk t is multiplied
+    // every wave's loads have landed in LDS once all have passed their wait
+    auto landed = [] {
+        __builtin_amdgcn_s_waitcnt(0x0F70);                       // vmcnt(0)
+        __syncthreads();
+    };
     if (n > 0) {
-        fetch(0);
-        put(0);
+        load_a(A0);
+        fetch_b();
+        put_b(0);
     }
     if (n > 1) {
-        fetch(1);
-        put(1);
+        load_a(A1);
+        fetch_b();
+        put_b(1);
     }
-    if (n > 2) fetch(2);
-    __syncthreads();
-    for (int64_t t = 0; t < n; ++t) {
-        multiply(t);
-        __syncthreads();                                          // every wave is done with buffer t & 1
+    if (n > 2) fetch_b();
+    landed();
+    // LDS holds chunks t and t + 1, the registers B's chunk t + 2
+    auto step = [&](int t, double* Ab, int buf) {
+        multiply(Ab, Bs + buf * kGemmB);
+        landed();                                                 // every wave is done with buffer t & 1
         if (t + 2 < n) {
-            // chunk t + 2 into the freed buffer: it is read after the next
-            // iteration's barrier
-            put((int)(t & 1));
-            if (t + 3 < n) fetch(t + 3);
+            put_b(buf);
+            if (t + 3 < n) fetch_b();
+            load_a(Ab);
         }
+    };
+    for (int t = 0; t < n; t += 2) {
+        step(t, A0, 0);
+        if (t + 1 < n) step(t + 1, A1, 1);
     }
 #pragma unroll
     for (int i = 0; i < NR; ++i)
@@ -838,15 +864,15 @@ __device__ __forceinline__ void gemm_tile(const double* __restrict__ A, int lda,
 }
 
 // Runs gemm_tile with the row-block count of this wave's half (a scalar branch).
-template <int RB, typename Chunk, typename LoadB, typename Busy, typename Store>
-__device__ __forceinline__ void gemm_tile_any(const double* __restrict__ A, int lda, int r0, int64_t n, Chunk&& chunk,
-                                              LoadB&& loadb, Busy&& busy, double* As, double* Bs, int nrow,
-                                              Store&& store) {
+template <int RB, typename RowA, typename FetchB, typename ValB, typename Busy, typename Store>
+__device__ __forceinline__ void gemm_tile_any(const double* __restrict__ A, int lda, int r0, int n, RowA&& rowa,
+                                              FetchB&& fetchb, ValB&& valb, Busy&& busy, double* A0, double* A1,
+                                              double* Bs, int nrow, Store&& store) {
     using G = GemmShape<RB>;
     if (__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave) >> 2) != 0)
-        gemm_tile<RB, RB - G::H>(A, lda, r0, n, chunk, loadb, busy, As, Bs, nrow, store);
+        gemm_tile<RB, RB - G::H>(A, lda, r0, n, rowa, fetchb, valb, busy, A0, A1, Bs, nrow, store);
     else
-        gemm_tile<RB, G::H>(A, lda, r0, n, chunk, loadb, busy, As, Bs, nrow, store);
+        gemm_tile<RB, G::H>(A, lda, r0, n, rowa, fetchb, valb, busy, A0, A1, Bs, nrow, store);
 }
 
 // Boxes whose check vectors are the columns of vbuf, in list order.
@@ -934,90 +960,128 @@ __global__ __launch_bounds__(kFBlock) void il_count_kernel(FmmDev a, M2LArgs g, 
 }
 
 // Partial V = A_c E over K split `split` for one tile of 64 listed boxes of
-// class blockIdx.x & 7 and one row group: blockIdx.x >> 3 = rg * units + u,
-// u = split * tiles + tile, units = gridDim.x / (8 row groups).  K blocks whose
+// class blockIdx.x & 7 and one row group, unit u = split * tiles + tile, for the
+// units u = v, v + V, ... of blockIdx.x >> 3 = rg * V + v: a workgroup per CU
+// (a workgroup per unit, up to the most a level can have, left some 32,000
+// workgroups of 152 KB of LDS each to find nothing to do: 0.2 ms a level).  K blocks whose
 // source box is missing for all 64 columns are skipped.
 template <int RB>
 __global__ __launch_bounds__(kGemmThreads) void m2l_gemm_kernel(FmmDev a, M2LArgs g, int l) {
     using G = GemmShape<RB>;
-    __shared__ double As[2 * G::na];
-    __shared__ double Bs[2 * kGemmKC * kGemmNT];
+    __shared__ alignas(16) double A0[G::na], A1[G::na];
+    __shared__ double Bs[2 * kGemmB];
     __shared__ int32_t s_act[kM2LMaxSplitBlocks + 1];          // active blocks of this split, then the count
     __shared__ int32_t s_src[kM2LMaxSplitBlocks][kGemmNT];     // their source boxes per column (-1: none)
     __shared__ uint8_t s_grp[kM2LMaxSplitBlocks][kGemmNT / 16]; // any source among 16 columns
     const int c = blockIdx.x & 7;
     const int mp = g.mp, ng = gemm_groups(mp, RB);
-    const int64_t units = gridDim.x / (8 * ng), w = blockIdx.x >> 3, P = (int64_t)1 << (3 * (l - 1));
-    const int rg = (int)(w / units);
-    const int64_t u = w % units;
+    const int64_t V = gridDim.x / (8 * ng), w = blockIdx.x >> 3, P = (int64_t)1 << (3 * (l - 1));
+    const int rg = (int)(w / V);
     const int64_t S = g.sched[0];
     if (rg >= ng) return;
     if (g.sched[1]) return;                                    // this level runs as pair sums
     const int64_t c0 = g.cscan[c * P], c1 = c < 7 ? g.cscan[(c + 1) * P] : *g.ctotal;
     const int64_t tiles = (c1 - c0 + kGemmNT - 1) / kGemmNT;
-    // split-major: the tiles running together on one XCD share one slice of A_c in its L2
-    const int64_t split = tiles > 0 ? u / tiles : S, tile = tiles > 0 ? u % tiles : 0;
-    if (split >= S) return;                                    // uniform over the workgroup
-    const int64_t col0 = c0 + tile * kGemmNT;
-    const int blk0 = (int)(split * kM2LBlocks / S), blk1 = (int)((split + 1) * kM2LBlocks / S);
-    const int64_t nbx = (int64_t)1 << l;
-    const int32_t* il = g.il + c * kILSize * 3;
-    // source box of block blk for column j (-1: none); the last block is the
-    // parent's L2L, present from level 3 on
-    auto source = [&](int blk, int j) -> int64_t {
-        if (col0 + j >= c1) return -1;
-        const int64_t b = g.list[col0 + j];
-        if (blk == kILSize) return l > 2 ? (b >> 3) : -1;
-        const int64_t ai[3] = {compact3(b) + il[3 * blk], compact3(b >> 1) + il[3 * blk + 1],
-                               compact3(b >> 2) + il[3 * blk + 2]};
-        if (ai[0] < 0 || ai[1] < 0 || ai[2] < 0 || ai[0] >= nbx || ai[1] >= nbx || ai[2] >= nbx) return -1;
-        const int64_t box = (int64_t)morton(ai[0], ai[1], ai[2]);
-        return a.sslot[a.base[l] + box] >= 0 ? box : -1;
-    };
-    {
-        const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-        for (int blk = blk0 + wave; blk < blk1; blk += kGemmThreads / kWave) {   // lane = column
-            const int64_t src = source(blk, lane);
-            s_src[blk - blk0][lane] = (int32_t)src;
-            const uint64_t m = __ballot(src >= 0);
-            if (lane == 0) {
-                s_act[blk - blk0] = m != 0 ? 1 : 0;
-                for (int gq = 0; gq < kGemmNT / 16; ++gq) s_grp[blk - blk0][gq] = ((m >> (16 * gq)) & 0xffffull) != 0;
+    const int64_t listed = *g.ctotal;
+    for (int64_t u = w % V; u < S * tiles; u += V) {
+        // split-major: the tiles running together on one XCD share one slice of A_c in its L2
+        const int64_t split = u / tiles, tile = u % tiles;
+        __syncthreads();                                           // the previous unit's tables have been read
+        const int64_t col0 = c0 + tile * kGemmNT;
+        const int blk0 = (int)(split * kM2LBlocks / S), blk1 = (int)((split + 1) * kM2LBlocks / S);
+        const int64_t nbx = (int64_t)1 << l;
+        const int32_t* il = g.il + c * kILSize * 3;
+        // source box of block blk for column j (-1: none); the last block is the
+        // parent's L2L, present from level 3 on
+        auto source = [&](int blk, int j) -> int64_t {
+            if (col0 + j >= c1) return -1;
+            const int64_t b = g.list[col0 + j];
+            if (blk == kILSize) return l > 2 ? (b >> 3) : -1;
+            const int64_t ai[3] = {compact3(b) + il[3 * blk], compact3(b >> 1) + il[3 * blk + 1],
+                                   compact3(b >> 2) + il[3 * blk + 2]};
+            if (ai[0] < 0 || ai[1] < 0 || ai[2] < 0 || ai[0] >= nbx || ai[1] >= nbx || ai[2] >= nbx) return -1;
+            const int64_t box = (int64_t)morton(ai[0], ai[1], ai[2]);
+            return a.sslot[a.base[l] + box] >= 0 ? box : -1;
+        };
+        {
+            const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+            for (int blk = blk0 + wave; blk < blk1; blk += kGemmThreads / kWave) {   // lane = column
+                const int64_t src = source(blk, lane);
+                s_src[blk - blk0][lane] = (int32_t)src;
+                const uint64_t m = __ballot(src >= 0);
+                if (lane == 0) {
+                    s_act[blk - blk0] = m != 0 ? 1 : 0;
+                    for (int gq = 0; gq < kGemmNT / 16; ++gq) s_grp[blk - blk0][gq] = ((m >> (16 * gq)) & 0xffffull) != 0;
+                }
             }
         }
+        __syncthreads();
+        if (threadIdx.x == 0) {                                    // active blocks (relative to blk0), in order
+            int n = 0;
+            for (int k = 0; k < blk1 - blk0; ++k)
+                if (s_act[k]) s_act[n++] = k;
+            s_act[kM2LMaxSplitBlocks] = n;
+        }
+        __syncthreads();
+        const int nact = s_act[kM2LMaxSplitBlocks];
+        const int cpb = mp / kGemmKC;                              // chunks per K block (the plan has kb == mp)
+        const double inv_h = (double)(1 << l) / a.R;
+        const double* ue = a.ue + a.base[l] * a.n3;
+        const double* de = a.de + a.base[l - 1] * a.n3;
+        const double* sig = a.sig ? a.sig + a.base[l] : nullptr;
+        auto act = [&](int i) { return __builtin_amdgcn_readfirstlane(s_act[i]); };
+        int ra = 0, rk = 0, row = 0;                               // A: active block, chunk of it
+        auto rowa = [&]() {
+            if (rk == 0) row = (blk0 + act(ra)) * mp;
+            const int r = row + rk * kGemmKC;
+            if (++rk == cpb) rk = 0, ++ra;
+            return r;
+        };
+        int ga = 0, gk = 0;
+        bool some = false;
+        auto busy = [&](int gq) {
+            if (gk == 0) some = s_grp[act(ga)][gq] != 0;
+            if (++gk == cpb) gk = 0, ++ga;
+            return some;
+        };
+        int ba = 0, bc = 0;
+        int32_t src = -1;
+        bool up = false;                                           // the parent's column (uniform)
+        const double* col = ue;
+        auto fetchb = [&](int j, int k, double (&raw)[kGemmBPT], int (&tag)[kGemmBPT]) {
+            if (bc == 0) {
+                const int blk = act(ba);
+                src = s_src[blk][j];
+                up = blk0 + blk == kILSize;
+                col = (up ? de : ue) + (int64_t)max(src, 0) * a.n3 + k;
+            }
+            if (bc < cpb - 1) {                                    // all rows below n3
+#pragma unroll
+                for (int i = 0; i < kGemmBPT; ++i) {
+                    raw[i] = col[bc * kGemmKC + 8 * i];
+                    tag[i] = src >= 0;
+                }
+                ++bc;
+                return;
+            }
+#pragma unroll
+            for (int i = 0; i < kGemmBPT; ++i) {
+                const int kk = bc * kGemmKC + k + 8 * i;
+                const bool flux = kk == a.n3 && sig && !up;
+                tag[i] = src < 0 ? 0 : kk < a.n3 ? 1 : flux ? 2 : 0;
+                raw[i] = *(flux ? sig + max(src, 0) : col - k + min(kk, a.n3 - 1));
+            }
+            bc = 0;
+            ++ba;
+        };
+        auto valb = [&](double v, int tag, int) { return tag == 0 ? 0.0 : tag == 1 ? v : v * inv_h; };
+        double* part = g.vbuf + split * listed * mp;
+        const int r0 = rg * G::mw;
+        gemm_tile_any<RB>(g.A + (int64_t)c * kM2LBlocks * mp * mp, mp, r0, nact * cpb, rowa, fetchb, valb, busy,
+                          A0, A1, Bs, mp - r0, [&](int j, int row, double v) {
+                              if (col0 + j < c1) part[(col0 + j) * mp + r0 + row] = v;
+                          });
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {                                    // active blocks (relative to blk0), in order
-        int n = 0;
-        for (int k = 0; k < blk1 - blk0; ++k)
-            if (s_act[k]) s_act[n++] = k;
-        s_act[kM2LMaxSplitBlocks] = n;
-    }
-    __syncthreads();
-    const int nact = s_act[kM2LMaxSplitBlocks];
-    const int cpb = mp / kGemmKC;                              // chunks per K block (the plan has kb == mp)
-    const double inv_h = (double)(1 << l) / a.R;
-    auto chunk = [&](int64_t t) {
-        const int ti = (int)t;
-        return (int64_t)(blk0 + s_act[ti / cpb]) * cpb + ti % cpb;
-    };
-    auto busy = [&](int64_t t, int gq) { return s_grp[s_act[(int)t / cpb]][gq] != 0; };
-    auto loadb = [&](int64_t q, int j, int bk) -> double {
-        const int qi = (int)q, blk = qi / cpb, kk = (qi % cpb) * kGemmKC + bk;
-        const int32_t src = s_src[blk - blk0][j];
-        if (src < 0) return 0.0;
-        if (blk == kILSize) return kk < a.n3 ? a.de[(a.base[l - 1] + src) * a.n3 + kk] : 0.0;
-        const int64_t box = a.base[l] + src;
-        if (kk < a.n3) return a.ue[box * a.n3 + kk];
-        return (kk == a.n3 && a.sig) ? a.sig[box] * inv_h : 0.0;
-    };
-    const int64_t listed = *g.ctotal;
-    double* part = g.vbuf + split * listed * mp;
-    const int r0 = rg * G::mw;
-    gemm_tile_any<RB>(g.A + (int64_t)c * kM2LBlocks * mp * mp, mp, r0, (int64_t)nact * cpb, chunk, loadb, busy, As,
-                      Bs, mp - r0, [&](int j, int row, double v) {
-                          if (col0 + j < c1) part[(col0 + j) * mp + r0 + row] = v;
-                      });
 }
 
 // Dynamic LDS of the pair-sum M2L kernel, in doubles: the template, then one
@@ -1158,8 +1222,8 @@ template <int RB>
 __global__ __launch_bounds__(kGemmThreads) void apply_gemm_kernel(FmmDev a, Columns g, const double* __restrict__ op,
                                                                   double* __restrict__ out, double* __restrict__ part) {
     using G = GemmShape<RB>;
-    __shared__ double As[2 * G::na];
-    __shared__ double Bs[2 * kGemmKC * kGemmNT];
+    __shared__ alignas(16) double A0[G::na], A1[G::na];
+    __shared__ double Bs[2 * kGemmB];
     const int mp = a.mp, ng = gemm_groups(mp, RB);
     const int64_t n = *g.n, nk = mp / kGemmKC;
     const int64_t tiles = (n + kGemmNT - 1) / kGemmNT, S = apply_splits(tiles, nk);
@@ -1168,14 +1232,23 @@ __global__ __launch_bounds__(kGemmThreads) void apply_gemm_kernel(FmmDev a, Colu
     if (rg >= ng || u >= tiles * S) return;                       // uniform over the workgroup
     const int64_t col0 = (u / S) * kGemmNT, sp = u % S;
     const int64_t k0 = sp * nk / S, k1 = (sp + 1) * nk / S;
-    auto chunk = [k0](int64_t t) { return k0 + t; };
-    auto busy = [](int64_t, int) { return true; };
-    auto loadb = [&](int64_t q, int j, int bk) -> double {
-        return col0 + j < n ? a.vbuf[(col0 + j) * mp + q * kGemmKC + bk] : 0.0;
+    int ka = (int)k0 * kGemmKC, kb = ka;
+    auto rowa = [&]() { return (ka += kGemmKC) - kGemmKC; };
+    auto busy = [](int) { return true; };
+    auto fetchb = [&](int j, int k, double (&raw)[kGemmBPT], int (&tag)[kGemmBPT]) {
+        const bool in = col0 + j < n;
+        const double* v = a.vbuf + (col0 + (in ? j : 0)) * mp + kb + k;
+#pragma unroll
+        for (int i = 0; i < kGemmBPT; ++i) {
+            raw[i] = v[8 * i];
+            tag[i] = in;
+        }
+        kb += kGemmKC;
     };
+    auto valb = [](double v, int tag, int) { return tag ? v : 0.0; };
     const int32_t* list = g.list;
     const int r0 = rg * G::mw;
-    gemm_tile_any<RB>(op, mp, r0, k1 - k0, chunk, loadb, busy, As, Bs, a.n3 - r0, [&](int j, int row, double v) {
+    gemm_tile_any<RB>(op, mp, r0, (int)(k1 - k0), rowa, fetchb, valb, busy, A0, A1, Bs, a.n3 - r0, [&](int j, int row, double v) {
         if (col0 + j >= n) return;
         if (S == 1) out[(int64_t)list[col0 + j] * a.n3 + r0 + row] = v;
         else part[(sp * n + col0 + j) * a.n3 + r0 + row] = v;
@@ -1198,8 +1271,8 @@ __global__ __launch_bounds__(kGemmThreads) void apply_exact_kernel(FmmDev a, Col
                                                                    double* __restrict__ out,
                                                                    double* __restrict__ part) {
     using G = GemmShape<RB>;
-    __shared__ double As[2 * G::na];
-    __shared__ double Bs[2 * kGemmKC * kGemmNT];
+    __shared__ alignas(16) double A0[G::na], A1[G::na];
+    __shared__ double Bs[2 * kGemmB];
     __shared__ double s_c[kGemmNT];
     const int mp = a.mp, ng = gemm_groups(mp, RB);
     const int64_t n = *g.n, nk = mp / kGemmKC;
@@ -1220,19 +1293,28 @@ __global__ __launch_bounds__(kGemmThreads) void apply_exact_kernel(FmmDev a, Col
         if ((threadIdx.x & 7) == 0) s_c[j] = top > 0.0 && top < 1e280 ? ldexp(1.5, 52 + e - kExactBits) : 0.0;
     }
     __syncthreads();
-    auto busy = [](int64_t, int) { return true; };
-    auto loadb = [&](int64_t q, int j, int bk) -> double {
-        if (col0 + j >= n) return 0.0;
-        const int64_t set = q / nk;
-        const double v = a.vbuf[(col0 + j) * mp + (q - set * nk) * kGemmKC + bk];
+    auto busy = [](int) { return true; };
+    auto valb = [&](double v, int tag, int j) {
         const double v1 = (v + s_c[j]) - s_c[j];
-        return set == 0 ? v1 : set == 1 ? v - v1 : v;
+        return tag == 0 ? v1 : tag == 1 ? v - v1 : tag == 2 ? v : 0.0;
     };
     const int32_t* list = g.list;
     const int r0 = rg * G::mw;
     auto run = [&](int64_t k0, int64_t k1, bool add) {
-        auto chunk = [k0](int64_t t) { return k0 + t; };
-        gemm_tile_any<RB>(op3, mp, r0, k1 - k0, chunk, loadb, busy, As, Bs, a.n3 - r0, [&](int j, int row, double v) {
+        int ka = (int)k0, kb = ka;
+        auto rowa = [&]() { return ka++ * kGemmKC; };
+        auto fetchb = [&](int j, int k, double (&raw)[kGemmBPT], int (&tag)[kGemmBPT]) {
+            const int set = kb < (int)nk ? 0 : kb < 2 * (int)nk ? 1 : 2;   // of the stacked operands
+            const bool in = col0 + j < n;
+            const double* v = a.vbuf + (col0 + (in ? j : 0)) * mp + (kb - set * (int)nk) * kGemmKC + k;
+#pragma unroll
+            for (int i = 0; i < kGemmBPT; ++i) {
+                raw[i] = v[8 * i];
+                tag[i] = in ? set : 3;
+            }
+            ++kb;
+        };
+        gemm_tile_any<RB>(op3, mp, r0, (int)(k1 - k0), rowa, fetchb, valb, busy, A0, A1, Bs, a.n3 - r0, [&](int j, int row, double v) {
             if (col0 + j >= n) return;
             double* o = parts == 1 ? out + (int64_t)list[col0 + j] * a.n3 + r0 + row
                                    : part + (sp * n + col0 + j) * a.n3 + r0 + row;
@@ -1903,11 +1985,8 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
             hipLaunchKernelGGL(m2l_sched_kernel, dim3(1), dim3(kWave), 0, st, g2.cscan, g2.ctotal, l, g2.npairs, n_parts,
                                g2.sched);
             if (!chk()) break;
-            // per class at most min(8^(l-1), n_trg) boxes in `tiles` tiles; units per
-            // class = splits x tiles <= max(kM2LUnits + tiles, kM2LMinSplits x tiles)
-            const int64_t tiles = (std::min<int64_t>(boxes >> 3, in.n_trg) + kGemmNT - 1) / kGemmNT;
-            // row groups outermost: grid = 8 classes x row groups x units
-            const dim3 gm((unsigned)(8 * ngr * std::max<int64_t>(kM2LUnits + tiles, kM2LMinSplits * tiles)));
+            // classes x row groups x the CUs of an XCD; a workgroup's LDS fills a CU
+            const dim3 gm((unsigned)(8 * ngr * kM2LPerClass));
             if (!with_rb(rb, [&](auto r) {
                     hipLaunchKernelGGL(m2l_gemm_kernel<decltype(r)::value>, gm, dim3(kGemmThreads), 0, st, a, g2, l);
                 })) {
@@ -1921,8 +2000,8 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
             if (!chk()) break;
             with_T(T, [&](auto tc) {
                 hipLaunchKernelGGL(m2l_pairs_kernel<decltype(tc)::value>,
-                                   dim3(f_grid(std::min<int64_t>(boxes, in.n_trg))), dim3(kFBlock), m2l_lds(ns), st, a,
-                                   g2, l);
+                                   dim3(f_grid(std::min<int64_t>({boxes, in.n_trg, kM2LPairBlocks}))), dim3(kFBlock),
+                                   m2l_lds(ns), st, a, g2, l);
             });
             if (!chk()) break;
             if (!apply(l, Columns{g2.list, g2.ctotal}, plan->d_downA, a.de + L.base[l] * a.n3)) break;

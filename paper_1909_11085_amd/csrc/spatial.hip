@@ -36,6 +36,7 @@ constexpr int kSortItems = 8;                     // most keys per thread of a s
 constexpr int kSortTile = kSpBlock * kSortItems;  // most keys per sort workgroup
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kSpBlock * kScanItems;  // elements per scan workgroup
+constexpr int64_t kScanFold = 4096;
 constexpr int64_t kSpMaxGrid = 1 << 16;
 constexpr int kOriginBlocks = 64;                // workgroups of the origin reduction
 static_assert(kSpBlock == kRadix, "one digit per thread");
@@ -185,9 +186,13 @@ __global__ __launch_bounds__(kSpBlock) void cells_kernel(int32_t n, const double
     }
 }
 
-// Exclusive prefix sum of int64 values, in three kernels: per-workgroup sums,
-// a sequential scan of those sums (one thread), per-workgroup scans plus their
-// offsets.  Exact, so the order does not matter for the result.
+// Exclusive prefix sum of int64 values: per-workgroup sums, then per-workgroup
+// scans, each workgroup adding up the sums before it; one kernel where a single
+// workgroup holds all.  Beyond kScanFold workgroups (8.4e6 values), where those
+// additions would pass the scan itself, one thread turns the sums into offsets
+// between the two; for fewer that kernel is most of the time (16 scans of a
+// 2,088,960-point evaluation 357 us with it, 152 without).  Exact, so the order does
+// not matter for the result.
 __global__ __launch_bounds__(kSpBlock) void scan_sums_kernel(const int64_t* __restrict__ in, int64_t n,
                                                              int64_t* __restrict__ sums) {
     __shared__ int64_t red[kSpBlock];
@@ -217,10 +222,26 @@ __global__ void scan_top_kernel(int64_t* sums, int64_t nb, int64_t* total) {
     *total = acc;
 }
 
-__global__ __launch_bounds__(kSpBlock) void scan_final_kernel(const int64_t* __restrict__ in, int64_t n,
-                                                              const int64_t* __restrict__ sums,
-                                                              int64_t* __restrict__ out) {
+// sums: of the workgroups (fold), or their offsets; total (fold only): receives
+// the whole sum.  in and out may be one array.
+__global__ __launch_bounds__(kSpBlock) void scan_final_kernel(const int64_t* in, int64_t n,
+                                                              const int64_t* __restrict__ sums, int fold,
+                                                              int64_t* out, int64_t* total) {
     __shared__ int64_t pre[kSpBlock];
+    int64_t before = 0;
+    if (fold) {
+        for (int64_t b = threadIdx.x; b < blockIdx.x; b += kSpBlock) before += sums[b];
+        pre[threadIdx.x] = before;
+        __syncthreads();
+        for (int o = kSpBlock / 2; o > 0; o >>= 1) {
+            if ((int)threadIdx.x < o) pre[threadIdx.x] += pre[threadIdx.x + o];
+            __syncthreads();
+        }
+        before = pre[0];
+        __syncthreads();
+    } else {
+        before = sums[blockIdx.x];
+    }
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
     int64_t v[kScanItems];
     int64_t s = 0;
@@ -238,7 +259,8 @@ __global__ __launch_bounds__(kSpBlock) void scan_final_kernel(const int64_t* __r
         pre[threadIdx.x] += add;
         __syncthreads();
     }
-    int64_t acc = sums[blockIdx.x] + pre[threadIdx.x] - s;
+    int64_t acc = before + pre[threadIdx.x] - s;
+    if (fold && blockIdx.x == gridDim.x - 1 && threadIdx.x == kSpBlock - 1) *total = acc + s;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         const int64_t i = base + (int64_t)threadIdx.x * kScanItems + k;
@@ -251,12 +273,17 @@ __global__ __launch_bounds__(kSpBlock) void scan_final_kernel(const int64_t* __r
 hipError_t exclusive_scan(const int64_t* in, int64_t n, int64_t* out, int64_t* scan_tmp, int64_t* total,
                           hipStream_t st) {
     const int64_t nb = std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile);
-    hipLaunchKernelGGL(scan_sums_kernel, dim3((unsigned)nb), dim3(kSpBlock), 0, st, in, n, scan_tmp);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(kWave), 0, st, scan_tmp, nb, total);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_final_kernel, dim3((unsigned)nb), dim3(kSpBlock), 0, st, in, n, scan_tmp, out);
+    const int fold = nb <= kScanFold;
+    hipError_t e;
+    if (nb > 1) {
+        hipLaunchKernelGGL(scan_sums_kernel, dim3((unsigned)nb), dim3(kSpBlock), 0, st, in, n, scan_tmp);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (!fold) {
+        hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(kWave), 0, st, scan_tmp, nb, total);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(scan_final_kernel, dim3((unsigned)nb), dim3(kSpBlock), 0, st, in, n, scan_tmp, fold, out, total);
     return hipGetLastError();
 }
 

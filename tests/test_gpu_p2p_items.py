@@ -47,3 +47,24 @@ def test_item_edges(kernel, excl, groups):
     assert_close(host(got), ref, FP64_TOL, "sum")
     for name, a, b in zip("f src trg".split(), _gpu(d, 1.3, excl, kernel=kernel), _oracle(d, 1.3, excl, kernel=kernel)):
         assert_close(host(a), b, FP64_TOL, name)
+
+
+@pytest.mark.parametrize("n_leaves", [7, 2048, 2049, 4096 * 2048, 4096 * 2048 + 1])
+def test_many_leaves(n_leaves):
+    """The work items' prefix sum over one workgroup, several, and more than add
+    up the sums before them: a few full leaves among empty ones, every list
+    naming them all, so the result is the direct sum."""
+    rng = np.random.default_rng(n_leaves % 1009)
+    full = np.unique(np.clip([0, 1, 2046, 2047, 2048, n_leaves // 2, n_leaves - 2, n_leaves - 1], 0, n_leaves - 1))
+    size = np.zeros(n_leaves, dtype=np.int64)
+    size[full] = rng.integers(1, 90, full.size)
+    ofs = np.concatenate([[0], np.cumsum(size)]).astype(np.int64)
+    lists = np.zeros(n_leaves, dtype=np.int64)
+    lists[full] = full.size
+    uo = np.concatenate([[0], np.cumsum(lists)]).astype(np.int64)
+    ul = np.tile(full, full.size).astype(np.int32)
+    n = int(ofs[-1])
+    y, f, w = rng.uniform(-3, 3, (3, n)), rng.standard_normal((3, n)), rng.uniform(0.5, 1.0, n)
+    Y = dev(y)
+    got = S.p2p_leaf((dev(ofs), dev(ofs), dev(uo), dev(ul)), Y, dev(f), dev(w), Y)
+    assert_close(host(got), O.sl(y, f, w, y), FP64_TOL, f"{n_leaves} leaves")

@@ -54,11 +54,11 @@ struct stokes_fmm_plan {
     int mp = 0;                 // 3 ns padded to a multiple of 16
     double* d_khat = nullptr;   // spectra of the M2L kernels (fmm_fft.hip)
     double* d_tw = nullptr;     // and the transforms' twiddles
-    double* d_m2l = nullptr;    // (8 classes, kM2LBlocks, mp, mp), orders from kDenseOrderSL on; see m2l_matrix_kernel
+    double* d_m2l = nullptr;    // (8 classes, kM2LBlocks, mp, mp), orders from kDenseOrder on; see m2l_matrix_kernel
     int32_t* d_il = nullptr;    // (8 classes, kILSize, 3) interaction-list offsets
     double* d_downA = nullptr;  // (mp, mp): downA[k * mp + r] = DOWN[r][k], zero padded
     double* d_upA = nullptr;    // the same for UP
-    double* d_down3 = nullptr;  // (3 mp, mp): DOWN cut in two, for apply_exact_kernel (order kDenseOrderSL)
+    double* d_down3 = nullptr;  // (3 mp, mp): DOWN cut in two, for apply_exact_kernel (order kLeafConvOrderDL)
 };
 
 namespace stokes {
@@ -69,16 +69,20 @@ constexpr double kPinvRcond = 1e-10;
 constexpr int kFBlock = 256;
 constexpr int kFWaves = kFBlock / kWave;
 constexpr int64_t kFMaxGrid = 1 << 16;
-// M2L runs as lattice convolutions (fmm_fft.hip) below these orders, as dense
-// products (or pair sums) from them on.  The convolution is as accurate, but it
+// M2L runs as lattice convolutions (fmm_fft.hip) below this order, as dense
+// products (or pair sums) from it on.  The convolution is as accurate, but it
 // sums in another order, and the pseudo-inverses amplify the rounding of
-// whatever order is taken: two orders of the same sums give outputs that differ
-// by 2e-9 at order 6 for the single layer (changing the dense products' K splits
-// alone moves them by 1.6e-9), 7e-10 for the double layer, 1e-10 at order 5 and
-// 2e-12 at order 4, of outputs that are within 1e-4, 1e-3, 5e-4 and 2e-3 of the
-// direct sums.  Orders whose results it would move by more than 1e-9 keep the
-// dense products.
-constexpr int kDenseOrderSL = 6, kDenseOrderDL = 7;
+// whatever order is taken, each level of its own and of the levels above: two
+// orders of the same sums give outputs that differ by 2e-9 at order 6 for the
+// single layer (changing the dense products' K splits alone moves them by
+// 1.6e-9), 1e-10 at order 5 and 2e-12 at order 4, of outputs that are within
+// 1e-4, 5e-4 and 2e-3 of the direct sums.  Results move by less than 1e-9 so.
+// The double layer at order 6 takes the convolution at the leaves alone, with
+// the rounding of their pseudo-inverse product taken out: at all levels it moved
+// results by up to 1.07e-9 (114 walls of 2e4 to 1e6 nodes at 60 to 960 cells),
+// at the leaves by up to 9.8e-10 (200 of them, the worst sizes among them).
+// 1,048,576 nodes at 522,240 points: 15.1 ms without, 10.3 with, 7.5 at all levels.
+constexpr int kDenseOrder = 6, kLeafConvOrderDL = 6;
 
 unsigned f_grid(int64_t units) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(units, kFMaxGrid)); }
 
@@ -636,8 +640,8 @@ __global__ __launch_bounds__(kFBlock) void l2p_kernel(FmmDev a, const uint64_t* 
 int64_t max_list(int64_t n_trg, int64_t n_leaves) { return 27 * std::min(n_trg, n_leaves); }
 
 // ---------------------------------------------------------------------------
-// M2L as dense products on the FP64 matrix cores (the orders from kDenseOrderSL
-// and kDenseOrderDL on).
+// M2L as dense products on the FP64 matrix cores (the orders from kDenseOrder
+// on).
 //
 // A target box's position in its parent (octant class c = b & 7 of its
 // Morton index) fixes its interaction list: 189 offsets o (source box minus
@@ -1459,10 +1463,10 @@ FmmLayout fmm_layout(int order, int64_t n_src, int64_t n_trg, int D) {
     // check vectors: a column per box holding sources (upward) or targets (downward), and the
     // K-split partials of the dense levels: splits x listed boxes <= 3 listed + 64 (units + 8)
     const int64_t cols = std::min(L.n_leaves, std::max<int64_t>({n_src, n_trg, 1}));
-    const int64_t parts = order >= kDenseOrderSL ? kM2LMinSplits * cols + kGemmNT * (kM2LUnits + 8) : 0;
+    const int64_t parts = order >= kDenseOrder ? kM2LMinSplits * cols + kGemmNT * (kM2LUnits + 8) : 0;
     L.off_vbuf = take((size_t)std::max(cols, parts) * mp * 8);
     // split partials of the pseudo-inverse products: S x listed <= kApplyUnits x 64 columns when S > 1
-    L.off_apart = take((size_t)(order == kDenseOrderSL ? 3 : 1) * kApplyUnits * kGemmNT * 3 * ns * 8);
+    L.off_apart = take((size_t)(order == kLeafConvOrderDL ? 3 : 1) * kApplyUnits * kGemmNT * 3 * ns * 8);
     L.total = off;
     return L;
 }
@@ -1738,7 +1742,7 @@ int fmm_plan_build(int device, int order, stokes_fmm_plan** out, std::string& er
             upA[(size_t)k * mp + r] = up[(size_t)r * n3 + k];
         }
     hipError_t e = hipMalloc(&p->d_khat, fft_spectra_bytes(order));
-    if (order == kDenseOrderSL) {
+    if (order == kLeafConvOrderDL) {
         std::vector<double> down3((size_t)3 * mp * mp, 0.0);
         for (int r = 0; r < n3; ++r) {
             double top = 0.0;
@@ -1764,7 +1768,7 @@ int fmm_plan_build(int device, int order, stokes_fmm_plan** out, std::string& er
     if (e == hipSuccess) e = hipMemcpy(p->d_downA, downA.data(), downA.size() * 8, hipMemcpyHostToDevice);
     static_assert(kAlphaUE == kAlphaDC, "M2L is a convolution on one lattice");
     if (e == hipSuccess) e = fft_build_spectra(order, kAlphaUE, p->d_khat, p->d_tw, 0);
-    if (order >= kDenseOrderSL) {
+    if (order >= kDenseOrder) {
         const size_t ab = (size_t)8 * kM2LBlocks * mp * mp * 8;
         if (e == hipSuccess) e = hipMalloc(&p->d_m2l, ab);
         if (e == hipSuccess) e = hipMalloc(&p->d_il, il.size() * 4);
@@ -1945,7 +1949,6 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
         if (chk()) apply(l, c, plan->d_upA, a.ue + L.base[l] * a.n3);
     }
     // downward pass: interaction lists, then the parent's density, then the pseudo-inverse
-    const bool conv = plan->order < (dl ? kDenseOrderDL : kDenseOrderSL);
     M2LArgs g2{};
     g2.A = plan->d_m2l;
     g2.il = plan->d_il;
@@ -1968,6 +1971,7 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
     m.vbuf = a.vbuf;
     for (int l = 2; l <= D && chk(); ++l) {
         const int64_t boxes = (int64_t)1 << (3 * l);
+        const bool conv = plan->order < kDenseOrder || (dl && plan->order == kLeafConvOrderDL && l == D);
         if (!conv) {
             const unsigned gb = f_grid((boxes + kFBlock - 1) / kFBlock);
             int64_t* cflag = const_cast<int64_t*>(g2.cscan);

@@ -21,9 +21,9 @@
 //   fft_inverse_kernel    back to the check points
 //
 // Measured (all M2L kernels of one evaluation): order 4 on the 261,120 points of
-// 480 cells at depth 5, 1.11 ms of dense products before, 0.33 ms; order 6, the
-// double layer of 1,048,576 wall nodes at 522,240 points at depth 6, 12.3 ms of
-// pair sums before, 4.1 ms.
+// 480 cells at depth 5, 1.11 ms of dense products before, 0.33 ms; order 6, all
+// levels of the double layer of 1,048,576 wall nodes at 522,240 points at depth 6,
+// 12.3 ms of pair sums before, 4.1 ms.
 //
 // Spectra buffers hold a batch of kz planes; a level whose octets could be too
 // many for one batch runs several.  Every sum has a fixed order.

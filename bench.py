@@ -68,7 +68,7 @@ PEAK_TFLOPS = {"fp64": 78.6, "mixed": 157.3}
 FLOPS_PER_PAIR_SL = 29
 FLOPS_PER_PAIR_SL_SYM = 23
 FLOPS_PER_PAIR_DL = 30
-KERNEL_NAMES = {"fp64": "sym_main<FwdSL,T=6> (each pair once)", "mixed": "direct_mixed<SL,T=2>",
+KERNEL_NAMES = {"fp64": "sym_main<FwdSL> (each pair once)", "mixed": "direct_mixed<SL,T=2>",
                 "fp64_one_sided": "direct_f64<SL,T=4>"}
 PROFILE_TRAFFIC = {"fp64": "sym_main_f64_sl_cfg2_traffic.txt", "mixed": "direct_mixed_sl_cfg2_traffic.txt",
                    "fp64_one_sided": "direct_f64_sl_cfg2_traffic.txt",
@@ -469,7 +469,7 @@ def bench_cfg4(S, W, t, timed, steps, oracle, one_sided=False):
                                                  precision=prec, group_h=gh), steps, 2)
         r[prec] = {"ms_per_step": ms, "pairs_per_s": pairs / (ms * 1e-3), "plan_ms_per_step": ms_plan,
                    "roofline": dict(_roofline(prec, pairs * FLOPS_PER_PAIR_SL, km,
-                                              "p2p_sum<SL,%s>" % ("FP64" if prec == "fp64" else "mixed")),
+                                              "p2p_sum64<SL>" if prec == "fp64" else "p2p_sum_mixed<SL>"),
                                     flops_per_pair=FLOPS_PER_PAIR_SL, traffic=traffic_from_profile("p2p_" + prec))}
     r["mixed_speedup_vs_fp64"] = r["fp64"]["ms_per_step"] / r["mixed"]["ms_per_step"]
     if oracle:
@@ -604,7 +604,7 @@ def time_checkpoint(S, W, t, timed, steps, warmup, oracle=True):
     pairs = n_fine * n_check
     X, F = t(wall.pos), t(phi)
     r = {"targets": wall.n, "fine_sources": n_fine, "check_points": n_check, "pairs": pairs,
-         "eta": eta, "p": p, "R_over_L": R, "r_over_L": R, "kernel": "direct_f64<DL,T=4> / direct_mixed<DL>",
+         "eta": eta, "p": p, "R_over_L": R, "r_over_L": R, "kernel": "direct_f64<DL,T=8> / direct_mixed<DL>",
          "flops_per_pair": FLOPS_PER_PAIR_DL}
     outs = {}
     for prec in ("fp64", "mixed"):

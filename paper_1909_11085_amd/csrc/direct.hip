@@ -699,7 +699,7 @@ int direct_blocks_per_cu(int kernel, int mixed) {
 
 // Targets per lane.  A long double-layer sum runs at the clock that the power
 // limit leaves it, and half the LDS reads per pair raise that: 294,912 wall nodes
-// at 65,297 targets 27.9 ms with 4, 27.1 with 8; 32,768 at 30,720 811 and 801 us.
+// at 115,217 targets 27.9 ms with 4, 27.1 with 8; 32,768 at 30,720 811 and 801 us.
 // Below about 9e8 pairs the waves in flight count for more (16,384 at 30,720 414
 // and 428 us), and so does more padding of the last target block than the
 // difference (32,768 at 15,360 414 and 433).

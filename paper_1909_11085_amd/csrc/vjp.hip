@@ -16,7 +16,9 @@
 //     dL/dy_m   = -d sum_n G(r_nm)              (G even)
 // Source-side gradients are transposed passes: the forward's sources act as
 // targets and its targets (carrying g) as sources; when only the density
-// gradient is asked for, a lighter pass skips the position terms.  For a shared point set
+// gradient is asked for, a lighter pass skips the position terms.  The double
+// layer's target side together with any of its source side is one sweep over the
+// pairs (dl_both_main).  For a shared point set
 // with one combined position gradient, a single fused pass gives
 // dL/dx_p = c sum_m [K(r_pm; g_p, q_m) + K(r_pm; q_p, g_m)] and dL/df_p.
 #include <algorithm>

@@ -208,7 +208,7 @@ stokes::SumInputs make_inputs(int kernel, const Parsed& p, int64_t n_src, const 
 // workgroup count asks for the kernels that it cuts).
 bool small_sum(const stokes_ctx* ctx, const stokes::SumInputs& in) {
     return in.n_src > 0 && in.n_trg > 0 && ctx->forced_grid == 0 &&
-           stokes::direct_is_small(in.kernel, in.mixed, in.n_src, in.n_trg);
+           stokes::direct_is_small(in.mixed, in.n_src, in.n_trg);
 }
 
 hipError_t run_direct(stokes_ctx* ctx, const stokes::SumInputs& in, const stokes::DirectPlan& plan, double* out,

@@ -118,7 +118,7 @@ hipError_t launch_direct(const SumInputs& in, const DirectPlan& p, double* out, 
 
 // Whether a float64 sum of these sizes runs as one kernel, and that kernel
 // (n_src, n_trg > 0; no workspace).
-bool direct_is_small(int kernel, int mixed, int64_t n_src, int64_t n_trg);
+bool direct_is_small(int mixed, int64_t n_src, int64_t n_trg);
 hipError_t launch_direct_small(const SumInputs& in, double* out, int accumulate, int n_cu, hipStream_t stream,
                                const KernelTimer& timer);
 

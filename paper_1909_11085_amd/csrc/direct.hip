@@ -521,11 +521,13 @@ __global__ __launch_bounds__(kBlock) void reduce_segments(const double* __restri
 // ---------------------------------------------------------------------------
 // The whole float64 sum of a small call in one launch, straight from the
 // caller's arrays.  Such a call is bound by latency, not by its pairs: the
-// kernels above are four dependent launches, and a few target blocks leave
-// most of the chip idle (4,352 points: 92 us there, 41 us here, of which the
-// 1.9e7 pairs need 13 at the rate of a full chip).  Here a workgroup owns TW targets and the 256 / TW
-// threads of a target share the sources, 256 staged at a time; every pair
-// carries the masks.  A target's partial sums are added in a fixed order.
+// kernels above are three dependent launches, and a few target blocks leave
+// most of the chip idle (4,352 points: 51 us there, 44 us here, of which the
+// 1.9e7 pairs need 13 at the rate of a full chip; 1,088 points 36 and 18).  Here a
+// workgroup owns TW targets and the 256 / TW threads of a target share the
+// sources, 256 staged at a time; every pair carries the masks.  The last tile
+// has no steps of padding alone (64 sources at 400,000 targets: 107 us with them,
+// 39 without).  A target's partial sums are added in a fixed order.
 template <int KT, int TW>
 __global__ __launch_bounds__(kBlock) void direct_small(SumInputs in, double pref, double* __restrict__ out,
                                                        int accumulate) {
@@ -538,7 +540,7 @@ __global__ __launch_bounds__(kBlock) void direct_small(SumInputs in, double pref
     const bool excl = in.excl != 0;
     const int32_t tg = in.trg_group ? in.trg_group[ic] : 0;
     double u[3] = {0.0, 0.0, 0.0};
-    for (int64_t b = 0; b < n; b += kBlock) {
+    auto tile = [&](int64_t b, auto whole) {
         const int64_t m = b + tid;
         double v[NC];
 #pragma unroll
@@ -559,9 +561,7 @@ __global__ __launch_bounds__(kBlock) void direct_small(SumInputs in, double pref
         for (int c = 0; c < NC; ++c) s_src[c][tid] = v[c];
         s_grp[tid] = g;
         __syncthreads();
-#pragma unroll 4
-        for (int k = 0; k < TW; ++k) {
-            const int j = k * H + h;
+        auto pair = [&](int j) {
             typename SrcRec<KT, 0>::type r;
             r.x = s_src[0][j]; r.y = s_src[1][j]; r.z = s_src[2][j];
             r.qx = s_src[3][j]; r.qy = s_src[4][j]; r.qz = s_src[5][j];
@@ -571,8 +571,17 @@ __global__ __launch_bounds__(kBlock) void direct_small(SumInputs in, double pref
                 r.nx = s_src[6][j]; r.ny = s_src[7][j]; r.nz = s_src[8][j];
             }
             pair_f64<KT, true>(r, x, y, z, excl && s_grp[j] == tg, u[0], u[1], u[2]);
+        };
+        if constexpr (decltype(whole)::value) {
+#pragma unroll 4
+            for (int k = 0; k < TW; ++k) pair(k * H + h);
+        } else {                               // no steps of padding alone
+            for (int k = 0; k * H < n - b; ++k) pair(k * H + h);
         }
-    }
+    };
+    int64_t b = 0;
+    for (; n - b >= kBlock; b += kBlock) tile(b, std::true_type{});
+    if (b < n) tile(b, std::false_type{});
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < 3; ++c) s_src[c][tid] = u[c];
@@ -628,16 +637,19 @@ static void launch_small_kt(const SumInputs& in, double* out, int accumulate, in
     }
 }
 
-// The line lies where the four-kernel path (the each-pair-once one on shared
-// sets) catches up, measured on cells, tracers and walls (this kernel / that
-// path): single layer 544 x 544 19 / 73 us, 4,352 x 4,352 41 / 92, 6,528 x 6,528
-// 82 / 138, 8,704 x 8,704 126 / 155, 13,056 x 13,056 263 / 278, 34,816 x 1,001
-// 112 / 576; double layer 2,048 x 2,193 19 / 75, 2,048 x 16,337 49 / 120, 10,368 x
-// 4,369 106 / 97, 32,768 x 2,193 204 / 167.  Mixed sums keep their sub-tiles'
-// float32 partial sums and stay on the other path.
-bool direct_is_small(int kernel, int mixed, int64_t n_src, int64_t n_trg) {
-    constexpr int64_t kPairsSL = 60'000'000, kPairsDL = 34'000'000;
-    return !mixed && n_src <= (kernel == 0 ? kPairsSL : kPairsDL) / n_trg;
+// The line lies where the other path (the each-pair-once one on shared sets)
+// catches up, measured on cells, tracers and walls (this kernel / that path, us).
+// A workgroup walks all sources 256 at a time, 0.6 us a tile, however few targets
+// there are: 1 target at 13,056 sources 36 / 37, at 26,112 67 / 52, at 984,064 3,120 /
+// 359.  Up to there pairs count: 8,704 x 2,000 45 / 56, x 4,001 74 / 66, 4,400 x 8,001 69 / 63,
+// shared 5,440 64 / 63 and 6,528 98 / 64.  Few tiles are staged so seldom that it keeps
+// up longer: 600 x 128,001 92 / 111, 128 x 1,000,000 142 / 147, 1,100 x 128,001 160 / 157.  The
+// double layer lies within 5% of these.  Mixed sums keep their sub-tiles' float32
+// partial sums and stay on the other path.
+bool direct_is_small(int mixed, int64_t n_src, int64_t n_trg) {
+    constexpr int64_t kTiles = 72, kPairs = 26'000'000, kFewTiles = 5, kPairsFewTiles = 120'000'000;
+    const int64_t tiles = ceil_div(n_src, (int64_t)kBlock);
+    return !mixed && tiles <= kTiles && n_src <= (tiles <= kFewTiles ? kPairsFewTiles : kPairs) / n_trg;
 }
 
 hipError_t launch_direct_small(const SumInputs& in, double* out, int accumulate, int n_cu, hipStream_t stream,
@@ -744,7 +756,7 @@ DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int 
     // workgroups where the partial sums would not fit; the first two also for the
     // small calls that run as one kernel
     const int64_t whole = std::min(g, p.units / (kTile / kSub));
-    if ((max_bytes > 0 && p.total > max_bytes) || direct_is_small(kernel, mixed, n_src, n_trg))
+    if ((max_bytes > 0 && p.total > max_bytes) || direct_is_small(mixed, n_src, n_trg))
         partials(whole, mixed ? kNearSlices : 0);
     if (max_bytes > 0 && p.total > max_bytes) partials(std::min(whole, std::max<int64_t>(1, g / 2)), mixed ? kNearSlices : 0);
     return p;

@@ -85,7 +85,7 @@ constexpr int32_t kPairSkip = 1 << 16; // excluded: same group, or zero distance
 struct DirectPlan {
     int T;                       // targets per lane
     int64_t n_src_pad;           // sources padded to kTile
-    int64_t n_sub;               // n_src_pad / kSub
+    int64_t n_sub;               // 64-source sub-tiles of a target block (all of n_src_pad where cut > 1)
     int64_t blocks_x;            // target blocks of kBlock * T targets
     int64_t units;               // blocks_x * n_sub
     int64_t grid;                // workgroups (resident count, at most units)

@@ -47,7 +47,7 @@ struct DirectArgs {
     const void* rec;          // packed source records
     const void* aux;          // FP64 path: padded int32 groups; mixed: float4 low parts
     const SubMeta* meta;
-    int64_t n_sub;            // source sub-tiles (a multiple of 4)
+    int64_t n_sub;            // source sub-tiles
     int64_t units;            // target blocks x sub-tiles
     int cut;                  // ranges begin at multiples of this many units
     double* part;             // partial sums, one segment per (block, target block) pair
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kBlock, T == kT64Long ? kW64Long : STOKES_DIRECT_W6
 
     int64_t ub = u0 / C, sub = u0 % C;         // unit position, advanced by up to four sub-tiles
     for (int64_t u = u0; u < u1;) {
-        const int s0 = (int)(sub & 3), s1 = (int)min((int64_t)4, s0 + (u1 - u));
+        const int s0 = (int)(sub & 3), s1 = (int)min((int64_t)4, s0 + min(u1 - u, C - sub));
         __syncthreads();                       // previous step's readers are done
         if (ub != tbk) {
             if (tbk >= 0) flush_segment<T>(a, tbk, wave, lane, ax, ay, az);
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kBlock, KT == 0 ? STOKES_DIRECT_W32SL : STOKES_DIRE
     int64_t ub = u0 / C, sub = u0 % C;
     Rec pre = rec[(sub & ~(int64_t)3) * kSub + threadIdx.x];
     for (int64_t u = u0; u < u1;) {
-        const int s0 = (int)(sub & 3), s1 = (int)min((int64_t)4, s0 + (u1 - u));
+        const int s0 = (int)(sub & 3), s1 = (int)min((int64_t)4, s0 + min(u1 - u, C - sub));
         const int64_t first = sub - s0;        // the chunk's first sub-tile
         __syncthreads();
         if (ub != tbk) {
@@ -471,19 +471,19 @@ __global__ __launch_bounds__(kBlock) void direct_near_mixed(DirectArgs a) {
 // ---------------------------------------------------------------------------
 // out[c][i] (=|+=) pref * (sum of target i's segments in workgroup order and of
 // its near-pass sums).  A call with few target blocks has many of both per
-// target (4,352 targets: about 150 segments and 64 near rows), so kRedParts
-// threads share a target, each taking a contiguous share, and the shares are
-// added in order.
+// target (4,352 targets: about 150 segments and 64 near rows), so there P =
+// kRedParts threads share a target, each taking a contiguous share, and the shares
+// are added in order; with few (see launch_typed) one thread takes them all.
 constexpr int kRedParts = 8;
-template <int T>
+template <int T, int P>
 __global__ __launch_bounds__(kBlock) void reduce_segments(const double* __restrict__ part,
                                                           const double* __restrict__ near_part,
                                                           int64_t n_trg, int64_t units,
                                                           int64_t n_sub, int64_t grid, int cut, int slices,
                                                           int64_t np, double pref, double* out,
                                                           int accumulate) {
-    constexpr int BT = kBlock * T, kTrg = kBlock / kRedParts;
-    __shared__ double s_sum[kRedParts][3][kTrg];
+    constexpr int BT = kBlock * T, kTrg = kBlock / P;
+    __shared__ double s_sum[P][3][kTrg];
     const int t = threadIdx.x % kTrg, q = threadIdx.x / kTrg;
     const int64_t i = (int64_t)blockIdx.x * kTrg + t;
     double s[3] = {0.0, 0.0, 0.0};
@@ -491,28 +491,37 @@ __global__ __launch_bounds__(kBlock) void reduce_segments(const double* __restri
         const int64_t tbk = i / BT, li = i % BT;
         const int64_t b0 = range_owner(tbk * n_sub, units, grid, cut);
         const int64_t b1 = range_owner((tbk + 1) * n_sub - 1, units, grid, cut) + 1;
-        const int64_t e0 = b0 + (b1 - b0) * q / kRedParts, e1 = b0 + (b1 - b0) * (q + 1) / kRedParts;
+        const int64_t e0 = b0 + (b1 - b0) * q / P, e1 = b0 + (b1 - b0) * (q + 1) / P;
 #pragma unroll 4
         for (int64_t b = e0; b < e1; ++b) {
             const double* seg = part + (b + tbk) * 3 * BT;
 #pragma unroll
             for (int c = 0; c < 3; ++c) s[c] += seg[c * BT + li];
         }
-        const int l0 = slices * q / kRedParts, l1 = slices * (q + 1) / kRedParts;
+        const int l0 = slices * q / P, l1 = slices * (q + 1) / P;
 #pragma unroll 4
         for (int sl = l0; sl < l1; ++sl)
 #pragma unroll
             for (int c = 0; c < 3; ++c) s[c] += near_part[(sl * 3 + c) * np + i];
     }
+    if constexpr (P == 1) {
+        if (i < n_trg)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) s_sum[q][c][t] = s[c];
-    __syncthreads();
-    if (q < 3 && i < n_trg) {
-        double v = s_sum[0][q][t];
+            for (int c = 0; c < 3; ++c) {
+                const int64_t o = c * n_trg + i;
+                out[o] = accumulate ? out[o] + pref * s[c] : pref * s[c];
+            }
+    } else {
 #pragma unroll
-        for (int p = 1; p < kRedParts; ++p) v += s_sum[p][q][t];
-        const int64_t o = q * n_trg + i;
-        out[o] = accumulate ? out[o] + pref * v : pref * v;
+        for (int c = 0; c < 3; ++c) s_sum[q][c][t] = s[c];
+        __syncthreads();
+        if (q < 3 && i < n_trg) {
+            double v = s_sum[0][q][t];
+#pragma unroll
+            for (int p = 1; p < P; ++p) v += s_sum[p][q][t];
+            const int64_t o = q * n_trg + i;
+            out[o] = accumulate ? out[o] + pref * v : pref * v;
+        }
     }
 }
 
@@ -730,9 +739,8 @@ DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int 
     DirectPlan p{};
     p.T = targets_per_lane(kernel, mixed, n_src, n_trg);
     p.n_src_pad = ceil_div(n_src, kTile) * kTile;
-    p.n_sub = p.n_src_pad / kSub;
     p.blocks_x = ceil_div(n_trg, (int64_t)kBlock * p.T);
-    p.units = p.n_sub * p.blocks_x;
+    const int64_t subs = ceil_div(n_src, (int64_t)kSub), chunks = p.n_src_pad / kTile;
     const size_t bt = (size_t)kBlock * p.T;
     size_t off = 0;
     p.off_src = off;
@@ -740,25 +748,32 @@ DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int 
     p.off_grp = off;
     off = align_up(off + (size_t)p.n_src_pad * (mixed ? sizeof(float4) : sizeof(int32_t)), 256);
     p.off_meta = off;
-    off = align_up(off + (size_t)p.n_sub * sizeof(SubMeta), 256);
+    off = align_up(off + (size_t)(p.n_src_pad / kSub) * sizeof(SubMeta), 256);
     p.off_part = off;
     int64_t g = forced_grid > 0 ? forced_grid : std::max(1, resident_blocks);
     if (forced_grid <= 0 && p.T == kT64Long) g = std::max<int64_t>(1, g * kW64Long / STOKES_DIRECT_W64);
+    // Units are the sub-tiles that hold sources, not those that pad the last chunk:
+    // with 64 sources those were three of four workgroups and of four partial sums a
+    // target (64 x 1,000,000 mixed 164 us with them, 122 without).  Ranges of whole
+    // chunks keep them, as they begin at multiples of four.
     auto partials = [&](int64_t workgroups, int slices) {
         p.grid = std::max<int64_t>(1, workgroups);
         p.near_slices = slices;
-        p.cut = p.units / (kTile / kSub) >= kWholeChunks * p.grid ? kTile / kSub : 1;
+        p.cut = chunks * p.blocks_x >= kWholeChunks * p.grid ? kTile / kSub : 1;
+        p.n_sub = p.cut > 1 ? p.n_src_pad / kSub : subs;
+        p.units = p.n_sub * p.blocks_x;
         p.off_near = align_up(p.off_part + (size_t)(p.grid + p.blocks_x) * 3 * bt * sizeof(double), 256);
         p.total = align_up(p.off_near + (size_t)slices * p.blocks_x * 3 * bt * sizeof(double), 256);
     };
-    partials(std::min(g, p.units), mixed ? near_slices(p.blocks_x, p.n_sub) : 0);
+    partials(std::min(g, subs * p.blocks_x), mixed ? near_slices(p.blocks_x, subs) : 0);
     // few near-pass rows, no more workgroups than 256-source chunks, and half the
     // workgroups where the partial sums would not fit; the first two also for the
     // small calls that run as one kernel
-    const int64_t whole = std::min(g, p.units / (kTile / kSub));
+    const int64_t whole = std::min(g, chunks * p.blocks_x);
+    const int rows = mixed ? (int)std::min<int64_t>(kNearSlices, subs) : 0;
     if ((max_bytes > 0 && p.total > max_bytes) || direct_is_small(mixed, n_src, n_trg))
-        partials(whole, mixed ? kNearSlices : 0);
-    if (max_bytes > 0 && p.total > max_bytes) partials(std::min(whole, std::max<int64_t>(1, g / 2)), mixed ? kNearSlices : 0);
+        partials(whole, rows);
+    if (max_bytes > 0 && p.total > max_bytes) partials(std::min(whole, std::max<int64_t>(1, g / 2)), rows);
     return p;
 }
 
@@ -819,9 +834,16 @@ static hipError_t launch_typed(const SumInputs& in, const DirectPlan& p, double*
     }
     // FP64 pair sums are 4x (single layer) or 8x (double layer) the bare sums
     const double pref = MIXED ? in.pref : (KT == 0 ? 0.25 : 0.125) * in.pref;
-    reduce_segments<T><<<dim3((unsigned)ceil_div(in.n_trg, kBlock / kRedParts)), dim3(kBlock), 0, stream>>>(
-        a.part, a.near_part, in.n_trg, p.units, p.n_sub, p.grid, p.cut, p.near_slices,
-        p.blocks_x * (int64_t)kBlock * T, pref, out, accumulate);
+    auto reduce = [&](auto parts) {
+        constexpr int P = decltype(parts)::value;
+        reduce_segments<T, P><<<dim3((unsigned)ceil_div(in.n_trg, kBlock / P)), dim3(kBlock), 0, stream>>>(
+            a.part, a.near_part, in.n_trg, p.units, p.n_sub, p.grid, p.cut, p.near_slices,
+            p.blocks_x * (int64_t)kBlock * T, pref, out, accumulate);
+    };
+    // threads that share a target pay from about two partial sums each on (400,000 targets
+    // with 4 or 5: 20 us shared, 10 alone)
+    if (p.grid + p.near_slices * p.blocks_x < 2 * kRedParts * p.blocks_x) reduce(std::integral_constant<int, 1>{});
+    else reduce(std::integral_constant<int, kRedParts>{});
     return hipGetLastError();
 }
 

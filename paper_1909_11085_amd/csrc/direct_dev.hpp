@@ -257,12 +257,13 @@ __device__ __forceinline__ void for_each_near(const Box& w, const Targets<T>& t,
 // the cells) have many: 8,001 tracers at 34,816 sources 0.64 ms with 4 rows, 0.23
 // with up to 64.  A row repeats the box tests, so past two workgroups per CU it
 // has four sub-tiles at least (19,602 targets at 3,267 sources: 135 us with 27
-// rows, 126 with 14; 4,096 points 62 us with 16, 55 with 64).
+// rows, 126 with 14; 4,096 points 62 us with 16, 55 with 64), and there are no more
+// rows than sub-tiles.
 constexpr int kNearSlices = 4, kNearSlicesMax = 64, kNearBlocks = 1024, kNearSubs = 4;
 inline int near_slices(int64_t blocks_x, int64_t n_sub) {
     const int64_t most = std::max(n_sub / kNearSubs, ceil_div(kNearBlocks / 2, blocks_x));
     const int64_t rows = std::min<int64_t>(std::min<int64_t>(kNearSlicesMax, most), ceil_div(kNearBlocks, blocks_x));
-    return (int)std::max<int64_t>(kNearSlices, rows);
+    return (int)std::min(n_sub, std::max<int64_t>(kNearSlices, rows));
 }
 
 // ---------------------------------------------------------------------------

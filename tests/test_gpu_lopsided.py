@@ -3,7 +3,9 @@ sources, a few sources at very many targets.
 
 Values: against the FP64 oracle at the edges of the one-kernel path's rule (72
 tiles of 256 sources; 1.2e8 pairs up to 5 tiles, 2.6e7 beyond) and of its last
-tile.  Tolerance: FP64_TOL, the float64 bar of every direct sum.
+tile.  Tolerance: FP64_TOL, the float64 bar of every direct sum (MIXED_TOL in mixed precision).
+
+Workspace: partial sums are for sub-tiles that hold sources.
 
 Times: a call's own choice of kernels may take at most 1.5 times as long as the
 kernels that cut the sources over the whole chip (a forced workgroup count keeps
@@ -11,13 +13,16 @@ a call on those), each the best of several runs.  One workgroup per target
 walking all sources took 8 times as long, padding every few sources to a full
 tile twice.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import paper_1909_11085_amd as S
+from paper_1909_11085_amd import _capi as C
 from oracle import oracle as O
-from tests.gpu_util import FP64_TOL, assert_close, dev, device, host
+from tests.gpu_util import FP64_TOL, MIXED_TOL, assert_close, dev, device, host
 
 pytestmark = pytest.mark.gpu
 
@@ -74,3 +79,29 @@ def test_no_slower_than_the_split_sum(kernel, ns, nt):
         S.set_grid_override(0)
     print(f"{kernel} {ns} x {nt}: {own:.3f} ms, split {split:.3f} ms", flush=True)
     assert own <= 1.5 * split, (own, split)
+
+
+@pytest.mark.parametrize("op", [C.OP_SL, C.OP_DL])
+def test_no_partial_sums_of_padding(op):
+    """Mixed sums: 64 sources are one sub-tile of 64, 256 are four, and both have one
+    record array of 256; what is left of the workspace is partial sums."""
+    size, opts, nt = ctypes.c_size_t(), C.Opts(C.MIXED, 0), 65_536
+    bytes_of = []
+    for ns in (64, 256):
+        assert C.lib().stokes_workspace_size(S.context(device()), op, ns, nt, 0, 0, ctypes.byref(opts),
+                                             ctypes.byref(size)) == C.OK
+        bytes_of.append(size.value)
+    assert bytes_of[0] <= 0.5 * bytes_of[1], bytes_of
+
+
+@pytest.mark.parametrize("kernel", ["sl", "dl"])
+@pytest.mark.parametrize("ns,nt", [(1, 3000), (64, 70_000), (65, 513), (193, 9000), (1537, 1025)])
+def test_mixed_values(kernel, ns, nt):
+    y, f, w, nv, x = _case(ns, ns, nt)
+    g, h = np.zeros(ns, np.int32), np.full(1, 0.2)
+    kw = dict(src_group=dev(g), exclude_same_group=False, precision="mixed", group_h=dev(h))
+    if kernel == "sl":
+        got, ref = S.sl(dev(y), dev(f), dev(w), dev(x), **kw), O.sl(y, f, w, x)
+    else:
+        got, ref = S.dl(dev(y), dev(f), dev(w), dev(nv), dev(x), **kw), O.dl(y, f, w, nv, x)
+    assert_close(host(got), ref, MIXED_TOL, f"{kernel} {ns} x {nt}")

@@ -358,13 +358,20 @@ __global__ __launch_bounds__(kBlock, KT == 0 ? STOKES_DIRECT_W32SL : STOKES_DIRE
     flush_segment<T>(a, tbk, wave, lane, ax, ay, az);
 }
 
+// Sub-tiles up to which the near pass notes near pairs in its float32 loop: a wave's
+// targets spread over few clusters then, and most sub-tiles have some.  With a second
+// pass where there are any / noted in the loop, whole calls of cells among 120,001
+// tracers: 9 sub-tiles 123 / 108 us, 18 178 / 157, 34 260 / 267; 64 cells (544) among 8,001 234 / 243.
+constexpr int kFewSubs = 24;
+
 // Near pass (mixed): the skipped sub-tiles with r from high + low float32 parts,
-// the same-group mask, and pairs inside the near radius in float64.  CNT:
+// the same-group mask, and pairs inside the near radius in float64.  FEW: see
+// kFewSubs.  CNT:
 // also record each pair's class (test-only instantiation).
-template <int KT, int T, bool CNT = false>
+template <int KT, int T, bool FEW, bool CNT = false>
 __global__ __launch_bounds__(kBlock) void direct_near_mixed(DirectArgs a) {
     using Rec = typename SrcRec<KT, 1>::type;
-    constexpr int BT = kBlock * T;
+    constexpr int BT = kBlock * T, kLoop = FEW ? 32 : kSub;
     // each wave stages its current sub-tile in its own slice (read back by
     // broadcast into VGPRs; only that wave touches it, and a wave's LDS
     // operations complete in order, so no workgroup barrier is needed)
@@ -406,46 +413,69 @@ __global__ __launch_bounds__(kBlock) void direct_near_mixed(DirectArgs a) {
             dz = (zs[k] - sr.oz) + (zl[k] - sl.z);
             return __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
         };
-        bool any = false;                      // a near pair of this lane, left to the second loop
-#pragma unroll 2
-        for (int j = 0; j < kSub; ++j) {
-            const Rec sr = s_src[wave][j];
-            const float4 sl = s_res[wave][j];
+        // The float64 pairs come after the float32 loop, which so has no branches: a
+        // lane notes its own as bits, and the lanes take theirs side by side,
+        // whatever the sources (a branch per source ran them one source after
+        // another: 576 sources at 120,001 tracers 81 us here, 64 so).  FEW notes
+        // them in the loop, 32 sources at a time; else a second pass over the
+        // offsets does, where any lane has one.
+        auto take = [&](uint32_t (&set)[T], int j0) {
 #pragma unroll
-            for (int k = 0; k < T; ++k) {
-                float dx, dy, dz;
-                const float r2 = offset(sr, sl, k, dx, dy, dz);
-                const bool excluded = excl && sr.g == t.g[k];
-                const bool near = r2 <= sr.t2;
-                any |= near && !excluded;
-                pair_f32<KT>(sr, dx, dy, dz, excluded || near, true, bx[k], by[k], bz[k]);
-                if constexpr (CNT) {
-                    const int64_t si = sub * kSub + j, ti = tb + k * kWave + lane;
-                    if (si < a.in.n_src && ti < a.in.n_trg) {
-                        // near_pair_f64 takes nothing at zero distance (float64)
-                        const int64_t ns = a.in.n_src;
-                        const bool zero = t.x[k] == a.in.src_xyz[si] && t.y[k] == a.in.src_xyz[ns + si] &&
-                                          t.z[k] == a.in.src_xyz[2 * ns + si];
-                        const int32_t cls = excluded ? kPairSkip : !near ? kPairF32 : zero ? kPairSkip : kPairF64;
-                        atomicAdd(a.in.pair_class + ti * ns + si, cls);
-                    }
-                }
-            }
-        }
-        // the float64 pairs apart, so that the loop above has no branches; most
-        // sub-tiles here have none (they are within an eighth of their extent)
-        if (__ballot(any) != 0) {
+            for (int k = 0; k < T; ++k)
+                for (; set[k] != 0; set[k] &= set[k] - 1)
+                    near_pair_f64<KT>(a.in, sub * kSub + j0 + __builtin_ctz(set[k]), t.x[k], t.y[k], t.z[k], ax[k],
+                                      ay[k], az[k]);
+        };
+        bool any = false;
 #pragma unroll 1
-            for (int j = 0; j < kSub; ++j) {
-                const Rec sr = s_src[wave][j];
-                const float4 sl = s_res[wave][j];
+        for (int j0 = 0; j0 < kSub; j0 += kLoop) {
+            uint32_t set[T] = {};
+#pragma unroll 2
+            for (int j = 0; j < kLoop; ++j) {
+                const Rec sr = s_src[wave][j0 + j];
+                const float4 sl = s_res[wave][j0 + j];
 #pragma unroll
                 for (int k = 0; k < T; ++k) {
                     float dx, dy, dz;
-                    if (offset(sr, sl, k, dx, dy, dz) <= sr.t2 && !(excl && sr.g == t.g[k]))
-                        near_pair_f64<KT>(a.in, sub * kSub + j, t.x[k], t.y[k], t.z[k], ax[k], ay[k], az[k]);
+                    const float r2 = offset(sr, sl, k, dx, dy, dz);
+                    const bool excluded = excl && sr.g == t.g[k];
+                    const bool near = r2 <= sr.t2;
+                    if constexpr (FEW) set[k] |= (uint32_t)(near && !excluded) << j;
+                    else any |= near && !excluded;
+                    pair_f32<KT>(sr, dx, dy, dz, excluded || near, true, bx[k], by[k], bz[k]);
+                    if constexpr (CNT) {
+                        const int64_t si = sub * kSub + j0 + j, ti = tb + k * kWave + lane;
+                        if (si < a.in.n_src && ti < a.in.n_trg) {
+                            // near_pair_f64 takes nothing at zero distance (float64)
+                            const int64_t ns = a.in.n_src;
+                            const bool zero = t.x[k] == a.in.src_xyz[si] && t.y[k] == a.in.src_xyz[ns + si] &&
+                                              t.z[k] == a.in.src_xyz[2 * ns + si];
+                            const int32_t cls = excluded ? kPairSkip : !near ? kPairF32 : zero ? kPairSkip : kPairF64;
+                            atomicAdd(a.in.pair_class + ti * ns + si, cls);
+                        }
+                    }
                 }
             }
+            if constexpr (FEW) take(set, j0);
+        }
+        if constexpr (!FEW) {
+            if (__ballot(any) != 0)
+#pragma unroll 1
+                for (int j0 = 0; j0 < kSub; j0 += 32) {
+                    uint32_t set[T] = {};
+#pragma unroll 2
+                    for (int j = 0; j < 32; ++j) {
+                        const Rec sr = s_src[wave][j0 + j];
+                        const float4 sl = s_res[wave][j0 + j];
+#pragma unroll
+                        for (int k = 0; k < T; ++k) {
+                            float dx, dy, dz;
+                            const bool near = offset(sr, sl, k, dx, dy, dz) <= sr.t2;
+                            set[k] |= (uint32_t)(near && !(excl && sr.g == t.g[k])) << j;
+                        }
+                    }
+                    take(set, j0);
+                }
         }
 #pragma unroll
         for (int k = 0; k < T; ++k) {
@@ -825,10 +855,15 @@ static hipError_t launch_typed(const SumInputs& in, const DirectPlan& p, double*
     if (e != hipSuccess) return e;
     if constexpr (MIXED != 0) {
         const dim3 near_grid((unsigned)p.blocks_x, (unsigned)p.near_slices);
-        if (in.pair_class)
-            direct_near_mixed<KT, T, true><<<near_grid, dim3(kBlock), 0, stream>>>(a);
-        else
-            direct_near_mixed<KT, T><<<near_grid, dim3(kBlock), 0, stream>>>(a);
+        auto near = [&](auto few) {
+            constexpr bool F = decltype(few)::value;
+            if (in.pair_class)
+                direct_near_mixed<KT, T, F, true><<<near_grid, dim3(kBlock), 0, stream>>>(a);
+            else
+                direct_near_mixed<KT, T, F><<<near_grid, dim3(kBlock), 0, stream>>>(a);
+        };
+        if (p.n_sub <= kFewSubs) near(std::true_type{});
+        else near(std::false_type{});
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

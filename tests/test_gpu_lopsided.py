@@ -105,3 +105,28 @@ def test_mixed_values(kernel, ns, nt):
     else:
         got, ref = S.dl(dev(y), dev(f), dev(w), dev(nv), dev(x), **kw), O.dl(y, f, w, nv, x)
     assert_close(host(got), ref, MIXED_TOL, f"{kernel} {ns} x {nt}")
+
+
+@pytest.mark.parametrize("ns,nt,timed", [(544, 120_001, True), (192, 200_001, True), (1536, 20_001, False),
+                                         (1537, 20_001, False), (2176, 30_001, False)])
+def test_near_pairs(ns, nt, timed):
+    """Mixed sums, a spherical group of points among targets spread around it, with
+    float64 pairs within half a spacing (some in most sub-tiles, one in a thousand of
+    all pairs): values on both sides of the 24 sub-tiles up to which the near pass
+    notes such pairs in its float32 loop, and well below that they may add a tenth
+    to the call's time (taken source by source they added a fifth to a quarter)."""
+    rng = np.random.default_rng(ns)
+    v = rng.standard_normal((3, ns))
+    y, f, w = 2.0 * v / np.linalg.norm(v, axis=0), rng.standard_normal((3, ns)), rng.uniform(0.1, 1.0, ns)
+    x = rng.uniform(-3, 3, (3, nt))
+    x[:, :10] = y[:, :10]
+    args = [dev(a) for a in (y, f, w, x)]
+    kw = dict(src_group=dev(np.zeros(ns, np.int32)), exclude_same_group=False, precision="mixed")
+    out = torch.empty((3, nt), dtype=torch.float64, device=device())
+    spacing = [dev(np.full(1, h)) for h in (1e-9, 0.3)]
+    times = [_best_ms(lambda: S.sl(*args, group_h=h, out=out, **kw)) for h in spacing]
+    print(f"{ns} x {nt}: {times[0]:.3f} ms without near pairs, {times[1]:.3f} ms with", flush=True)
+    i = np.arange(0, nt, 37)
+    i[:10] = np.arange(10)
+    assert_close(host(out)[:, i], O.sl(y, f, w, x[:, i]), MIXED_TOL, "near")
+    assert not timed or times[1] <= 1.1 * times[0], times

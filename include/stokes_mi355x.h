@@ -570,24 +570,30 @@ int stokes_collision_candidates(stokes_ctx* ctx, int32_t n_boxes, const double* 
  * The plan holds the check-to-equivalent pseudo-inverses (singular values
  * below 1e-10 of the largest dropped), computed on the host at creation by a
  * threaded Jacobi SVD (about 0.1 s at order 4, 1.5 s at 6, 8 s at 8, 30 s at
- * 10 on 8 cores), and the M2L operators, built on the device: spectra of the
- * kernel on the surface lattice (a few MB; orders below 6, and the double
- * layer's leaf level at order 6), and from order 6 on, for each of the 8 positions of a box in
- * its parent, its 189 interaction-list translations and the parent-to-child
- * one at unit scale (8 x 190 x m^2 doubles, m = 3 (6 (order-1)^2 + 2) rounded
- * up to 16: 2.6 GB at order 6, 9.8 GB at 8, 26 GB at 10).  All of it is device
- * memory owned by the plan until stokes_fmm_plan_destroy. */
+ * 10 on 8 cores), and the M2L operators, built on the device: up to order 6
+ * the spectra of the kernel on the surface lattice (11 MB at order 4, 24 at 5,
+ * 44 at 6, for the double layer's leaf level there), and from order 6 on, for
+ * each of the 8 positions of a box in its parent, its 189 interaction-list
+ * translations and the parent-to-child one at unit scale (8 x 190 x m^2
+ * doubles, m = 3 (6 (order-1)^2 + 2) rounded up to 16: 2.6 GB at order 6,
+ * 9.8 GB at 8, 26 GB at 10).  All of it is device memory owned by the plan
+ * until stokes_fmm_plan_destroy. */
 int stokes_fmm_plan_create(stokes_ctx* ctx, int32_t order, stokes_fmm_plan** plan);   /* order 2..10 */
 void stokes_fmm_plan_destroy(stokes_fmm_plan* plan);
 
 /* Workspace for n_src sources, n_trg targets and depth (2..7): the per-box
  * densities grow as 8^depth * 6 * (6 (order-1)^2 + 2) doubles, the check
  * matrix of a level as 3 min(8^depth, max(n_src, n_trg)) + 262,656 columns of
- * m doubles (m as above), plus 32,768 columns of 3 (6 (order-1)^2 + 2) doubles
- * for the split pseudo-inverse products; up to order 6 the box spectra take at
- * most 3.2 GiB beside them.  excl (may be NULL) as in the
- * evaluation: the same-group rule adds about 150 bytes per point and 32 per
- * group. */
+ * m doubles (m as above; below order 6 min(8^depth, max(n_src, n_trg)) columns),
+ * plus 32,768 columns of 3 (6 (order-1)^2 + 2) doubles for the split
+ * pseudo-inverse products.  Below order 6 the box spectra come beside them, 384
+ * order (2 order - 1)^2 bytes for each of min(8^(depth-1), n_src) + 1 boxes and
+ * as much for each of min(8^(depth-1), n_trg): at the sources up to 3,200 MiB or
+ * one order-th of that, whichever is more, at the targets up to 3,200 MiB.  At
+ * order 6 (double layer) they lie in the check matrix's space beyond
+ * min(8^depth, max(n_src, n_trg)) columns, which grows only if that is too
+ * small.  excl (may be NULL) as in the evaluation: the same-group rule adds about
+ * 150 bytes per point and 32 per group. */
 int stokes_fmm_workspace_size(const stokes_ctx* ctx, const stokes_fmm_plan* plan, int64_t n_src,
                               int64_t n_trg, int32_t depth, const stokes_exclusion* excl, size_t* bytes);
 

@@ -83,6 +83,14 @@ constexpr int64_t kFMaxGrid = 1 << 16;
 // at the leaves by up to 9.8e-10 (200 of them, the worst sizes among them).
 // 1,048,576 nodes at 522,240 points: 15.1 ms without, 10.3 with, 7.5 at all levels.
 constexpr int kDenseOrder = 6, kLeafConvOrderDL = 6;
+static_assert(kDenseOrder - 1 <= kFftMaxOrder && kLeafConvOrderDL <= kFftMaxOrder, "orders with convolution levels");
+// Whether an order's plan serves convolution levels, and whether level l of an
+// evaluation of depth D is one.  Operators, spectra and lists of the convolution
+// exist for these alone.
+constexpr bool conv_order(int order) { return order < kDenseOrder || order == kLeafConvOrderDL; }
+constexpr bool conv_level(int order, bool dl, int l, int D) {
+    return order < kDenseOrder || (dl && order == kLeafConvOrderDL && l == D);
+}
 
 unsigned f_grid(int64_t units) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(units, kFMaxGrid)); }
 
@@ -1392,9 +1400,11 @@ struct FmmLayout {
     SortLayout sort;
     size_t off_skeys, off_svals, off_tkeys, off_tvals, off_sort, off_sx, off_sq, off_sn, off_tx, off_sofs, off_tofs,
         off_sslot, off_tslot, off_sig, off_ue, off_de, off_uofs, off_scan, off_ul, off_p2p, off_bscan, off_btmp,
-        off_counts, off_slist, off_tlist, off_cflag, off_cscan, off_ctotal, off_clist, off_sched, off_nbr, off_q, off_sigq, off_v, off_vbuf, off_apart, total;
+        off_counts, off_slist, off_tlist, off_cflag, off_cscan, off_ctotal, off_clist, off_sched, off_nbr, off_q,
+        off_v, off_sigq, off_vbuf, off_apart, total;
 };
 
+// The same for both layers (the double layer's at order 6).
 FmmLayout fmm_layout(int order, int64_t n_src, int64_t n_trg, int D) {
     const int ns = 6 * (order - 1) * (order - 1) + 2;
     const int mp = pad16(3 * ns);
@@ -1445,16 +1455,16 @@ FmmLayout fmm_layout(int order, int64_t n_src, int64_t n_trg, int D) {
     L.off_counts = take((size_t)2 * (kFmmMaxDepth + 1) * 8);
     L.off_slist = take((size_t)L.nbox * 4);
     L.off_tlist = take((size_t)L.nbox * 4);
-    L.off_nbr = take((size_t)26 * L.base[D] * 4);
-    // spectra of a level's octets, the largest of the levels
+    L.off_nbr = take(conv_order(order) ? (size_t)26 * L.base[D] * 4 : 0);
+    L.off_sigq = take(conv_order(order) ? (size_t)(octets(D, n_src) + 1) * 8 * 8 : 0);
+    // spectra of a convolution level's octets, the largest of the levels
     size_t q = 0, v = 0;
-    for (int l = 2; l <= D; ++l) {
-        q = std::max(q, fft_q_bytes(order, octets(l, n_src), octets(l, n_trg)));
-        v = std::max(v, fft_v_bytes(order, octets(l, n_src), octets(l, n_trg)));
-    }
-    L.off_q = take(q);
-    L.off_v = take(v);
-    L.off_sigq = take((size_t)(octets(D, n_src) + 1) * 8 * 8);
+    for (int l = 2; l <= D; ++l)
+        if (conv_level(order, true, l, D)) {
+            const FftBatches bt = fft_batches(order, octets(l, n_src), octets(l, n_trg));
+            q = std::max(q, align_up(bt.q_bytes, 256));
+            v = std::max(v, bt.v_bytes);
+        }
     L.off_cflag = take((size_t)L.n_leaves * 8);
     L.off_cscan = take((size_t)scan_tmp_count(L.n_leaves) * 8);
     L.off_ctotal = take(8);
@@ -1464,9 +1474,15 @@ FmmLayout fmm_layout(int order, int64_t n_src, int64_t n_trg, int D) {
     // K-split partials of the dense levels: splits x listed boxes <= 3 listed + 64 (units + 8)
     const int64_t cols = std::min(L.n_leaves, std::max<int64_t>({n_src, n_trg, 1}));
     const int64_t parts = order >= kDenseOrder ? kM2LMinSplits * cols + kGemmNT * (kM2LUnits + 8) : 0;
-    L.off_vbuf = take((size_t)std::max(cols, parts) * mp * 8);
+    // (the spectra, and after them the partials of apply_exact_kernel, lie beside the columns, where
+    // the dense levels have theirs: 262,656 columns, the exact partials 3 kApplyUnits x 64 = 98,304)
+    const size_t vbuf = align_up((size_t)cols * mp * 8, 256);
+    L.off_vbuf = take(std::max(vbuf + q + v, (size_t)parts * mp * 8));
+    L.off_q = L.off_vbuf + vbuf;
+    L.off_v = L.off_q + q;
     // split partials of the pseudo-inverse products: S x listed <= kApplyUnits x 64 columns when S > 1
-    L.off_apart = take((size_t)(order == kLeafConvOrderDL ? 3 : 1) * kApplyUnits * kGemmNT * 3 * ns * 8);
+    static_assert(kLeafConvOrderDL >= kDenseOrder && 3 * kApplyUnits <= kM2LUnits, "room for the exact partials");
+    L.off_apart = take((size_t)kApplyUnits * kGemmNT * 3 * ns * 8);
     L.total = off;
     return L;
 }
@@ -1741,7 +1757,7 @@ int fmm_plan_build(int device, int order, stokes_fmm_plan** out, std::string& er
             downA[(size_t)k * mp + r] = down[(size_t)r * n3 + k];
             upA[(size_t)k * mp + r] = up[(size_t)r * n3 + k];
         }
-    hipError_t e = hipMalloc(&p->d_khat, fft_spectra_bytes(order));
+    hipError_t e = hipSuccess;
     if (order == kLeafConvOrderDL) {
         std::vector<double> down3((size_t)3 * mp * mp, 0.0);
         for (int r = 0; r < n3; ++r) {
@@ -1761,13 +1777,16 @@ int fmm_plan_build(int device, int order, stokes_fmm_plan** out, std::string& er
         if (e == hipSuccess) e = hipMalloc(&p->d_down3, down3.size() * 8);
         if (e == hipSuccess) e = hipMemcpy(p->d_down3, down3.data(), down3.size() * 8, hipMemcpyHostToDevice);
     }
-    if (e == hipSuccess) e = hipMalloc(&p->d_tw, (size_t)2 * fft_n(order) * 8);
     if (e == hipSuccess) e = hipMalloc(&p->d_downA, downA.size() * 8);
     if (e == hipSuccess) e = hipMalloc(&p->d_upA, upA.size() * 8);
     if (e == hipSuccess) e = hipMemcpy(p->d_upA, upA.data(), upA.size() * 8, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_downA, downA.data(), downA.size() * 8, hipMemcpyHostToDevice);
     static_assert(kAlphaUE == kAlphaDC, "M2L is a convolution on one lattice");
-    if (e == hipSuccess) e = fft_build_spectra(order, kAlphaUE, p->d_khat, p->d_tw, 0);
+    if (conv_order(order)) {
+        if (e == hipSuccess) e = hipMalloc(&p->d_khat, fft_spectra_bytes(order));
+        if (e == hipSuccess) e = hipMalloc(&p->d_tw, (size_t)2 * fft_n(order) * 8);
+        if (e == hipSuccess) e = fft_build_spectra(order, kAlphaUE, p->d_khat, p->d_tw, 0);
+    }
     if (order >= kDenseOrder) {
         const size_t ab = (size_t)8 * kM2LBlocks * mp * mp * 8;
         if (e == hipSuccess) e = hipMalloc(&p->d_m2l, ab);
@@ -1894,7 +1913,7 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
             e = exclusive_scan_i64(f, 2 * L.nbox, f, reinterpret_cast<int64_t*>(ws + L.off_btmp), f + 2 * L.nbox, st);
         if (e == hipSuccess)
             hipLaunchKernelGGL(box_lists_kernel, dim3(gb), dim3(kFBlock), 0, st, a, L.nbox, f, slist, tlist, counts);
-        if (chk())
+        if (chk() && conv_level(plan->order, dl, D, D))
             hipLaunchKernelGGL(octet_neighbours_kernel, dim3(f_grid((L.base[D] + kFBlock - 1) / kFBlock)),
                                dim3(kFBlock), 0, st, a, counts, nbr);
     }
@@ -1905,12 +1924,12 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
     a.mp = plan->mp;
     const int rb = gemm_rb(plan->mp), ngr = gemm_groups(plan->mp, rb);
     // OP V for the listed boxes of a level, into out (rows n3 per box)
-    double* apart = reinterpret_cast<double*>(ws + L.off_apart);
     auto apply = [&](int l, const Columns& c, const double* op, double* out, bool exact = false) {
         // units: tiles x splits <= max(tiles, kApplyUnits), tiles at most the bound below
         const int64_t tiles_ub =
             (std::min<int64_t>((int64_t)1 << (3 * l), std::max(in.n_src, in.n_trg)) + kGemmNT - 1) / kGemmNT;
         const int per_split = exact ? 3 : 1;
+        double* apart = reinterpret_cast<double*>(ws + (exact ? L.off_q : L.off_apart));
         const dim3 g((unsigned)(ngr * std::max<int64_t>(tiles_ub, per_split * kApplyUnits)));
         if (exact) {
             hipLaunchKernelGGL(apply_exact_kernel<kGemmMaxRB>, g, dim3(kGemmThreads), 0, st, a, c, op, out, apart);
@@ -1971,8 +1990,7 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
     m.vbuf = a.vbuf;
     for (int l = 2; l <= D && chk(); ++l) {
         const int64_t boxes = (int64_t)1 << (3 * l);
-        const bool conv = plan->order < kDenseOrder || (dl && plan->order == kLeafConvOrderDL && l == D);
-        if (!conv) {
+        if (!conv_level(plan->order, dl, l, D)) {
             const unsigned gb = f_grid((boxes + kFBlock - 1) / kFBlock);
             int64_t* cflag = const_cast<int64_t*>(g2.cscan);
             hipLaunchKernelGGL(class_flags_kernel, dim3(gb), dim3(kFBlock), 0, st, a, l, cflag);

@@ -25,8 +25,9 @@
 // levels of the double layer of 1,048,576 wall nodes at 522,240 points at depth 6,
 // 12.3 ms of pair sums before, 4.1 ms.
 //
-// Spectra buffers hold a batch of kz planes; a level whose octets could be too
-// many for one batch runs several.  Every sum has a fixed order.
+// The spectra buffers hold a batch of kz planes, and at the targets a share of
+// the octets; a level whose octets could be too many runs several.  Every sum has
+// a fixed order, which the batches do not change.
 #include <math.h>
 
 #include <algorithm>
@@ -38,7 +39,11 @@
 namespace stokes {
 namespace {
 
-constexpr size_t kFftBudget = (size_t)3200 << 20;    // bytes a spectra buffer may take before planes are split
+// Bytes of the source octets' spectra before planes are split, and of the target
+// octets' before those are.  More batches cost launches and reads of the densities:
+// 1,048,576 wall nodes at 522,240 points, order 6, depth 6, 10.3 ms with these, 10.6
+// with 1 GiB and 640 MiB; order 4, 300,000 points of a shell at depth 6, 3.74 and 3.90.
+constexpr size_t kFftSrcBytes = (size_t)3200 << 20, kFftTrgBytes = (size_t)3200 << 20;
 constexpr int kFftSplitMax = 512;                    // octets up to which the four waves of a workgroup share a tile
 constexpr int kFftNT = 2;                            // 16-column tiles per wave when they do not
 
@@ -66,7 +71,8 @@ __device__ __forceinline__ int surf_index(int i, int j, int k) {
 // (re, im).  Offsets of adjacent boxes are zero.
 __global__ __launch_bounds__(256) void spectra_kernel(int p, double alpha, const double* __restrict__ tw,
                                                       double* __restrict__ khat) {
-    __shared__ double2 A[19 * 19], B[19 * 19], w[19];
+    constexpr int kN = fft_n(kFftMaxOrder);
+    __shared__ double2 A[kN * kN], B[kN * kN], w[kN];
     const int N = fft_n(p), o = blockIdx.x;
     const int ox[3] = {o / 49 - 3, o / 7 % 7 - 3, o % 7 - 3};
     const bool adjacent = abs(ox[0]) <= 1 && abs(ox[1]) <= 1 && abs(ox[2]) <= 1;
@@ -255,9 +261,9 @@ __global__ __launch_bounds__(256, 2) void fft_translate_kernel(FftLevel a, int64
     constexpr int kPart = 3 * NT * 4 * kWave;               // doubles of a wave's accumulators
     __shared__ __attribute__((aligned(16))) double s_op[kOpAll];
     __shared__ double s_red[SPLIT ? 3 * kPart : 1];
-    const int64_t nt = *a.n_toct, ns = *a.n_soct;
-    if (nt == 0) return;
-    const int64_t tiles = (nt + COLS - 1) / COLS, U = tiles * nf, G = gridDim.x;
+    const int64_t nt = *a.n_toct, ns = *a.n_soct, t1 = min(nt, a.t0 + a.tn);
+    if (t1 <= a.t0) return;
+    const int64_t tiles = (t1 - a.t0 + COLS - 1) / COLS, U = tiles * nf, G = gridDim.x;
     const int64_t idx = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);     // G is a multiple of 8
     const int64_t u0 = idx * U / G, u1 = (idx + 1) * U / G;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -277,7 +283,7 @@ __global__ __launch_bounds__(256, 2) void fft_translate_kernel(FftLevel a, int64
             loaded = f;
             __syncthreads();
         }
-        const int64_t col0 = tile * COLS + (SPLIT ? 0 : wave * 16 * NT);
+        const int64_t col0 = a.t0 + tile * COLS + (SPLIT ? 0 : wave * 16 * NT);
         v4d acc[3][NT];
 #pragma unroll
         for (int i = 0; i < 3; ++i)
@@ -289,7 +295,7 @@ __global__ __launch_bounds__(256, 2) void fft_translate_kernel(FftLevel a, int64
 #pragma unroll
             for (int k = 0; k < NT; ++k) {
                 const int64_t col = col0 + 16 * k + row;
-                s[k] = i < nd && col < nt ? a.nbr[direction(i) * nt + col] : (int32_t)ns;
+                s[k] = i < nd && col < t1 ? a.nbr[direction(i) * nt + col] : (int32_t)ns;
             }
         };
         struct Frag { double2 b[NT][6]; double s[NT][2]; };
@@ -353,7 +359,7 @@ __global__ __launch_bounds__(256, 2) void fft_translate_kernel(FftLevel a, int64
                                                                              0, 0, 0);
             }
         };
-        if (SPLIT || col0 < nt) {
+        if (SPLIT || col0 < t1) {
             int32_t s0[NT], s1[NT];
             Frag r0, r1;
             slots(0, s0);
@@ -400,8 +406,8 @@ __global__ __launch_bounds__(256, 2) void fft_translate_kernel(FftLevel a, int64
 #pragma unroll
             for (int k = 0; k < NT; ++k) {
                 const int64_t col = col0 + 16 * k + row;
-                if (col >= nt) continue;
-                double2* o = reinterpret_cast<double2*>(a.v + (f * nt + col) * kFftRow + g * 6);
+                if (col >= t1) continue;
+                double2* o = reinterpret_cast<double2*>(a.v + (f * a.tn + col - a.t0) * kFftRow + g * 6);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     o[c] = make_double2(acc[c][k][0], acc[c][k][1]);
@@ -423,10 +429,10 @@ __global__ __launch_bounds__(fft_threads(P)) void fft_inverse_kernel(FftLevel a,
                                                                      int k0, int k1) {
     constexpr int N = fft_n(P), NT = fft_threads(P);
     __shared__ double2 A[24 * P * P], B[24 * P * N];
-    const int64_t n = *a.n_toct;
+    const int64_t t1 = min(*a.n_toct, a.t0 + a.tn), n = a.tn;
     const int tid = threadIdx.x;
     const int f0 = fft_first(P, k0);
-    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
+    for (int64_t i = a.t0 + blockIdx.x; i < t1; i += gridDim.x) {
         const int64_t box0 = (int64_t)a.toct[i] * 8;
         for (int kz = k0; kz < k1; ++kz) {
             const int cc = tid % 24, ky = tid / 24;
@@ -435,7 +441,7 @@ __global__ __launch_bounds__(fft_threads(P)) void fft_inverse_kernel(FftLevel a,
                 const bool mirror = kz == 0 && ky >= P;
                 const int kyr = mirror ? N - ky : ky;
                 const int f = fft_first(P, kz) - f0 + (kz > 0 ? ky * N : kyr == 0 ? 0 : P + (kyr - 1) * N);
-                const double* v = a.v + ((int64_t)f * n + i) * kFftRow + 2 * cc;
+                const double* v = a.v + ((int64_t)f * n + i - a.t0) * kFftRow + 2 * cc;
                 double2 s[P];
 #pragma unroll
                 for (int x = 0; x < P; ++x) s[x] = make_double2(0.0, 0.0);
@@ -507,14 +513,11 @@ bool with_order(int p, F&& f) {
         case 3: f(std::integral_constant<int, 3>{}); return true;
         case 4: f(std::integral_constant<int, 4>{}); return true;
         case 5: f(std::integral_constant<int, 5>{}); return true;
-        case 6: f(std::integral_constant<int, 6>{}); return true;
-        case 7: f(std::integral_constant<int, 7>{}); return true;
-        case 8: f(std::integral_constant<int, 8>{}); return true;
-        case 9: f(std::integral_constant<int, 9>{}); return true;
-        case 10: f(std::integral_constant<int, 10>{}); return true;
+        case kFftMaxOrder: f(std::integral_constant<int, kFftMaxOrder>{}); return true;
         default: return false;
     }
 }
+static_assert(kFftMaxOrder == 6, "with_order covers 2 .. kFftMaxOrder");
 
 size_t plane_bytes(int p, int64_t octets) { return (size_t)fft_n(p) * fft_n(p) * (size_t)octets * kFftRow * 8; }
 
@@ -535,46 +538,50 @@ hipError_t fft_build_spectra(int p, double alpha, double* khat, double* tw, hipS
     return hipGetLastError();
 }
 
-int fft_planes(int p, int64_t max_soct, int64_t max_toct) {
-    const size_t one = plane_bytes(p, std::max(max_soct + 1, max_toct));
-    return (int)std::min<size_t>(p, std::max<size_t>(1, kFftBudget / one));
-}
-size_t fft_q_bytes(int p, int64_t max_soct, int64_t max_toct) {
-    return batch_freqs(p, fft_planes(p, max_soct, max_toct)) * (size_t)(max_soct + 1) * kFftRow * 8;
-}
-size_t fft_v_bytes(int p, int64_t max_soct, int64_t max_toct) {
-    return batch_freqs(p, fft_planes(p, max_soct, max_toct)) * (size_t)max_toct * kFftRow * 8;
+FftBatches fft_batches(int p, int64_t max_soct, int64_t max_toct) {
+    FftBatches r{};
+    r.planes = (int)std::min<size_t>(p, std::max<size_t>(1, kFftSrcBytes / plane_bytes(p, max_soct + 1)));
+    const size_t freqs = batch_freqs(p, r.planes), octet = freqs * kFftRow * 8;
+    const int64_t fit = (int64_t)(kFftTrgBytes / octet) / 128 * 128;   // whole tiles; 13,056 octets or more
+    r.tcols = std::min(max_toct, fit);
+    r.q_bytes = (size_t)(max_soct + 1) * octet;
+    r.v_bytes = (size_t)r.tcols * octet;
+    return r;
 }
 
-hipError_t launch_fft_m2l(const FftLevel& a, int64_t max_soct, int64_t max_toct, int cus, hipStream_t st) {
-    const int planes = fft_planes(a.p, max_soct, max_toct);
+hipError_t launch_fft_m2l(const FftLevel& level, int64_t max_soct, int64_t max_toct, int cus, hipStream_t st) {
+    FftLevel a = level;
+    const FftBatches bt = fft_batches(a.p, max_soct, max_toct);
     // grid-stride over the octets: enough workgroups to fill the chip with the smaller ones
     const unsigned gs = (unsigned)std::min<int64_t>(max_soct + 1, 8 * (int64_t)cus);
-    const unsigned gt = (unsigned)std::min<int64_t>(max_toct, 8 * (int64_t)cus);
+    const unsigned gt = (unsigned)std::min<int64_t>(bt.tcols, 8 * (int64_t)cus);
+    // two workgroups fit a CU (registers); a level with few octets still has a unit per frequency
+    const dim3 g((unsigned)((2 * cus + 7) / 8 * 8));
+    const bool split = max_toct <= kFftSplitMax;
     hipError_t e = hipSuccess;
-    for (int k0 = 0; k0 < a.p && e == hipSuccess; k0 += planes) {
-        const int k1 = std::min(a.p, k0 + planes);
+    for (int k0 = 0; k0 < a.p; k0 += bt.planes) {
+        const int k1 = std::min(a.p, k0 + bt.planes);
         const int64_t f0 = fft_first(a.p, k0), nf = fft_first(a.p, k1) - f0;
         if (!with_order(a.p, [&](auto o) {
                 hipLaunchKernelGGL(fft_forward_kernel<decltype(o)::value>, dim3(gs),
                                    dim3(fft_threads(decltype(o)::value)), 0, st, a, a.tw, k0, k1);
             }))
             return hipErrorInvalidValue;
-        if ((e = hipGetLastError()) != hipSuccess) break;
-        // two workgroups fit a CU (registers); a level with few octets still has a unit per frequency
-        const dim3 g((unsigned)((2 * cus + 7) / 8 * 8));
-        const bool split = max_toct <= kFftSplitMax;
-        if (split && a.sig) hipLaunchKernelGGL((fft_translate_kernel<1, true, true>), g, dim3(256), 0, st, a, f0, nf);
-        else if (split) hipLaunchKernelGGL((fft_translate_kernel<1, true, false>), g, dim3(256), 0, st, a, f0, nf);
-        else if (a.sig)
-            hipLaunchKernelGGL((fft_translate_kernel<kFftNT, false, true>), g, dim3(256), 0, st, a, f0, nf);
-        else hipLaunchKernelGGL((fft_translate_kernel<kFftNT, false, false>), g, dim3(256), 0, st, a, f0, nf);
-        if ((e = hipGetLastError()) != hipSuccess) break;
-        (void)with_order(a.p, [&](auto o) {
-            hipLaunchKernelGGL(fft_inverse_kernel<decltype(o)::value>, dim3(gt),
-                               dim3(fft_threads(decltype(o)::value)), 0, st, a, a.tw, k0, k1);
-        });
-        e = hipGetLastError();
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        for (a.t0 = 0; a.t0 < max_toct; a.t0 += bt.tcols) {
+            a.tn = std::min(bt.tcols, max_toct - a.t0);
+            if (split && a.sig) hipLaunchKernelGGL((fft_translate_kernel<1, true, true>), g, dim3(256), 0, st, a, f0, nf);
+            else if (split) hipLaunchKernelGGL((fft_translate_kernel<1, true, false>), g, dim3(256), 0, st, a, f0, nf);
+            else if (a.sig)
+                hipLaunchKernelGGL((fft_translate_kernel<kFftNT, false, true>), g, dim3(256), 0, st, a, f0, nf);
+            else hipLaunchKernelGGL((fft_translate_kernel<kFftNT, false, false>), g, dim3(256), 0, st, a, f0, nf);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            (void)with_order(a.p, [&](auto o) {
+                hipLaunchKernelGGL(fft_inverse_kernel<decltype(o)::value>, dim3(gt),
+                                   dim3(fft_threads(decltype(o)::value)), 0, st, a, a.tw, k0, k1);
+            });
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
     }
     return e;
 }

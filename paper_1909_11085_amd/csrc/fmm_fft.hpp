@@ -20,6 +20,7 @@ __host__ __device__ constexpr int fft_first(int p, int kz) {      // frequencies
 }
 __host__ __device__ constexpr int fft_freqs(int p) { return fft_first(p, p); }
 
+constexpr int kFftMaxOrder = 6;                   // the highest order with a convolution level
 constexpr int kFftOffsets = 343;                  // source minus target box, -3 .. 3 per axis
 constexpr int kFftOpStride = kFftOffsets * 24;    // doubles per frequency: 18 per offset, then 6 (flux)
 constexpr int kFftRow = 48;                       // doubles per octet and frequency: 8 children x 3 complex
@@ -45,18 +46,21 @@ struct FftLevel {
     const int32_t* nbr;          // (26, *n_toct): source octet next to a target octet, *n_soct when none
     const double* sig;           // per box of the level: point-source flux (double layer), else null
     double inv_h;                // 1 / box half-width
-    double* q;                   // spectra of the source octets of a batch of planes
+    double* q;                   // spectra of the source octets of a batch of planes (plan.q_bytes)
     double* sigq;                // flux over h, 8 per source octet
-    double* v;                   // spectra at the target octets
+    double* v;                   // spectra at a batch's share of the target octets (plan.v_bytes)
+    int64_t t0, tn;              // that share: target octets t0 .. t0 + tn - 1 (set by the launch)
     double* vbuf;                // check vectors times h, mp per column
     bool add;                    // add to vbuf's columns instead of writing them
 };
 
-// Planes per batch for at most n_soct and n_toct octets, and the bytes of the
-// two spectra buffers that such batches need.
-int fft_planes(int p, int64_t max_soct, int64_t max_toct);
-size_t fft_q_bytes(int p, int64_t max_soct, int64_t max_toct);
-size_t fft_v_bytes(int p, int64_t max_soct, int64_t max_toct);
+// The batches of a level with at most max_soct source and max_toct target
+// octets: planes per batch, target octets at a time, and the bytes of the two
+// spectra buffers.  The source octets' spectra take up to 3,200 MiB, or one plane's
+// (2 p - 1)^2 x 384 bytes an octet where that is more; the target octets' up to
+// 3,200 MiB.  The batches change no sum and no order of one.
+struct FftBatches { int planes; int64_t tcols; size_t q_bytes, v_bytes; };
+FftBatches fft_batches(int p, int64_t max_soct, int64_t max_toct);
 
 // Writes (or adds) into the vbuf column of every box of the level that holds
 // targets h times its check vector from the interaction lists; when writing,

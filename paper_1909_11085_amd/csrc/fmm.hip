@@ -85,11 +85,23 @@ constexpr int64_t kFMaxGrid = 1 << 16;
 constexpr int kDenseOrder = 6, kLeafConvOrderDL = 6;
 static_assert(kDenseOrder - 1 <= kFftMaxOrder && kLeafConvOrderDL <= kFftMaxOrder, "orders with convolution levels");
 // Whether an order's plan serves convolution levels, and whether level l of an
-// evaluation of depth D is one.  Operators, spectra and lists of the convolution
-// exist for these alone.
+// evaluation of depth D with this many sources and targets (the fewer) is one.
+// Operators, spectra and lists of the convolution exist for these alone.  A level
+// with fewer points than half its octets (boxes of level l - 1) has mostly one
+// child in an octet, of whose 64 child pairs the convolution does all: such a
+// level runs as pair sums, at order 6 (with fewer points than octets) by the dense
+// levels' kernels.  Whole evaluations, one point for 8, 4, 2 and 1 octets of the leaves,
+// pair sums there / convolution (double layer, depth 6, ms): order 5, uniform points
+// 5.2, 6.8, 9.4, 15.2 / 7.8, 11.6, 17.4, 25.2, points of a sphere 3.5, 4.3, 6.1, 8.2 / 4.7, 5.6,
+// 6.3, 7.0; order 6, 11.7, 19.7, 35.8, 61.2 / 17.1, 29.6, 51.8, 78.8 and 6.9, 9.8, 14.8, 20.0 / 9.7,
+// 12.4, 14.9, 16.9.  At orders 2 and 3 the convolution is the faster at every fill (order 3,
+// one point for 4 octets of a sphere, 1.65 against 1.96).
 constexpr bool conv_order(int order) { return order < kDenseOrder || order == kLeafConvOrderDL; }
-constexpr bool conv_level(int order, bool dl, int l, int D) {
-    return order < kDenseOrder || (dl && order == kLeafConvOrderDL && l == D);
+constexpr bool conv_level(int order, bool dl, int l, int D, int64_t points) {
+    const int64_t octets = (int64_t)1 << (3 * (l - 1));
+    return order < 4             ? true
+           : order < kDenseOrder ? points >= octets / 2
+                                 : dl && order == kLeafConvOrderDL && l == D && points >= octets;
 }
 
 unsigned f_grid(int64_t units) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(units, kFMaxGrid)); }
@@ -901,7 +913,7 @@ struct M2LArgs {
                                // upward pass reuses it for the boxes holding sources
     const int64_t* ctotal;     // number of listed boxes
     const int32_t* list;       // target boxes of the level, grouped by class
-    int64_t* sched;            // [0]: K splits of this level, [1]: 1 = pair sums instead of the GEMM
+    int64_t* sched;            // [0]: K splits of this level, [1]: 1 = pair sums instead of the GEMM (dense orders)
     int64_t* npairs;           // per workgroup of il_count_kernel: non-empty (target box,
                                // interaction-list box) pairs of the level
     double* vbuf;              // (splits, listed boxes, mp): partial check vectors times h
@@ -1111,7 +1123,7 @@ size_t m2l_lds(int ns) { return ((size_t)((3 * ns + 1) & ~1) + (size_t)kFWaves *
 template <int T>
 __global__ __launch_bounds__(kFBlock) void m2l_pairs_kernel(FmmDev a, M2LArgs g, int l) {
     extern __shared__ double sh[];
-    if (!g.sched[1]) return;                                   // this level runs as a GEMM
+    if (g.sched && !g.sched[1]) return;                        // this level runs as a GEMM (null: never)
     double* surf = sh;
     double* rest = surf + ((3 * a.ns + 1) & ~1);               // 16-byte aligned
     double* part = rest;
@@ -1460,7 +1472,7 @@ FmmLayout fmm_layout(int order, int64_t n_src, int64_t n_trg, int D) {
     // spectra of a convolution level's octets, the largest of the levels
     size_t q = 0, v = 0;
     for (int l = 2; l <= D; ++l)
-        if (conv_level(order, true, l, D)) {
+        if (conv_level(order, true, l, D, std::min(n_src, n_trg))) {
             const FftBatches bt = fft_batches(order, octets(l, n_src), octets(l, n_trg));
             q = std::max(q, align_up(bt.q_bytes, 256));
             v = std::max(v, bt.v_bytes);
@@ -1913,7 +1925,7 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
             e = exclusive_scan_i64(f, 2 * L.nbox, f, reinterpret_cast<int64_t*>(ws + L.off_btmp), f + 2 * L.nbox, st);
         if (e == hipSuccess)
             hipLaunchKernelGGL(box_lists_kernel, dim3(gb), dim3(kFBlock), 0, st, a, L.nbox, f, slist, tlist, counts);
-        if (chk() && conv_level(plan->order, dl, D, D))
+        if (chk() && conv_order(plan->order))
             hipLaunchKernelGGL(octet_neighbours_kernel, dim3(f_grid((L.base[D] + kFBlock - 1) / kFBlock)),
                                dim3(kFBlock), 0, st, a, counts, nbr);
     }
@@ -1990,7 +2002,24 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
     m.vbuf = a.vbuf;
     for (int l = 2; l <= D && chk(); ++l) {
         const int64_t boxes = (int64_t)1 << (3 * l);
-        if (!conv_level(plan->order, dl, l, D)) {
+        auto pairs = [&](const M2LArgs& g) {
+            with_T(T, [&](auto tc) {
+                hipLaunchKernelGGL(m2l_pairs_kernel<decltype(tc)::value>,
+                                   dim3(f_grid(std::min<int64_t>({boxes, in.n_trg, kM2LPairBlocks}))), dim3(kFBlock),
+                                   m2l_lds(ns), st, a, g, l);
+            });
+            return chk();
+        };
+        const bool conv = conv_level(plan->order, dl, l, D, std::min(in.n_src, in.n_trg));
+        if (!conv && plan->order < kDenseOrder) {
+            const Columns c = targets(l);
+            M2LArgs g{};
+            g.list = c.list;
+            g.ctotal = c.n;
+            if (!pairs(g) || !apply(l, c, plan->d_downA, a.de + L.base[l] * a.n3)) break;
+            continue;
+        }
+        if (!conv) {
             const unsigned gb = f_grid((boxes + kFBlock - 1) / kFBlock);
             int64_t* cflag = const_cast<int64_t*>(g2.cscan);
             hipLaunchKernelGGL(class_flags_kernel, dim3(gb), dim3(kFBlock), 0, st, a, l, cflag);
@@ -2020,12 +2049,7 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
                                dim3(f_grid((std::min<int64_t>(boxes, in.n_trg) * plan->mp + kFBlock - 1) / kFBlock)),
                                dim3(kFBlock), 0, st, g2);
             if (!chk()) break;
-            with_T(T, [&](auto tc) {
-                hipLaunchKernelGGL(m2l_pairs_kernel<decltype(tc)::value>,
-                                   dim3(f_grid(std::min<int64_t>({boxes, in.n_trg, kM2LPairBlocks}))), dim3(kFBlock),
-                                   m2l_lds(ns), st, a, g2, l);
-            });
-            if (!chk()) break;
+            if (!pairs(g2)) break;
             if (!apply(l, Columns{g2.list, g2.ctotal}, plan->d_downA, a.de + L.base[l] * a.n3)) break;
             continue;
         }

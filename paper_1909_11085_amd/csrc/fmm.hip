@@ -85,7 +85,7 @@ constexpr int64_t kFMaxGrid = 1 << 16;
 constexpr int kDenseOrder = 6, kLeafConvOrderDL = 6;
 static_assert(kDenseOrder - 1 <= kFftMaxOrder && kLeafConvOrderDL <= kFftMaxOrder, "orders with convolution levels");
 // Whether an order's plan serves convolution levels, and whether level l of an
-// evaluation of depth D with this many sources and targets (the fewer) is one.
+// evaluation of depth D with this many sources or targets (the more) is one.
 // Operators, spectra and lists of the convolution exist for these alone.  A level
 // with fewer points than half its octets (boxes of level l - 1) has mostly one
 // child in an octet, of whose 64 child pairs the convolution does all: such a
@@ -95,7 +95,8 @@ static_assert(kDenseOrder - 1 <= kFftMaxOrder && kLeafConvOrderDL <= kFftMaxOrde
 // 5.2, 6.8, 9.4, 15.2 / 7.8, 11.6, 17.4, 25.2, points of a sphere 3.5, 4.3, 6.1, 8.2 / 4.7, 5.6,
 // 6.3, 7.0; order 6, 11.7, 19.7, 35.8, 61.2 / 17.1, 29.6, 51.8, 78.8 and 6.9, 9.8, 14.8, 20.0 / 9.7,
 // 12.4, 14.9, 16.9.  At orders 2 and 3 the convolution is the faster at every fill (order 3,
-// one point for 4 octets of a sphere, 1.65 against 1.96).
+// one point for 4 octets of a sphere, 1.65 against 1.96), and so it is where one
+// side alone is sparse (1 target at 500,000 sources, order 5, depth 5, 1.8 against 3.5).
 constexpr bool conv_order(int order) { return order < kDenseOrder || order == kLeafConvOrderDL; }
 constexpr bool conv_level(int order, bool dl, int l, int D, int64_t points) {
     const int64_t octets = (int64_t)1 << (3 * (l - 1));
@@ -1472,7 +1473,7 @@ FmmLayout fmm_layout(int order, int64_t n_src, int64_t n_trg, int D) {
     // spectra of a convolution level's octets, the largest of the levels
     size_t q = 0, v = 0;
     for (int l = 2; l <= D; ++l)
-        if (conv_level(order, true, l, D, std::min(n_src, n_trg))) {
+        if (conv_level(order, true, l, D, std::max(n_src, n_trg))) {
             const FftBatches bt = fft_batches(order, octets(l, n_src), octets(l, n_trg));
             q = std::max(q, align_up(bt.q_bytes, 256));
             v = std::max(v, bt.v_bytes);
@@ -2010,7 +2011,7 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
             });
             return chk();
         };
-        const bool conv = conv_level(plan->order, dl, l, D, std::min(in.n_src, in.n_trg));
+        const bool conv = conv_level(plan->order, dl, l, D, std::max(in.n_src, in.n_trg));
         if (!conv && plan->order < kDenseOrder) {
             const Columns c = targets(l);
             M2LArgs g{};

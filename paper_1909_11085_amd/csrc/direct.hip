@@ -611,7 +611,7 @@ __global__ __launch_bounds__(kBlock) void direct_small(SumInputs in, double pref
             }
             pair_f64<KT, true>(r, x, y, z, excl && s_grp[j] == tg, u[0], u[1], u[2]);
         };
-        if constexpr (decltype(whole)::value) {
+        if constexpr (decltype(whole)::value || TW <= 4) {
 #pragma unroll 4
             for (int k = 0; k < TW; ++k) pair(k * H + h);
         } else {                               // no steps of padding alone
@@ -619,8 +619,8 @@ __global__ __launch_bounds__(kBlock) void direct_small(SumInputs in, double pref
         }
     };
     int64_t b = 0;
-    for (; n - b >= kBlock; b += kBlock) tile(b, std::true_type{});
-    if (b < n) tile(b, std::false_type{});
+    for (; b < (TW <= 4 ? n : n - kBlock + 1); b += kBlock) tile(b, std::true_type{});
+    if (b < n) tile(b, std::false_type{});     // (a few steps save nothing: TW > 4)
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < 3; ++c) s_src[c][tid] = u[c];

@@ -132,8 +132,10 @@ int stokes_version(void);
 
 /* Launch-shape override for tests: number of workgroups of the direct sums
  * (0 = automatic, the number resident on the device at once; at most 2^20).
- * Changes the work partition and the workspace size only; FP64 results stay
- * within the same error bound.  Not thread-safe against running calls. */
+ * Changes the work partition and the workspace size only, and takes small
+ * float64 calls, which run as one kernel otherwise, to the kernels that it
+ * cuts; FP64 results stay within the same error bound.  Not thread-safe
+ * against running calls. */
 int stokes_set_grid_override(stokes_ctx* ctx, int32_t workgroups);
 
 /* Each-pair-once evaluation of shared point sets (on by default).  When a
@@ -143,8 +145,9 @@ int stokes_set_grid_override(stokes_ctx* ctx, int32_t workgroups);
  * Stokeslet's symmetry S(x, y) = S(y, x) lets every unordered pair be
  * evaluated once for both of its points (float64).  on = 0 makes such calls
  * evaluate each ordered pair separately, as for distinct point sets (tests,
- * benchmarks).  Results agree within the float64 bound either way.  Not
- * thread-safe against running calls. */
+ * benchmarks).  Calls small enough for one kernel (up to some 5,000 points) take
+ * it either way, which evaluates each ordered pair.  Results agree within the
+ * float64 bound either way.  Not thread-safe against running calls. */
 int stokes_set_pair_symmetry(stokes_ctx* ctx, int32_t on);
 
 /* Test-only record of the mixed-precision split (float32 pairs, float64 near
@@ -210,13 +213,15 @@ int stokes_sl_eval(stokes_ctx* ctx, int64_t n_src, const double* src_xyz, const 
  * and launch shape of stokes_sl_eval with pair symmetry off, so bitwise its
  * values then), also on shared point sets.
  * The call allocates nothing: no hipMalloc, hipFree or allocating library
- * routine.  Sizes whose scratch (stokes_workspace_size with STOKES_OP_SL)
- * exceeds the array are rejected with STOKES_EWORKSPACE before any launch:
- * on a device with 256 compute units, about 230,000 sources and targets each
- * (a shared point set) in float64 and 300,000 in mixed precision.  All calls on one GPU share its array: two calls
- * whose executions overlap on that GPU (from other streams, threads or
- * contexts) race and may both return wrong results; order them on one
- * stream.  Nothing in the array needs to start at zero: every call writes all
+ * routine.  Sizes whose packed records, partial sums of 3 (float64) or 4
+ * (mixed) workgroups per compute unit and four near-pass rows exceed the array
+ * are rejected with STOKES_EWORKSPACE before any launch: on a device with 256
+ * compute units, above about 230,000 sources and targets each (a shared point
+ * set) in float64 and 300,000 in mixed precision.  At the sizes it accepts,
+ * stokes_sl_eval with pair symmetry off needs no more than the array either.
+ * All calls on one GPU share its array: two calls whose executions overlap on
+ * that GPU (from other streams, threads or contexts) race and may both return
+ * wrong results; order them on one stream.  Nothing in the array needs to start at zero: every call writes all
  * of the scratch it reads. */
 #define STOKES_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 int stokes_sl_eval_noalloc(stokes_ctx* ctx, int64_t n_src, const double* src_xyz,

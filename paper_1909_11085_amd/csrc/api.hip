@@ -204,6 +204,17 @@ stokes::SumInputs make_inputs(int kernel, const Parsed& p, int64_t n_src, const 
     return in;
 }
 
+// The plan of a direct sum.  Where the no-allocation entry point accepts a
+// single-layer call's sizes, the plan keeps to its scratch array, so that both entry
+// points cut the work alike (and give the same bits).
+stokes::DirectPlan direct_plan(const stokes_ctx* ctx, int kernel, int mixed, int64_t n_src, int64_t n_trg) {
+    const size_t scratch = (size_t)STOKES_NOALLOC_SCRATCH_BYTES;
+    const bool fits = kernel == STOKES_KERNEL_SL && stokes::direct_scratch_measure(kernel, mixed, n_src, n_trg, ctx->n_cu,
+                                                                                   ctx->forced_grid) <= scratch;
+    return stokes::plan_direct(kernel, mixed, n_src, n_trg, ctx->resident[kernel][mixed], ctx->forced_grid,
+                               fits ? scratch : 0);
+}
+
 // Whether a direct sum runs as the one kernel of small calls (a forced
 // workgroup count asks for the kernels that it cuts).
 bool small_sum(const stokes_ctx* ctx, const stokes::SumInputs& in) {
@@ -576,8 +587,7 @@ int stokes_workspace_size(const stokes_ctx* ctx, int32_t op, int64_t n_src, int6
         case STOKES_OP_DL: {
             if (n_src == 0 || n_trg == 0) { *bytes = 0; return STOKES_OK; }
             const int k = op == STOKES_OP_SL ? 0 : 1;
-            *bytes = stokes::plan_direct(k, mixed, n_src, n_trg, ctx->resident[k][mixed],
-                                         ctx->forced_grid).total;
+            *bytes = direct_plan(ctx, k, mixed, n_src, n_trg).total;
             // equal sizes may be a shared point set: room for the each-pair-once sum
             if (sym_available(ctx, k, mixed, n_src, n_trg))
                 *bytes = std::max(*bytes, stokes::plan_sym(0, n_src, ctx->sym_resident, ctx->forced_grid).total);
@@ -612,8 +622,7 @@ static int direct_eval(stokes_ctx* ctx, int kernel, int64_t n_src, const double*
                        const double* density, const double* weight, const double* normal,
                        int64_t n_trg, const double* trg_xyz, double pref,
                        const stokes_exclusion* excl, const stokes_opts* opts, double* vel_out,
-                       void* workspace, size_t ws_bytes, void* stream, bool allow_sym = true,
-                       size_t plan_limit = 0) {
+                       void* workspace, size_t ws_bytes, void* stream, bool allow_sym = true) {
     if (!ctx) return fail(STOKES_EINVAL, "ctx is NULL");
     int rc = check_sizes(n_src, n_trg);
     if (rc) return rc;
@@ -632,8 +641,7 @@ static int direct_eval(stokes_ctx* ctx, int kernel, int64_t n_src, const double*
     stokes::DirectPlan plan{};
     size_t need = 0;
     if (n_src > 0 && n_trg > 0) {
-        plan = stokes::plan_direct(kernel, mixed, n_src, n_trg, ctx->resident[kernel][mixed],
-                                   ctx->forced_grid, plan_limit);
+        plan = direct_plan(ctx, kernel, mixed, n_src, n_trg);
         need = plan.total;
     }
     rc = check_workspace(workspace, ws_bytes, need);
@@ -699,8 +707,7 @@ int stokes_sl_eval_noalloc(stokes_ctx* ctx, int64_t n_src, const double* src_xyz
                                                 "array: ") + hipGetErrorString(ctx->scratch_status));
     return direct_eval(ctx, STOKES_KERNEL_SL, n_src, src_xyz, density, weight, nullptr, n_trg, trg_xyz,
                        1.0 / (8.0 * kPi * mu), excl, opts, vel_out, ctx->scratch,
-                       (size_t)STOKES_NOALLOC_SCRATCH_BYTES, stream, /*allow_sym=*/false,
-                       /*plan_limit=*/(size_t)STOKES_NOALLOC_SCRATCH_BYTES);
+                       (size_t)STOKES_NOALLOC_SCRATCH_BYTES, stream, /*allow_sym=*/false);
 }
 
 int stokes_dl_eval(stokes_ctx* ctx, int64_t n_src, const double* src_xyz, const double* density,

@@ -98,7 +98,7 @@ struct DirectPlan {
 int direct_blocks_per_cu(int kernel, int mixed);
 
 // resident_blocks: workgroups resident on the whole device; forced_grid > 0
-// overrides it (tests); max_bytes > 0: workgroups and near-pass rows are given
+// overrides it (tests); max_bytes > 0: near-pass rows and workgroups are given
 // up where the workspace would be larger.
 DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int resident_blocks,
                        int forced_grid, size_t max_bytes = 0);

@@ -796,14 +796,18 @@ DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int 
         p.total = align_up(p.off_near + (size_t)slices * p.blocks_x * 3 * bt * sizeof(double), 256);
     };
     partials(std::min(g, subs * p.blocks_x), mixed ? near_slices(p.blocks_x, subs) : 0);
-    // few near-pass rows, no more workgroups than 256-source chunks, and half the
-    // workgroups where the partial sums would not fit; the first two also for the
-    // small calls that run as one kernel
+    // few near-pass rows and no more workgroups than 256-source chunks where the
+    // partial sums would not fit, and for the small calls that run as one kernel; then
+    // as many workgroups as fit
     const int64_t whole = std::min(g, chunks * p.blocks_x);
     const int rows = mixed ? (int)std::min<int64_t>(kNearSlices, subs) : 0;
     if ((max_bytes > 0 && p.total > max_bytes) || direct_is_small(mixed, n_src, n_trg))
         partials(whole, rows);
-    if (max_bytes > 0 && p.total > max_bytes) partials(std::min(whole, std::max<int64_t>(1, g / 2)), rows);
+    if (max_bytes > 0 && p.total > max_bytes) {
+        const size_t row = 3 * bt * sizeof(double), fixed = p.off_part + 512 + (size_t)rows * p.blocks_x * row;
+        const int64_t fit = fixed < max_bytes ? (int64_t)((max_bytes - fixed) / row) - p.blocks_x : 1;
+        partials(std::max<int64_t>(1, std::min(whole, fit)), rows);
+    }
     return p;
 }
 

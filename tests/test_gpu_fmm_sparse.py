@@ -96,6 +96,18 @@ def test_batches_of_planes_and_targets(kernel):
     _check(kernel, 4, 7, src, trg, 10, zero=pad)
 
 
+@pytest.mark.parametrize("pad", [3000, 60_000])
+def test_exact_product_in_parts_and_whole(pad):
+    """Order 6, double layer, depth 5: up to 16,384 leaves holding targets the exact pseudo-inverse product
+    splits its sums, beyond it does not (60,000 points hold about 27,000); 4,096 points and more make the
+    leaves a convolution."""
+    rng = np.random.default_rng(12)
+    near = lambda n: -0.7 + 0.4 * rng.uniform(0, 1, (3, n))
+    src = np.concatenate([near(25), rng.uniform(0.5, 1, (3, 5)), rng.uniform(-1, 1, (3, pad + 1200))], axis=1)
+    trg = np.concatenate([near(20), rng.uniform(0.4, 1, (3, 10)), rng.uniform(-1, 1, (3, pad + 1200))], axis=1)
+    _check("dl", 6, 5, src, trg, 13, zero=pad + 1200)
+
+
 def _best_ms(call):
     call()
     torch.cuda.synchronize()

@@ -22,7 +22,7 @@
 //     registers.  Mixed precision evaluates pairs in float32
 //     on offsets from the sub-tile centre (each rounded once from float64),
 //     sums each sub-tile in float32 and adds it into float64 accumulators.
-//     In the near pass (possible exclusions or near pairs, or a gap below half
+//     In the near pass (possible exclusions or near pairs, or a gap below an eighth of
 //     the sub-tile's extent) r is formed from float32 high parts plus float32
 //     residues, and pairs within the near radius are evaluated in float64.
 //   * work balance (stream-K): the grid holds exactly the resident number of

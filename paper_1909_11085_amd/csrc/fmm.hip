@@ -76,11 +76,12 @@ constexpr int64_t kFMaxGrid = 1 << 16;
 // orders of the same sums give outputs that differ by 2e-9 at order 6 for the
 // single layer (changing the dense products' K splits alone moves them by
 // 1.6e-9), 1e-10 at order 5 and 2e-12 at order 4, of outputs that are within
-// 1e-4, 5e-4 and 2e-3 of the direct sums.  Results move by less than 1e-9 so.
-// The double layer at order 6 takes the convolution at the leaves alone, with
-// the rounding of their pseudo-inverse product taken out: at all levels it moved
-// results by up to 1.07e-9 (114 walls of 2e4 to 1e6 nodes at 60 to 960 cells),
-// at the leaves by up to 9.8e-10 (200 of them, the worst sizes among them).
+// 1e-4, 5e-4 and 2e-3 of the direct sums.  So the line is not one of accuracy: it
+// keeps results within about 1e-9 of those of the dense products.  For the same
+// reason the double layer at order 6 takes the convolution at the leaves alone,
+// with the rounding of their pseudo-inverse product taken out: measured, not
+// bounded, it moves results by up to 9.8e-10 there (200 walls of 2e4 to 1e6 nodes at
+// 60 to 960 cells, the worst sizes among them), by up to 1.07e-9 at all levels (114).
 // 1,048,576 nodes at 522,240 points: 15.1 ms without, 10.3 with, 7.5 at all levels.
 constexpr int kDenseOrder = 6, kLeafConvOrderDL = 6;
 static_assert(kDenseOrder - 1 <= kFftMaxOrder && kLeafConvOrderDL <= kFftMaxOrder, "orders with convolution levels");
@@ -695,7 +696,6 @@ constexpr int kM2LUnits = 4096;      // work units a level's M2L aims for (K is 
 constexpr double kM2LDenseFill = 0.35;   // below this interaction-list fill, M2L runs as pair sums
 constexpr int kILCountParts = 2048;      // workgroups (partial counts) of the interaction-list count
 constexpr int64_t kM2LPairBlocks = 8192;   // workgroups of a pair-sum level at most (most levels have none)
-constexpr int kM2LPerClass = 32;      // workgroups per class and row group: 256 CUs in 8 classes
 constexpr int kM2LMinSplits = 3;     // so that a split has at most kM2LMaxSplitBlocks blocks
 constexpr int kM2LMaxSplitBlocks = (kILSize + 1 + kM2LMinSplits - 1) / kM2LMinSplits;
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -1391,13 +1391,16 @@ void with_T(int T, F&& f) {
     }
 }
 static_assert(kMaxT == 8, "with_T covers 1 .. kMaxT");
-template <typename F>
+template <bool DENSE, typename F>           // DENSE: the orders from kDenseOrder on
 bool with_rb(int rb, F&& f) {
-    switch (rb) {                       // orders 2 .. 10: mp / 16 = 2, 5, 11, 19, 29, 41, 56, 73, 92
+    if constexpr (!DENSE) switch (rb) {     // orders 2 .. 10: mp / 16 = 2, 5, 11, 19, 29, 41, 56, 73, 92
         case 2: f(std::integral_constant<int, 2>{}); return true;
         case 5: f(std::integral_constant<int, 5>{}); return true;
         case 11: f(std::integral_constant<int, 11>{}); return true;
         case 19: f(std::integral_constant<int, 19>{}); return true;
+        default: break;
+    }
+    switch (rb) {
         case 21: f(std::integral_constant<int, 21>{}); return true;    // 41 in 2 groups
         case 23: f(std::integral_constant<int, 23>{}); return true;    // 92 in 4
         case 25: f(std::integral_constant<int, 25>{}); return true;    // 73 in 3
@@ -1946,7 +1949,7 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
         const dim3 g((unsigned)(ngr * std::max<int64_t>(tiles_ub, per_split * kApplyUnits)));
         if (exact) {
             hipLaunchKernelGGL(apply_exact_kernel<kGemmMaxRB>, g, dim3(kGemmThreads), 0, st, a, c, op, out, apart);
-        } else if (!with_rb(rb, [&](auto r) {
+        } else if (!with_rb<false>(rb, [&](auto r) {
                        hipLaunchKernelGGL(apply_gemm_kernel<decltype(r)::value>, g, dim3(kGemmThreads), 0, st, a, c,
                                           op, out, apart);
                    })) {
@@ -2037,9 +2040,9 @@ hipError_t launch_fmm(const stokes_fmm_plan* plan, const FmmInputs& in, double* 
             hipLaunchKernelGGL(m2l_sched_kernel, dim3(1), dim3(kWave), 0, st, g2.cscan, g2.ctotal, l, g2.npairs, n_parts,
                                g2.sched);
             if (!chk()) break;
-            // classes x row groups x the CUs of an XCD; a workgroup's LDS fills a CU
-            const dim3 gm((unsigned)(8 * ngr * kM2LPerClass));
-            if (!with_rb(rb, [&](auto r) {
+            // classes x row groups x an eighth of the CUs; a workgroup's LDS fills a CU
+            const dim3 gm((unsigned)(8 * ngr * std::max(1, plan->cus / 8)));
+            if (!with_rb<true>(rb, [&](auto r) {
                     hipLaunchKernelGGL(m2l_gemm_kernel<decltype(r)::value>, gm, dim3(kGemmThreads), 0, st, a, g2, l);
                 })) {
                 e = hipErrorInvalidValue;                   // no GEMM instance for this order (not reached for 2..10)

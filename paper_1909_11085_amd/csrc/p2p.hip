@@ -983,9 +983,12 @@ __global__ __launch_bounds__(kP2PThreads) void p2p_item_slots(int64_t max_items,
     }
 }
 
-// The items of each leaf, in leaf and chunk order, with their cost keys: the
-// pair loop of an n-target item runs s/R steps over the s listed sources,
-// R = min(16, 64/n); the key is the inverted log-scale code of that cost, so
+// The items of each leaf, in leaf and chunk order, with their cost keys: with
+// one target per lane the pair loop of an n-target item runs s/R steps over the
+// s listed sources, R = min(16, 64/n) (the mixed kernel's form; the float64 one,
+// with several targets per lane, has more phases for 33 to 63 targets, and its
+// items of those sizes come earlier than their cost says, as a plan serves
+// both); the key is the inverted log-scale code of that cost, so
 // that an ascending stable sort puts the largest first (the host-built plan's
 // order up to costs within 2^-10 of each other, which keep leaf order).  The
 // order only schedules the items: each target's sum is one item's.
@@ -1365,7 +1368,7 @@ int p2p_plan_build(int device, int32_t n_leaves, int64_t n_src, int64_t n_trg,
         pairs += nt * s;
         for (int64_t c = 0; c * kWave < nt; ++c) {
             if (c > INT32_MAX) { err = "leaf too large"; return STOKES_EUNSUPPORTED; }
-            // the pair loop of an n-target item runs s/R steps, R = min(16, 64/n)
+            // with one target per lane an n-target item runs s/R steps, R = min(16, 64/n) (see p2p_csr_items)
             const int64_t n_c = std::min<int64_t>(kWave, nt - c * kWave);
             const int64_t rep = std::min<int64_t>(kMaxRep, kWave / n_c);
             items.push_back({s * 64 / rep + s + 1, L, (int32_t)c});

@@ -2,7 +2,7 @@
 //
 // A pass sums, for every target, a pair function over all sources (minus the
 // same-group and zero-distance pairs), into NACC float64 accumulators.  The
-// layout and scheduling are those of the direct sums:
+// layout is that of the direct sums; units and near pass are this file's own:
 //   * prep: one thread per source builds a packed record (policy-defined) and
 //     each wave summarises its 64-source sub-tile (box, group range);
 //   * main: stream-K split of (target block x 256-source chunk) units over

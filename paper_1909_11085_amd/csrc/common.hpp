@@ -90,6 +90,7 @@ struct DirectPlan {
     int64_t units;               // blocks_x * n_sub
     int64_t grid;                // workgroups (resident count, at most units)
     int cut;                     // units that a workgroup's range begins at multiples of
+    int64_t step;                // 256-source chunks from one to the next that a range takes (float64)
     int near_slices;             // grid rows of the near pass
     size_t off_src, off_grp, off_meta, off_part, off_near, total;
 };

@@ -36,6 +36,7 @@
 #include <float.h>
 #include <limits.h>
 
+#include <numeric>
 #include <type_traits>
 
 #include "direct_dev.hpp"
@@ -50,6 +51,7 @@ struct DirectArgs {
     int64_t n_sub;            // source sub-tiles
     int64_t units;            // target blocks x sub-tiles
     int cut;                  // ranges begin at multiples of this many units
+    int64_t step;             // float64: a target block takes chunk k * step mod (chunks) k-th
     double* part;             // partial sums, one segment per (block, target block) pair
     double* near_part;        // near-pass sums, (near slices, 3, blocks_x * kBlock * T)
 };
@@ -190,7 +192,9 @@ constexpr int kT64Long = 8, kW64Long = 2;
 // compares and select add about a fifth to a pair, where a pass of its own finds
 // them again and brings its own partial sums (6.4e7 double-layer pairs of a
 // check-point quadrature 197 us with such a pass, 141 here; 16,001 tracers at
-// 34,816 sources 550 and 428, 60,001 at 108,800 4.94 and 4.65 ms).
+// 34,816 sources 550 and 428, 60,001 at 108,800 4.94 and 4.65 ms).  Where targets
+// lie among their own sources those sub-tiles follow each other, so a range takes
+// its chunks spread over all sources (see spread_step).
 template <int KT, int T>
 __global__ __launch_bounds__(kBlock, T == kT64Long ? kW64Long : STOKES_DIRECT_W64) void direct_f64(DirectArgs a) {
     using Rec = typename SrcRec<KT, 0>::type;
@@ -216,6 +220,8 @@ __global__ __launch_bounds__(kBlock, T == kT64Long ? kW64Long : STOKES_DIRECT_W6
     for (int k = 0; k < T; ++k) ax[k] = ay[k] = az[k] = 0.0;
 
     int64_t ub = u0 / C, sub = u0 % C;         // unit position, advanced by up to four sub-tiles
+    const int64_t chunks = (C + 3) >> 2;
+    int64_t chunk = (sub >> 2) * a.step % chunks;
     for (int64_t u = u0; u < u1;) {
         const int s0 = (int)(sub & 3), s1 = (int)min((int64_t)4, s0 + min(u1 - u, C - sub));
         __syncthreads();                       // previous step's readers are done
@@ -229,7 +235,7 @@ __global__ __launch_bounds__(kBlock, T == kT64Long ? kW64Long : STOKES_DIRECT_W6
 #pragma unroll
             for (int k = 0; k < T; ++k) ax[k] = ay[k] = az[k] = 0.0;
         }
-        const int64_t first = sub - s0;        // the chunk's first sub-tile
+        const int64_t first = chunk * 4;       // the chunk's first sub-tile
         if (wave >= s0 && wave < s1) {
             s_rec[threadIdx.x] = rec[first * kSub + threadIdx.x];
             s_grp[threadIdx.x] = grp[first * kSub + threadIdx.x];
@@ -263,7 +269,8 @@ __global__ __launch_bounds__(kBlock, T == kT64Long ? kW64Long : STOKES_DIRECT_W6
         }
         u += s1 - s0;
         sub += s1 - s0;
-        if (sub == C) { sub = 0; ++ub; }
+        if (sub == C) { sub = chunk = 0; ++ub; }
+        else if ((sub & 3) == 0 && (chunk += a.step) >= chunks) chunk -= chunks;
     }
     flush_segment<T>(a, tbk, wave, lane, ax, ay, az);
 }
@@ -764,6 +771,18 @@ static int targets_per_lane(int kernel, int mixed, int64_t n_src, int64_t n_trg)
 // Workgroups with at least this many 256-source chunks each take whole chunks.
 constexpr int64_t kWholeChunks = 16;
 
+// Step through a target block's n chunks that deals any run of them evenly to its
+// ranges: coprime to n, near its golden section.  Check points lie in the boxes of
+// their own patch's sources, so one range of eight had the block's masked sub-tiles;
+// a boundary product of 6,144 nodes (98,304 sources at 55,296 check points) 5.78 ms
+// in order, 4.86 so; of 13,824 nodes (2.75e10 pairs) 24.2 and 22.6; sources and
+// targets apart, 98,304 at 55,296, 4.44 and 4.47.
+static int64_t spread_step(int64_t n) {
+    int64_t s = std::max<int64_t>(1, (int64_t)(0.618034 * (double)n));
+    while (std::gcd(s, n) != 1) ++s;
+    return s;
+}
+
 DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int resident_blocks,
                        int forced_grid, size_t max_bytes) {
     DirectPlan p{};
@@ -791,6 +810,7 @@ DirectPlan plan_direct(int kernel, int mixed, int64_t n_src, int64_t n_trg, int 
         p.near_slices = slices;
         p.cut = chunks * p.blocks_x >= kWholeChunks * p.grid ? kTile / kSub : 1;
         p.n_sub = p.cut > 1 ? p.n_src_pad / kSub : subs;
+        p.step = p.cut > 1 && !mixed ? spread_step(chunks) : 1;
         p.units = p.n_sub * p.blocks_x;
         p.off_near = align_up(p.off_part + (size_t)(p.grid + p.blocks_x) * 3 * bt * sizeof(double), 256);
         p.total = align_up(p.off_near + (size_t)slices * p.blocks_x * 3 * bt * sizeof(double), 256);
@@ -844,6 +864,7 @@ static hipError_t launch_typed(const SumInputs& in, const DirectPlan& p, double*
     a.n_sub = p.n_sub;
     a.units = p.units;
     a.cut = p.cut;
+    a.step = p.step;
     a.part = reinterpret_cast<double*>(base + p.off_part);
     a.near_part = reinterpret_cast<double*>(base + p.off_near);
     if (timer.on()) (void)hipEventRecord(timer.start, stream);

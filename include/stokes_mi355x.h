@@ -206,23 +206,22 @@ int stokes_sl_eval(stokes_ctx* ctx, int64_t n_src, const double* src_xyz, const 
 /* For callers that cannot allocate device memory or pass a workspace (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation): stokes_sl_eval with its scratch in a library-owned static
- * device array of STOKES_NOALLOC_SCRATCH_BYTES (64 MiB) instead of a caller
- * workspace.  Every GPU that the library runs on holds one such array for the
+ * device array instead of a caller workspace.  Every GPU that the library runs on holds one such array for the
  * life of the process.  Arguments, results and errors otherwise as
  * stokes_sl_eval; every ordered pair is evaluated separately (the kernels
  * and launch shape of stokes_sl_eval with pair symmetry off, so bitwise its
  * values then), also on shared point sets.
  * The call allocates nothing: no hipMalloc, hipFree or allocating library
  * routine.  Sizes whose packed records, partial sums of 3 (float64) or 4
- * (mixed) workgroups per compute unit and four near-pass rows exceed the array
- * are rejected with STOKES_EWORKSPACE before any launch: on a device with 256
- * compute units, above about 230,000 sources and targets each (a shared point
- * set) in float64 and 300,000 in mixed precision.  At the sizes it accepts,
- * stokes_sl_eval with pair symmetry off needs no more than the array either.
- * All calls on one GPU share its array: two calls whose executions overlap on
- * that GPU (from other streams, threads or contexts) race and may both return
- * wrong results; order them on one stream.  Nothing in the array needs to start at zero: every call writes all
- * of the scratch it reads. */
+ * (mixed) workgroups per compute unit and four near-pass rows exceed
+ * STOKES_NOALLOC_SCRATCH_BYTES (64 MiB) are rejected with STOKES_EWORKSPACE
+ * before any launch: on a device with 256 compute units, above about 230,000
+ * sources and targets each (a shared point set) in float64 and 300,000 in mixed
+ * precision.  The array is 32 MiB larger, so that it holds those sizes with all
+ * workgroups.  All calls on one GPU share it: two calls whose executions overlap
+ * on that GPU (from other streams, threads or contexts) race and may both return
+ * wrong results; order them on one stream.  Nothing in the array needs to start
+ * at zero: every call writes all of the scratch it reads. */
 #define STOKES_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 int stokes_sl_eval_noalloc(stokes_ctx* ctx, int64_t n_src, const double* src_xyz,
                            const double* density, const double* weight, int64_t n_trg,

@@ -67,7 +67,11 @@ KernelTimer next_timer(stokes_ctx* ctx) {
 // this name is not a device address: stokes_create takes the address of the
 // current device's copy with hipGetSymbolAddress and keeps it in the context,
 // and only that address reaches kernels.
-static __device__ __align__(256) unsigned char scratch[STOKES_NOALLOC_SCRATCH_BYTES];
+// Sizes are accepted by direct_scratch_measure; beyond it the array holds what
+// their full plans take: up to 8 workgroups per CU instead of 3 or 4 and 1,024
+// (near-pass row, target block) pairs, 12 KB each in mixed precision, 256 CUs.
+constexpr size_t kScratchBytes = STOKES_NOALLOC_SCRATCH_BYTES + ((size_t)32 << 20);
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 
@@ -206,13 +210,14 @@ stokes::SumInputs make_inputs(int kernel, const Parsed& p, int64_t n_src, const 
 
 // The plan of a direct sum.  Where the no-allocation entry point accepts a
 // single-layer call's sizes, the plan keeps to its scratch array, so that both entry
-// points cut the work alike (and give the same bits).
+// points cut the work alike (and give the same bits).  Only a forced workgroup count
+// makes plans that the array does not hold.
 stokes::DirectPlan direct_plan(const stokes_ctx* ctx, int kernel, int mixed, int64_t n_src, int64_t n_trg) {
-    const size_t scratch = (size_t)STOKES_NOALLOC_SCRATCH_BYTES;
     const bool fits = kernel == STOKES_KERNEL_SL && stokes::direct_scratch_measure(kernel, mixed, n_src, n_trg, ctx->n_cu,
-                                                                                   ctx->forced_grid) <= scratch;
+                                                                                   ctx->forced_grid) <=
+                          (size_t)STOKES_NOALLOC_SCRATCH_BYTES;
     return stokes::plan_direct(kernel, mixed, n_src, n_trg, ctx->resident[kernel][mixed], ctx->forced_grid,
-                               fits ? scratch : 0);
+                               fits ? kScratchBytes : 0);
 }
 
 // Whether a direct sum runs as the one kernel of small calls (a forced
@@ -707,7 +712,7 @@ int stokes_sl_eval_noalloc(stokes_ctx* ctx, int64_t n_src, const double* src_xyz
                                                 "array: ") + hipGetErrorString(ctx->scratch_status));
     return direct_eval(ctx, STOKES_KERNEL_SL, n_src, src_xyz, density, weight, nullptr, n_trg, trg_xyz,
                        1.0 / (8.0 * kPi * mu), excl, opts, vel_out, ctx->scratch,
-                       (size_t)STOKES_NOALLOC_SCRATCH_BYTES, stream, /*allow_sym=*/false);
+                       kScratchBytes, stream, /*allow_sym=*/false);
 }
 
 int stokes_dl_eval(stokes_ctx* ctx, int64_t n_src, const double* src_xyz, const double* density,

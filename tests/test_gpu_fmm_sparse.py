@@ -108,6 +108,30 @@ def test_exact_product_in_parts_and_whole(pad):
     _check("dl", 6, 5, src, trg, 13, zero=pad + 1200)
 
 
+def test_exact_product_has_no_rounding():
+    """The same targets, one in every octet, alone (4,096 leaves, the exact product's sums split) and with others
+    in 20,480 more leaves (not split): all upper levels and the leaves' check vectors are the same bits, so only
+    the order of that product's sums differs.  What it leaves in float64 is 2^-21 of a plain product's rounding
+    (which moves results by up to 1e-9) and one rounding of the densities: 1e-12 is a hundred times that."""
+    rng = np.random.default_rng(14)
+    n = 16
+    cell = np.stack(np.meshgrid(*[np.arange(n)] * 3, indexing="ij")).reshape(3, -1)
+    src = -1.0 + (cell + rng.uniform(0.01, 0.99, cell.shape)) * (2.0 / n)
+    own = -1.0 + (cell + rng.uniform(0.01, 0.49, cell.shape)) * (2.0 / n)
+    more = [own]
+    for child in range(3, 8):
+        half = 0.5 * np.array([child & 1, child >> 1 & 1, child >> 2])[:, None]
+        more.append(-1.0 + (cell + half + 0.25) * (2.0 / n))
+    f, w, nrm = rng.standard_normal(src.shape), rng.uniform(0.5, 1.0, src.shape[1]), rng.standard_normal(src.shape)
+    nrm /= np.linalg.norm(nrm, axis=0)
+    args = _plan(6), dev(src), dev(f), dev(w), dev(nrm)
+    cube = ((0.0, 0.0, 0.0), 1.0, 5)
+    split = host(S.fmm_dl(*args, dev(own), *cube))
+    whole = host(S.fmm_dl(*args, dev(np.concatenate(more, axis=1)), *cube))[:, : own.shape[1]]
+    e = rel_l2(split, whole)
+    assert e < 1e-12, e
+
+
 def _best_ms(call):
     call()
     torch.cuda.synchronize()

@@ -27,7 +27,8 @@
 //     residues, and pairs within the near radius are evaluated in float64.
 //   * work balance (stream-K): the grid holds exactly the resident number of
 //     workgroups; the (target block x 64-source sub-tile) units are cut into
-//     equal contiguous ranges, one per workgroup.  A workgroup flushes float64
+//     equal contiguous ranges, one per workgroup (long float64 ranges count a
+//     target block's chunks in an order of their own).  A workgroup flushes float64
 //     partial sums whenever its range moves to a new target block; segment
 //     ids (workgroup + target block) are consecutive, and a second kernel
 //     adds each target's segments in fixed order (deterministic, no atomics).
